@@ -13,6 +13,7 @@
 // block partials are summed by a second kernel in a fixed order, so the result does not depend on
 // scheduling.
 #include "mrmf_internal.h"
+#include "reduce.h"
 
 namespace mrmf {
 namespace {
@@ -34,29 +35,6 @@ __device__ __forceinline__ uint32_t div_magic32(uint32_t n, uint64_t magic) {
 // Re conj(t) x_F of each run of consecutive terms with one parameter are summed per lane, then over the
 // wave with a fixed butterfly, and added by lane 0 to the wave's accumulator in LDS: the per-parameter
 // state is one double per wave instead of one per thread, which keeps the occupancy of the gather high.
-// v moved across lanes by one DPP pattern (rows outside row_mask contribute 0), one 32-bit half at a time
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_move(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u)), CTRL, ROW_MASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u >> 32)), CTRL, ROW_MASK, 0xf,
-                                               false);
-    return __builtin_bit_cast(double, (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) |
-                                          static_cast<uint64_t>(static_cast<uint32_t>(lo)));
-}
-
-// Sum over the 64 lanes of a wave with a fixed pattern of DPP moves (lane pairs 1 and 2 apart, the half
-// and full row mirrors, then the row broadcasts of lanes 15 and 31); the total ends in lane 63.
-__device__ __forceinline__ double wave_sum(double v) {
-    v += dpp_move<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
-    v += dpp_move<0x4E, 0xf>(v);   // quad_perm [2, 3, 0, 1]
-    v += dpp_move<0x141, 0xf>(v);  // row_half_mirror
-    v += dpp_move<0x140, 0xf>(v);  // row_mirror: every lane holds its row's sum
-    v += dpp_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v += dpp_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-    return v;                      // lane 63: the wave's sum
-}
-
 template <bool WIDE, bool LDS_TAB, int R>
 __global__ __launch_bounds__(kAdjBlock) void k_adjoint(PlanArgs p, const AdjTerm* __restrict__ terms, int n_terms,
                                                        const double* __restrict__ ftab_g, int n_ftab,

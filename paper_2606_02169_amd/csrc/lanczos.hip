@@ -1,7 +1,8 @@
 // Device-resident Lanczos eigensolver driving the matrix-free map (the Krylov use of x -> H x, Sec. I)
 // and the FP64 vector reductions it needs.  Every scalar of the recurrence (alpha_j, beta_j, the Gram-
 // Schmidt coefficients, the Ritz value) stays in device memory; the host only enqueues kernels.  After a
-// breakdown every later kernel of the call sees the `stopped` flag and returns at once.
+// breakdown every later kernel of the call sees its step's halt flag and returns at once.
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 
@@ -12,39 +13,50 @@ namespace mrmf {
 namespace {
 
 constexpr int kRB = 256;            // threads per reduction block
-constexpr int kMaxRedBlocks = 512;  // first-stage partials per reduction
+constexpr int kMaxRedBlocks = 512;  // first-stage partials of mrmf_dot_z / mrmf_norm_z
+constexpr int kVecBlocks = 1024;    // first-stage partials of the recurrence's vector kernels
 constexpr int kGroup = 8;           // basis vectors per Gram-Schmidt block
 
+// Scalars of a call.  `halt` (one flag per step, in the scratch after this struct) says whether step j runs at
+// all: the kernel that ends step j writes halt[j + 1], so no kernel reads a flag that another block of the same
+// launch writes.
 struct LzState {
-    int32_t stopped;  // recurrence ended (breakdown, zero start vector, or last step done)
-    int32_t steps;    // k: number of alpha_j computed
+    int32_t steps;     // k: number of alpha_j computed
     int32_t breakdown;
-    int32_t skip2;    // conditional Gram-Schmidt: the second pass of this step is skipped (or stopped)
-    double tnorm;  // Gershgorin estimate of ||T|| so far
-    double nrm0;   // ||v0||
-    double theta;  // lowest Ritz value
-    double wn2;    // conditional Gram-Schmidt: ||w||^2 before the first pass
     int32_t n_second;  // conditional Gram-Schmidt: second passes taken so far
     int32_t n_pro;     // partial reorthogonalisation: full Gram-Schmidt passes taken so far
-    int32_t skip_pro;  // partial reorthogonalisation: this step's pass (and its norm) is skipped
+    int32_t skip2;     // full and conditional Gram-Schmidt: this step's immediate second pass is skipped
+    int32_t skip_pro;  // partial reorthogonalisation: this step's pass is skipped
     int32_t force;     // partial reorthogonalisation: the next step reorthogonalises as well
-    double unrm;       // ||V s|| of the Ritz vector before it is normalised
-    int32_t skip_u;    // the Ritz vector is zero (no step taken): left as it is
     int32_t pad;
+    double theta;      // lowest Ritz value
 };
 
-int red_blocks(int64_t n) {
+int red_blocks(int64_t n, int most) {
     const int64_t b = (n + kRB - 1) / kRB;
-    return static_cast<int>(b < kMaxRedBlocks ? (b < 1 ? 1 : b) : kMaxRedBlocks);
+    return static_cast<int>(b < most ? (b < 1 ? 1 : b) : most);
 }
+
+// Row blocks of a Gram-Schmidt inner-product launch over k vectors: groups of kGroup vectors are blocks of
+// their own, so many vectors need fewer row blocks to fill the GPU, and the partial sums stay within
+// gs_partials() entries.
+int gs_blocks(int64_t n, int k) { return red_blocks(n, k <= 16 ? 1024 : k <= 32 ? 512 : 256); }
+size_t gs_partials(int32_t m) { return std::max<size_t>(size_t(32) * 512, size_t(m + 1) * 256); }
 
 __device__ __forceinline__ bool halted(const int32_t* stopped) { return stopped != nullptr && *stopped != 0; }
 
+// The sum of nb partial sums in a fixed order, in every thread of a block of kRB.  lds: kRB / 64 doubles; the
+// partials come from an earlier kernel, so a consumer sums them itself instead of waiting for a launch of one
+// thread that does (35 us for 512 partials read one after the other, against about 1 us here).
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nb, double* lds) {
+    double v[1] = {0.0};
+    for (int b = threadIdx.x; b < nb; b += kRB) v[0] += p[b];
+    return block_total<1>(v, lds);
+}
+
 // ---------------------------------------------------------------- first-stage reductions
 __global__ __launch_bounds__(kRB) void k_norm2_partial(int64_t n, const double2* __restrict__ a,
-                                                        double* __restrict__ partial,
-                                                        const int32_t* __restrict__ stopped) {
-    if (halted(stopped)) return;
+                                                        double* __restrict__ partial) {
     __shared__ double lds[kRB / 64];
     double v[1] = {0.0};
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
@@ -58,9 +70,7 @@ __global__ __launch_bounds__(kRB) void k_norm2_partial(int64_t n, const double2*
 // partial[b] = sum over the block's rows of conj(a) b
 __global__ __launch_bounds__(kRB) void k_dot_partial(int64_t n, const double2* __restrict__ a,
                                                       const double2* __restrict__ b,
-                                                      double2* __restrict__ partial,
-                                                      const int32_t* __restrict__ stopped) {
-    if (halted(stopped)) return;
+                                                      double2* __restrict__ partial) {
     __shared__ double lds[2 * kRB / 64];
     double v[2] = {0.0, 0.0};
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
@@ -72,22 +82,28 @@ __global__ __launch_bounds__(kRB) void k_dot_partial(int64_t n, const double2* _
     if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(v[0], v[1]);
 }
 
-// partial[b] = sum over the block's rows of conj(a) b for a c64 b (the c64 matvec's output, read as it is)
-__global__ __launch_bounds__(kRB) void k_dot_partial32(int64_t n, const double2* __restrict__ a,
-                                                        const float2* __restrict__ b,
-                                                        double2* __restrict__ partial,
+// partial[b] = sum over the block's rows of Re conj(v_j) H v_j; H v_j is w, or h32 for the c64 matvec's output
+__global__ __launch_bounds__(kRB) void k_alpha_partial(int64_t n, const double2* __restrict__ vj,
+                                                        const double2* __restrict__ w,
+                                                        const float2* __restrict__ h32,
+                                                        double* __restrict__ partial,
                                                         const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    __shared__ double lds[2 * kRB / 64];
-    double v[2] = {0.0, 0.0};
+    __shared__ double lds[kRB / 64];
+    double v[1] = {0.0};
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
-        const double2 x = a[i];
-        const float2 y = b[i];
-        v[0] += x.x * static_cast<double>(y.x) + x.y * static_cast<double>(y.y);
-        v[1] += x.x * static_cast<double>(y.y) - x.y * static_cast<double>(y.x);
+        const double2 x = vj[i];
+        double2 y;
+        if (h32) {
+            const float2 h = h32[i];
+            y = make_double2(h.x, h.y);
+        } else {
+            y = w[i];
+        }
+        v[0] += x.x * y.x + x.y * y.y;
     }
-    block_sum<2>(v, lds);
-    if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(v[0], v[1]);
+    block_sum<1>(v, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
 
 // ||hu - theta u||^2 partials
@@ -107,84 +123,225 @@ __global__ __launch_bounds__(kRB) void k_resid_partial(int64_t n, const double2*
     if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
 
-// Gram-Schmidt coefficients c_i = <V_i|w>, i = 0..k-1: partial[i * nb + block]
-__global__ __launch_bounds__(kRB) void k_gemvt_partial(int64_t n, const double2* __restrict__ V, int k,
-                                                        const double2* __restrict__ w,
-                                                        double2* __restrict__ partial, int nb,
-                                                        const int32_t* __restrict__ stopped) {
-    if (halted(stopped)) return;
-    __shared__ double lds[2 * kGroup * kRB / 64];
+// ---------------------------------------------------------------- Gram-Schmidt
+// Whether a Gram-Schmidt kernel runs.  stopped: the step's halt flag, or the flag of a pass that may be skipped
+// (then *stopped != 0 skips it).  A second pass decides by itself, in its first kernel (k_gs_dots with pre set):
+// it runs when the first one left ||w||^2 below half its value before (Daniel, Gragg, Kaufman and Stewart,
+// 1976), and block (0, 0) leaves the decision in st->skip2 for the two kernels after it.
+//
+// Inner products c_i = <V_i|w>, i < k (partial sums pc[i nb + block]); TWO: also s_i = <V_i|v> for i < k - 1,
+// the coefficients of the second pass of v = V_{k-1} (ps).  Bound by the reads of the basis: one read serves both
+// products, and the blocks of the other groups of kGroup vectors that read the same rows of w and v run at the
+// same time on the same XCD (blockIdx.x decides it), so those hit its L2.  On 10 million rows and 20 vectors on
+// average a pass over the basis takes 0.72 ms (5.3 TB/s, the GPU's copy rate), and a step of the full form two of
+// them instead of four (2 x 0.72 against 4 x 0.64 ms).
+template <bool TWO>
+__global__ __launch_bounds__(kRB) void k_gs_dots(int64_t n, const double2* __restrict__ V, int k,
+                                                  const double2* __restrict__ w, const double2* __restrict__ v,
+                                                  double2* __restrict__ pc, double2* __restrict__ ps, int nb,
+                                                  const double* __restrict__ pre, const double* __restrict__ post,
+                                                  int nbv, int count, LzState* __restrict__ st,
+                                                  const int32_t* __restrict__ stopped) {
+    constexpr int kV = (TWO ? 4 : 2) * kGroup;
+    __shared__ double lds[kV * kRB / 64];
+    if (pre != nullptr) {
+        const bool halt = halted(stopped);
+        const double before = halt ? 0.0 : sum_partials(pre, nbv, lds);
+        const double after = halt ? 0.0 : sum_partials(post, nbv, lds);
+        const bool skip = halt || after >= 0.5 * before;
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+            st->skip2 = skip;
+            if (!skip && count) ++st->n_second;
+        }
+        if (skip) return;
+    } else if (halted(stopped)) {
+        return;
+    }
     const int base = blockIdx.y * kGroup;
-    double v[2 * kGroup];
+    double a[kV];
 #pragma unroll
-    for (int g = 0; g < 2 * kGroup; ++g) v[g] = 0.0;
+    for (int g = 0; g < kV; ++g) a[g] = 0.0;
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(nb) * kRB) {
         const double2 y = w[i];
+        const double2 z = TWO ? v[i] : make_double2(0.0, 0.0);
+        double2 x[kGroup];
+#pragma unroll
+        for (int g = 0; g < kGroup; ++g)
+            x[g] = base + g < k ? V[int64_t(base + g) * n + i] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int g = 0; g < kGroup; ++g) {
-            if (base + g < k) {
-                const double2 x = V[int64_t(base + g) * n + i];
-                v[2 * g] += x.x * y.x + x.y * y.y;
-                v[2 * g + 1] += x.x * y.y - x.y * y.x;
+            a[2 * g] += x[g].x * y.x + x[g].y * y.y;
+            a[2 * g + 1] += x[g].x * y.y - x[g].y * y.x;
+            if (TWO) {
+                a[2 * kGroup + 2 * g] += x[g].x * z.x + x[g].y * z.y;
+                a[2 * kGroup + 2 * g + 1] += x[g].x * z.y - x[g].y * z.x;
             }
         }
     }
-    block_sum<2 * kGroup>(v, lds);
-    if (threadIdx.x == 0) {
-        for (int g = 0; g < kGroup; ++g)
-            if (base + g < k) partial[int64_t(base + g) * nb + blockIdx.x] = make_double2(v[2 * g], v[2 * g + 1]);
+    block_sum_lds<kV>(a, lds);
+    const int t = threadIdx.x;
+    if (t < kV / 2) {  // thread t: coefficient t mod kGroup of c (t < kGroup) or of s
+        const int g = t % kGroup;
+        double re = 0.0, im = 0.0;
+        for (int q = 0; q < kRB / 64; ++q) {
+            re += lds[q * kV + 2 * t];
+            im += lds[q * kV + 2 * t + 1];
+        }
+        if (base + g < k) (t < kGroup ? pc : ps)[int64_t(base + g) * nb + blockIdx.x] = make_double2(re, im);
     }
 }
 
-__global__ void k_gemvt_finalize(int k, int nb, const double2* __restrict__ partial, double2* __restrict__ c,
-                                 const int32_t* __restrict__ stopped) {
+// c_i (and s_i) from their partial sums: one wave per coefficient
+__global__ __launch_bounds__(64) void k_gs_finalize(int k, int nb, const double2* __restrict__ pc,
+                                                     const double2* __restrict__ ps, double2* __restrict__ c,
+                                                     double2* __restrict__ s, const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= k) return;
-    double sr = 0.0, si = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        sr += partial[int64_t(i) * nb + b].x;
-        si += partial[int64_t(i) * nb + b].y;
+    const int i = blockIdx.x % k;
+    const bool second = blockIdx.x >= static_cast<unsigned>(k);
+    const double2* p = (second ? ps : pc) + int64_t(i) * nb;
+    double v[2] = {0.0, 0.0};
+    for (int b = threadIdx.x; b < nb; b += 64) {
+        v[0] += p[b].x;
+        v[1] += p[b].y;
     }
-    c[i] = make_double2(sr, si);
+    wave_sum<2>(v);
+    if (threadIdx.x == 63) (second ? s : c)[i] = make_double2(v[0], v[1]);
 }
 
-// w = (zero ? 0 : w) + sgn * sum_{i<k} c_i V_i  (k read from kdev when given)
-__global__ __launch_bounds__(kRB) void k_gemv_acc(int64_t n, const double2* __restrict__ V, int k,
-                                                   const int32_t* __restrict__ kdev,
-                                                   const double2* __restrict__ c, double2* __restrict__ w,
-                                                   int zero, double sgn, const int32_t* __restrict__ stopped) {
+// w -= sum_{i<k} c_i V_i and the partial sums of the new ||w||^2; TWO: also v -= sum_{i<k-1} s_i V_i for
+// v = V_{k-1} (the second pass of v), in the same read of the basis.  nbs > 0: c and s come as nbs partial sums
+// each (few rows: summed here, which saves the launch of k_gs_finalize).  Coefficients in chunks of kCoef in LDS.
+constexpr int kCoef = 256;
+template <bool TWO>
+__global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* V, int k,
+                                                    const double2* __restrict__ c, const double2* __restrict__ s,
+                                                    int nbs, double2* w, double2* v,  // v may be a row of V
+                                                    double* __restrict__ partial,
+                                                    const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    const int kk = kdev ? *kdev : k;
+    __shared__ double2 lc[kCoef], ls[TWO ? kCoef : 1];
+    __shared__ double lds[kRB / 64];
+    double nrm[1] = {0.0};
+    const int64_t step = int64_t(gridDim.x) * kRB;
+    for (int k0 = 0; k0 < k; k0 += kCoef) {
+        const int kn = k - k0 < kCoef ? k - k0 : kCoef;
+        const bool last = k0 + kCoef >= k;
+        __syncthreads();
+        for (int g = threadIdx.x; g < kn; g += kRB) {
+            double2 a = make_double2(0.0, 0.0), b = make_double2(0.0, 0.0);
+            if (nbs > 0) {
+                for (int q = 0; q < nbs; ++q) {
+                    const double2 p = c[int64_t(k0 + g) * nbs + q];
+                    a.x += p.x;
+                    a.y += p.y;
+                }
+                if (TWO && k0 + g < k - 1)
+                    for (int q = 0; q < nbs; ++q) {
+                        const double2 p = s[int64_t(k0 + g) * nbs + q];
+                        b.x += p.x;
+                        b.y += p.y;
+                    }
+            } else {
+                a = c[k0 + g];
+                if (TWO && k0 + g < k - 1) b = s[k0 + g];
+            }
+            lc[g] = a;
+            if (TWO) ls[g] = b;  // s_{k-1} = 0: v keeps its own component
+        }
+        __syncthreads();
+        for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += step) {
+            double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
+            int g = 0;
+            for (; g + kGroup <= kn; g += kGroup) {
+                double2 x[kGroup];
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) x[q] = V[int64_t(k0 + g + q) * n + i];
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) {
+                    const double2 cg = lc[g + q];
+                    ar += cg.x * x[q].x - cg.y * x[q].y;
+                    ai += cg.x * x[q].y + cg.y * x[q].x;
+                    if (TWO) {
+                        const double2 sg = ls[g + q];
+                        br += sg.x * x[q].x - sg.y * x[q].y;
+                        bi += sg.x * x[q].y + sg.y * x[q].x;
+                    }
+                }
+            }
+            for (; g < kn; ++g) {
+                const double2 cg = lc[g], x = V[int64_t(k0 + g) * n + i];
+                ar += cg.x * x.x - cg.y * x.y;
+                ai += cg.x * x.y + cg.y * x.x;
+                if (TWO) {
+                    const double2 sg = ls[g];
+                    br += sg.x * x.x - sg.y * x.y;
+                    bi += sg.x * x.y + sg.y * x.x;
+                }
+            }
+            const double2 y = w[i];
+            const double2 r = make_double2(y.x - ar, y.y - ai);
+            w[i] = r;
+            if (last) nrm[0] += r.x * r.x + r.y * r.y;
+            if (TWO) {
+                const double2 z = v[i];
+                v[i] = make_double2(z.x - br, z.y - bi);
+            }
+        }
+    }
+    block_sum<1>(nrm, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
+}
+
+// u = sum_{i<steps} s_i V_i and the partial sums of ||u||^2
+__global__ __launch_bounds__(kRB) void k_ritz_vector(int64_t n, const double2* __restrict__ V,
+                                                      const LzState* __restrict__ st,
+                                                      const double2* __restrict__ s, double2* __restrict__ u,
+                                                      double* __restrict__ partial) {
+    __shared__ double lds[kRB / 64];
+    const int k = st->steps;
+    double nrm[1] = {0.0};
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
         double ar = 0.0, ai = 0.0;
-        for (int g = 0; g < kk; ++g) {
-            const double2 cg = c[g], x = V[int64_t(g) * n + i];
-            ar += cg.x * x.x - cg.y * x.y;
-            ai += cg.x * x.y + cg.y * x.x;
+        int g = 0;
+        for (; g + kGroup <= k; g += kGroup) {
+            double2 x[kGroup];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) x[q] = V[int64_t(g + q) * n + i];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                const double f = s[g + q].x;
+                ar += f * x[q].x;
+                ai += f * x[q].y;
+            }
         }
-        if (zero) {
-            w[i] = make_double2(sgn * ar, sgn * ai);
-        } else {
-            const double2 y = w[i];
-            w[i] = make_double2(y.x + sgn * ar, y.y + sgn * ai);
+        for (; g < k; ++g) {
+            const double f = s[g].x;
+            const double2 x = V[int64_t(g) * n + i];
+            ar += f * x.x;
+            ai += f * x.y;
         }
+        u[i] = make_double2(ar, ai);
+        nrm[0] += ar * ar + ai * ai;
     }
+    block_sum<1>(nrm, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
 }
 
-// w = (h32 ? h32 upcast : w) - alpha v_j - beta v_{j-1}, and the partial sums of ||w||^2 (one per block;
-// launched with the reduction grid, so the partials are those k_norm2_partial would give)
+// alpha_j from its partial sums, then w = (h32 ? h32 upcast : w) - alpha_j v_j - beta_{j-1} v_{j-1} and the
+// partial sums of ||w||^2 (one per block)
 __global__ __launch_bounds__(kRB) void k_three_term_norm(int64_t n, double2* __restrict__ w,
                                                           const float2* __restrict__ h32,
                                                           const double2* __restrict__ vj,
                                                           const double2* __restrict__ vjm1,
-                                                          const double* __restrict__ alpha,
+                                                          const double* __restrict__ pa, int nb,
+                                                          double* __restrict__ alpha,
                                                           const double* __restrict__ beta,
                                                           double* __restrict__ partial,
                                                           const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
     __shared__ double lds[kRB / 64];
-    const double a = *alpha;
+    const double a = sum_partials(pa, nb, lds);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
     const double b = vjm1 ? *beta : 0.0;
     double v[1] = {0.0};
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
@@ -210,12 +367,9 @@ __global__ __launch_bounds__(kRB) void k_three_term_norm(int64_t n, double2* __r
     if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
 
-// dst = src / denom (and a c64 copy when dst32 is given)
-__global__ __launch_bounds__(kRB) void k_scale(int64_t n, const double2* src, double2* dst,
-                                                const double* __restrict__ denom, float2* __restrict__ dst32,
-                                                const int32_t* __restrict__ stopped) {
-    if (halted(stopped)) return;
-    const double s = *denom;
+// ---------------------------------------------------------------- the ends of a step
+__device__ __forceinline__ void scale_rows(int64_t n, const double2* src, double2* dst, double s,
+                                           float2* __restrict__ dst32) {
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kRB) {
         const double2 x = src[i];
         const double2 y = make_double2(x.x / s, x.y / s);
@@ -224,45 +378,60 @@ __global__ __launch_bounds__(kRB) void k_scale(int64_t n, const double2* src, do
     }
 }
 
-// ---------------------------------------------------------------- second stages
-__global__ void k_init_finalize(const double* __restrict__ partial, int nb, LzState* __restrict__ st) {
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    const double nrm = sqrt(s);
-    st->steps = 0;
-    st->breakdown = 0;
-    st->skip2 = 0;
-    st->wn2 = 0.0;
-    st->n_second = 0;
-    st->n_pro = 0;
-    st->skip_pro = 1;
-    st->force = 0;
-    st->tnorm = 0.0;
-    st->nrm0 = nrm;
-    st->theta = __builtin_nan("");
-    st->stopped = (nrm > 0.0 && isfinite(nrm)) ? 0 : 1;
+// v_0 = v0 / ||v0|| (and its c64 copy when dst32 is given); a zero or non-finite start ends the recurrence
+__global__ __launch_bounds__(kRB) void k_start(int64_t n, const double2* __restrict__ v0,
+                                                const double* __restrict__ partial, int nb,
+                                                double2* __restrict__ dst, float2* __restrict__ dst32,
+                                                LzState* __restrict__ st, int32_t* __restrict__ halt) {
+    __shared__ double lds[kRB / 64];
+    const double nrm = sqrt(sum_partials(partial, nb, lds));
+    const bool ok = nrm > 0.0 && isfinite(nrm);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->steps = 0;
+        st->breakdown = 0;
+        st->n_second = 0;
+        st->n_pro = 0;
+        st->skip2 = 1;
+        st->skip_pro = 1;
+        st->force = 0;
+        st->theta = __builtin_nan("");
+        halt[0] = ok ? 0 : 1;
+    }
+    if (ok) scale_rows(n, v0, dst, nrm, dst32);
 }
 
-__global__ void k_alpha_finalize(const double2* __restrict__ partial, int nb, double* __restrict__ alpha,
-                                 const int32_t* __restrict__ stopped) {
-    if (halted(stopped)) return;
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b].x;
-    *alpha = s;
-}
-
-// Conditional Gram-Schmidt: wn2 = ||w||^2 before the first pass (store = 1), or after it (store = 0):
-// skip2 = 1 unless the pass shrank ||w||^2 below half (or the recurrence has stopped).
-__global__ void k_cgs_norm(const double* __restrict__ partial, int nb, int store, LzState* __restrict__ st) {
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    if (store) {
-        st->wn2 = s;
+// The end of step j: beta_j = ||w|| from its partial sums, the running estimate of ||T|| (tnorm[j + 1]; tnorm[0]
+// is 0), the breakdown test, and v_{j+1} = w / beta_j unless this was the last step.
+__global__ __launch_bounds__(kRB) void k_next(int64_t n, double2* __restrict__ w, const double* __restrict__ partial,
+                                               int nb, int j, int last, const double* __restrict__ alpha,
+                                               double* __restrict__ beta, double* __restrict__ tnorm,
+                                               float2* __restrict__ dst32, LzState* __restrict__ st,
+                                               int32_t* __restrict__ halt) {
+    __shared__ double lds[kRB / 64];
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (halt[j] != 0) {
+        if (first) halt[j + 1] = 1;
         return;
     }
-    const int skip = st->stopped != 0 || s >= 0.5 * st->wn2;
-    st->skip2 = skip;
-    if (!skip) ++st->n_second;
+    const double bj = sqrt(sum_partials(partial, nb, lds));
+    const double tn = fmax(j > 0 ? tnorm[j] : 0.0, fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0));
+    const bool broke = !last && bj <= 1e-14 * tn;
+    if (first) {
+        beta[j] = bj;
+        tnorm[j + 1] = tn;
+        st->steps = j + 1;
+        if (broke) st->breakdown = 1;
+        halt[j + 1] = (last || broke) ? 1 : 0;
+    }
+    if (!last && !broke) scale_rows(n, w, w, bj, dst32);
+}
+
+// u /= ||V s|| (a basis that is only semi-orthogonal leaves it 1 + O(sqrt(eps))); a zero u is left as it is
+__global__ __launch_bounds__(kRB) void k_unit(int64_t n, double2* __restrict__ u, const double* __restrict__ partial,
+                                               int nb) {
+    __shared__ double lds[kRB / 64];
+    const double nrm = sqrt(sum_partials(partial, nb, lds));
+    if (nrm > 0.0 && isfinite(nrm)) scale_rows(n, u, u, nrm, nullptr);
 }
 
 // Partial reorthogonalisation (H. D. Simon, "The Lanczos algorithm with partial reorthogonalization",
@@ -281,27 +450,22 @@ __global__ void k_cgs_norm(const double* __restrict__ partial, int nb, int store
 // FP64), and so is the next step's (the loss of orthogonality spreads to it through the recurrence); the
 // estimates then restart at eps64 sqrt(D).  Semi-orthogonality (every |omega| <= sqrt(eps)) keeps the
 // Ritz values as accurate as full reorthogonalisation would, to O(eps ||H||).
-// One block; omega rows i at omega + (i mod 3) (m + 2); partial: the ||w||^2 partial sums of this step.
+// One block; omega rows i at omega + (i mod 3) (m + 2); partial: the ||w||^2 partial sums of this step;
+// tnorm[j]: the estimate of ||T|| before this step.
 __global__ __launch_bounds__(kRB) void k_pro_estimate(const double* __restrict__ partial, int nb, int j, int m,
                                                       int64_t D, double eps, const double* __restrict__ alpha,
-                                                      const double* __restrict__ beta, double* __restrict__ omega,
-                                                      LzState* __restrict__ st) {
-    __shared__ double red[kRB];
-    __shared__ double s_bj;
+                                                      const double* __restrict__ beta,
+                                                      const double* __restrict__ tnorm, double* __restrict__ omega,
+                                                      LzState* __restrict__ st, const int32_t* __restrict__ stopped) {
+    __shared__ double red[kRB], lds[kRB / 64];
     const int tid = threadIdx.x;
-    if (st->stopped) {
+    if (halted(stopped)) {
         if (tid == 0) st->skip_pro = 1;
         return;
     }
-    if (tid == 0) {
-        double s = 0.0;
-        for (int b = 0; b < nb; ++b) s += partial[b];
-        s_bj = sqrt(s);
-    }
-    __syncthreads();
-    const double bj = s_bj;
+    const double bj = sqrt(sum_partials(partial, nb, lds));
     const double eps64 = 2.220446049250313e-16;
-    const double tn = fmax(st->tnorm, fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0));
+    const double tn = fmax(j > 0 ? tnorm[j] : 0.0, fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0));
     const double* wc = omega + (j % 3) * (m + 2);          // omega_{j, k}, k < j
     const double* wp = omega + ((j + 2) % 3) * (m + 2);    // omega_{j-1, k}, k < j - 1
     double* wn = omega + ((j + 1) % 3) * (m + 2);          // omega_{j+1, k}, k <= j
@@ -343,47 +507,26 @@ __global__ __launch_bounds__(kRB) void k_pro_estimate(const double* __restrict__
     }
 }
 
-__global__ void k_beta_finalize(const double* __restrict__ partial, int nb, int j, int last,
-                                const double* __restrict__ alpha, double* __restrict__ beta,
-                                LzState* __restrict__ st) {
-    if (st->stopped) return;
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    const double bj = sqrt(s);
-    beta[j] = bj;
-    const double t = fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0);
-    st->tnorm = fmax(st->tnorm, t);
-    st->steps = j + 1;
-    if (last) {
-        st->stopped = 1;
-    } else if (bj <= 1e-14 * st->tnorm) {
-        st->stopped = 1;
-        st->breakdown = 1;
+__global__ __launch_bounds__(kRB) void k_scalar_finalize(const double* __restrict__ partial, int nb,
+                                                          double* __restrict__ out, int sq) {
+    __shared__ double lds[kRB / 64];
+    const double s = sum_partials(partial, nb, lds);
+    if (threadIdx.x == 0) *out = sq ? sqrt(s) : s;
+}
+
+__global__ __launch_bounds__(kRB) void k_dot_finalize(const double2* __restrict__ partial, int nb,
+                                                       double* __restrict__ out) {
+    __shared__ double lds[2 * kRB / 64];
+    double v[2] = {0.0, 0.0};
+    for (int b = threadIdx.x; b < nb; b += kRB) {
+        v[0] += partial[b].x;
+        v[1] += partial[b].y;
     }
-}
-
-// ||V s|| of the Ritz vector (a basis that is only semi-orthogonal leaves it 1 + O(sqrt(eps))).
-__global__ void k_unorm_finalize(const double* __restrict__ partial, int nb, LzState* __restrict__ st) {
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    st->unrm = sqrt(s);
-    st->skip_u = (st->unrm > 0.0 && isfinite(st->unrm)) ? 0 : 1;
-}
-
-__global__ void k_scalar_finalize(const double* __restrict__ partial, int nb, double* __restrict__ out, int sq) {
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    *out = sq ? sqrt(s) : s;
-}
-
-__global__ void k_dot_finalize(const double2* __restrict__ partial, int nb, double* __restrict__ out) {
-    double sr = 0.0, si = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        sr += partial[b].x;
-        si += partial[b].y;
+    block_sum<2>(v, lds);
+    if (threadIdx.x == 0) {
+        out[0] = v[0];
+        out[1] = v[1];
     }
-    out[0] = sr;
-    out[1] = si;
 }
 
 // Number of eigenvalues of the k x k symmetric tridiagonal (a, b) below x: the count of negative pivots
@@ -403,146 +546,192 @@ __device__ int sturm_count(const double* a, const double* b, int k, double x, do
     return cnt;
 }
 
-// Lowest eigenpair of T (one thread; k is small): the lowest eigenvalue by bisection on the Sturm count
-// (Barth, Martin and Wilkinson), then its eigenvector by inverse iteration (Wilkinson; Peters and
-// Wilkinson 1971) with T - theta I factored by Gaussian elimination with partial pivoting, which for a
-// tridiagonal matrix keeps a lower band of one and an upper band of two (dl, d, du, du2).
-// work: 5 * m doubles.  s_out: complex coefficients (s_i, 0) for the Ritz vector, zero past k.
-__global__ void k_tridiag_lowest(const double* __restrict__ alpha, const double* __restrict__ beta, int m,
-                                 LzState* __restrict__ st, double* __restrict__ work,
-                                 double2* __restrict__ s_out, double* __restrict__ result) {
-    const int k = st->steps;
+// Lowest eigenpair of T (one wave; k is small): the lowest eigenvalue from the Sturm count (Barth, Martin and
+// Wilkinson), then its eigenvector by inverse iteration (Wilkinson; Peters and Wilkinson 1971) with T - theta I
+// factored by Gaussian elimination with partial pivoting, which for a tridiagonal matrix keeps a lower band of
+// one and an upper band of two (dl, d, du, du2).  The 64 lanes count at 64 points of the bracket at once, which
+// narrows it 65 times a round (about 10 rounds of k divisions instead of 55 to 60 bisections), and alpha, beta and
+// the bands sit in LDS while k <= kTriLds (in global memory a step of the elimination waits about a microsecond):
+// 390 us -> 104 us at k = 50.  work: 5 * m doubles.  s_out: complex coefficients (s_i, 0) for the Ritz vector,
+// zero past k.
+constexpr int kTriLds = 1024;
+__global__ __launch_bounds__(64) void k_tridiag_lowest(const double* __restrict__ alpha,
+                                                        const double* __restrict__ beta, int m,
+                                                        LzState* __restrict__ st, double* __restrict__ work,
+                                                        double2* __restrict__ s_out, double* __restrict__ result) {
+    __shared__ double lt[7 * kTriLds];
+    const int k = st->steps, lane = threadIdx.x;
     const double qnan = __builtin_nan("");
-    for (int i = 0; i < m; ++i) s_out[i] = make_double2(0.0, 0.0);
+    for (int i = lane; i < m; i += 64) s_out[i] = make_double2(0.0, 0.0);
     if (k == 0) {
-        result[0] = result[1] = result[2] = qnan;
-        result[3] = 0.0;
-        st->theta = qnan;
+        if (lane == 0) {
+            result[0] = result[1] = result[2] = qnan;
+            result[3] = 0.0;
+            st->theta = qnan;
+        }
         return;
     }
+    const bool in_lds = k <= kTriLds;
     const double* a = alpha;
     const double* b = beta;
+    double* band = work;  // dl, d, du, du2, x: `pitch` doubles each
+    int pitch = m;
+    if (in_lds) {
+        for (int i = lane; i < k; i += 64) {
+            lt[i] = alpha[i];
+            lt[kTriLds + i] = beta[i];
+        }
+        a = lt;
+        b = lt + kTriLds;
+        band = lt + 2 * kTriLds;
+        pitch = kTriLds;
+    }
+    __syncthreads();
     double lo = INFINITY, hi = -INFINITY, bmax2 = 0.0;
-    for (int i = 0; i < k; ++i) {
+    for (int i = lane; i < k; i += 64) {
         const double r = (i > 0 ? fabs(b[i - 1]) : 0.0) + (i < k - 1 ? fabs(b[i]) : 0.0);
         lo = fmin(lo, a[i] - r);
         hi = fmax(hi, a[i] + r);
         if (i < k - 1) bmax2 = fmax(bmax2, b[i] * b[i]);
     }
+    for (int w = 32; w > 0; w >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, w, 64));
+        hi = fmax(hi, __shfl_xor(hi, w, 64));
+        bmax2 = fmax(bmax2, __shfl_xor(bmax2, w, 64));
+    }
     const double pivmin = 2.2250738585072014e-308 * fmax(1.0, bmax2);
     const double tn = fmax(fabs(lo), fabs(hi));
     lo -= 4.0 * 2.220446049250313e-16 * tn + pivmin;
     hi += 4.0 * 2.220446049250313e-16 * tn + pivmin;
-    for (int it = 0; it < 400; ++it) {
+    // count(lo) = 0 and count(hi) >= 1 throughout; every round keeps the interval between the last point that
+    // counts 0 and the first that counts more.  A round whose points all fall on the ends has no number left
+    // between them; the bracket of adjacent numbers is left by bisection as a round of its middle.
+    for (int round = 0; round < 400; ++round) {
         const double mid = 0.5 * (lo + hi);
-        if (mid <= lo || mid >= hi) break;
-        if (sturm_count(a, b, k, mid, pivmin) >= 1)
-            hi = mid;
-        else
-            lo = mid;
+        if (!(mid > lo && mid < hi)) break;
+        const double h = (hi - lo) / 65.0;
+        double x = lo + h * (lane + 1);
+        if (!(x > lo && x < hi)) x = mid;
+        const bool above = sturm_count(a, b, k, x, pivmin) >= 1;
+        // the bracket from the points themselves (they need not be ascending where h is near rounding)
+        double nlo = above ? lo : x, nhi = above ? x : hi;
+        for (int w = 32; w > 0; w >>= 1) nhi = fmin(nhi, __shfl_xor(nhi, w, 64));
+        if (nlo >= nhi) nlo = lo;  // a count that is not monotone in x by rounding
+        for (int w = 32; w > 0; w >>= 1) nlo = fmax(nlo, __shfl_xor(nlo, w, 64));
+        if (nlo == lo && nhi == hi) break;
+        lo = nlo;
+        hi = nhi;
     }
     const double theta = 0.5 * (lo + hi);
-    // inverse iteration: LU with partial pivoting of T - theta I (rows swapped as needed)
-    double* dl = work;
-    double* d = work + m;
-    double* du = work + 2 * m;
-    double* du2 = work + 3 * m;
-    double* x = work + 4 * m;
-    double sn = 0.0;
-    for (int i = 0; i < k; ++i) x[i] = 1.0;
+    // inverse iteration: LU with partial pivoting of T - theta I (rows swapped as needed), by one lane
+    double* dl = band;
+    double* d = band + pitch;
+    double* du = band + 2 * pitch;
+    double* du2 = band + 3 * pitch;
+    double* x = band + 4 * pitch;
+    for (int i = lane; i < k; i += 64) x[i] = 1.0;
+    __syncthreads();
     const double tiny = 2.220446049250313e-16 * fmax(tn, 1e-300);
     for (int iter = 0; iter < 3; ++iter) {
-        for (int i = 0; i < k; ++i) {
+        for (int i = lane; i < k; i += 64) {
             d[i] = a[i] - theta;
             if (i < k - 1) dl[i] = du[i] = b[i];
             du2[i] = 0.0;
         }
-        // factor with row interchanges, applying the same eliminations to the right-hand side
-        for (int i = 0; i < k - 1; ++i) {
-            if (fabs(d[i]) >= fabs(dl[i])) {
-                if (d[i] == 0.0) d[i] = tiny;
-                const double f = dl[i] / d[i];
-                dl[i] = f;
-                d[i + 1] -= f * du[i];
-                du2[i] = 0.0;
-                // right-hand side forward step (no swap)
-                x[i + 1] -= f * x[i];
-            } else {
-                const double f = d[i] / dl[i];
-                d[i] = dl[i];
-                dl[i] = f;
-                const double t = du[i];
-                du[i] = d[i + 1];
-                d[i + 1] = t - f * d[i + 1];
-                if (i < k - 2) {
-                    du2[i] = du[i + 1];
-                    du[i + 1] = -f * du[i + 1];
+        __syncthreads();
+        if (lane == 0) {
+            // factor with row interchanges, applying the same eliminations to the right-hand side
+            for (int i = 0; i < k - 1; ++i) {
+                if (fabs(d[i]) >= fabs(dl[i])) {
+                    if (d[i] == 0.0) d[i] = tiny;
+                    const double f = dl[i] / d[i];
+                    dl[i] = f;
+                    d[i + 1] -= f * du[i];
+                    du2[i] = 0.0;
+                    // right-hand side forward step (no swap)
+                    x[i + 1] -= f * x[i];
+                } else {
+                    const double f = d[i] / dl[i];
+                    d[i] = dl[i];
+                    dl[i] = f;
+                    const double t = du[i];
+                    du[i] = d[i + 1];
+                    d[i + 1] = t - f * d[i + 1];
+                    if (i < k - 2) {
+                        du2[i] = du[i + 1];
+                        du[i + 1] = -f * du[i + 1];
+                    }
+                    const double xt = x[i];
+                    x[i] = x[i + 1];
+                    x[i + 1] = xt - f * x[i + 1];
                 }
-                const double xt = x[i];
-                x[i] = x[i + 1];
-                x[i + 1] = xt - f * x[i + 1];
             }
+            if (d[k - 1] == 0.0) d[k - 1] = tiny;
+            // back substitution with the upper band (d, du, du2)
+            x[k - 1] /= d[k - 1];
+            if (k > 1) x[k - 2] = (x[k - 2] - du[k - 2] * x[k - 1]) / d[k - 2];
+            for (int i = k - 3; i >= 0; --i) x[i] = (x[i] - du[i] * x[i + 1] - du2[i] * x[i + 2]) / d[i];
         }
-        if (d[k - 1] == 0.0) d[k - 1] = tiny;
-        // back substitution with the upper band (d, du, du2)
-        x[k - 1] /= d[k - 1];
-        if (k > 1) x[k - 2] = (x[k - 2] - du[k - 2] * x[k - 1]) / d[k - 2];
-        for (int i = k - 3; i >= 0; --i) x[i] = (x[i] - du[i] * x[i + 1] - du2[i] * x[i + 2]) / d[i];
-        sn = 0.0;
-        for (int i = 0; i < k; ++i) sn += x[i] * x[i];
+        __syncthreads();
+        double sn = 0.0;
+        for (int i = lane; i < k; i += 64) sn += x[i] * x[i];
+        for (int w = 32; w > 0; w >>= 1) sn += __shfl_xor(sn, w, 64);
         sn = sqrt(sn);
-        for (int i = 0; i < k; ++i) x[i] /= sn;
+        for (int i = lane; i < k; i += 64) x[i] /= sn;
+        __syncthreads();
     }
-    for (int i = 0; i < k; ++i) s_out[i] = make_double2(x[i], 0.0);
-    st->theta = theta;
-    result[0] = theta;
-    result[1] = beta[k - 1] * fabs(x[k - 1]);
-    result[3] = static_cast<double>(k);
+    for (int i = lane; i < k; i += 64) s_out[i] = make_double2(x[i], 0.0);
+    if (lane == 0) {
+        st->theta = theta;
+        result[0] = theta;
+        result[1] = beta[k - 1] * fabs(x[k - 1]);
+        result[3] = static_cast<double>(k);
+    }
 }
 
 // result[2] = sqrt(sum partials)
-__global__ void k_resid_finalize(const double* __restrict__ partial, int nb, const LzState* __restrict__ st,
-                                 double* __restrict__ result) {
+__global__ __launch_bounds__(kRB) void k_resid_finalize(const double* __restrict__ partial, int nb,
+                                                         const LzState* __restrict__ st,
+                                                         double* __restrict__ result) {
     if (st->steps == 0) return;
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    result[2] = sqrt(s);
+    __shared__ double lds[kRB / 64];
+    const double s = sum_partials(partial, nb, lds);
+    if (threadIdx.x == 0) result[2] = sqrt(s);
 }
 
 struct LzLayout {
-    size_t state, partial, coef, svec, work, omega, tmp, x32, y32, total;
+    size_t state, halt, tnorm, pa, pn0, pn1, pc, ps, coef, coef2, svec, work, omega, tmp, x32, y32, total;
 };
 
 LzLayout lz_layout(int64_t D, int32_t m, int32_t precision) {
     LzLayout L{};
     size_t off = 0;
-    L.state = off;
-    off = align_up(off + sizeof(LzState), 256);
-    L.partial = off;
-    off = align_up(off + sizeof(double2) * size_t(m + 1) * kMaxRedBlocks, 256);
-    L.coef = off;
-    off = align_up(off + sizeof(double2) * size_t(m + 1), 256);
-    L.svec = off;
-    off = align_up(off + sizeof(double2) * size_t(m + 1), 256);
-    L.work = off;
-    off = align_up(off + sizeof(double) * 5 * size_t(m + 1), 256);
-    L.omega = off;
-    off = align_up(off + sizeof(double) * 3 * size_t(m + 2), 256);
-    L.tmp = off;
-    off = align_up(off + sizeof(double2) * size_t(D), 256);
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off = align_up(off + bytes, 256);
+        return at;
+    };
+    L.state = take(sizeof(LzState));
+    L.halt = take(sizeof(int32_t) * size_t(m + 1));
+    L.tnorm = take(sizeof(double) * size_t(m + 1));
+    L.pa = take(sizeof(double) * kVecBlocks);   // alpha_j
+    L.pn0 = take(sizeof(double) * kVecBlocks);  // ||w||^2 after the three-term update
+    L.pn1 = take(sizeof(double) * kVecBlocks);  // ||w||^2 after a Gram-Schmidt pass
+    L.pc = take(sizeof(double2) * gs_partials(m));
+    L.ps = take(sizeof(double2) * gs_partials(m));
+    L.coef = take(sizeof(double2) * size_t(m + 1));
+    L.coef2 = take(sizeof(double2) * size_t(m + 1));
+    L.svec = take(sizeof(double2) * size_t(m + 1));
+    L.work = take(sizeof(double) * 5 * size_t(m + 1));
+    L.omega = take(sizeof(double) * 3 * size_t(m + 2));
+    L.tmp = take(sizeof(double2) * size_t(D));
     L.x32 = L.y32 = off;
     if (precision == MRMF_PREC_C_IN_Z) {
-        off = align_up(off + sizeof(float2) * size_t(D), 256);
-        L.y32 = off;
-        off = align_up(off + sizeof(float2) * size_t(D), 256);
+        L.x32 = take(sizeof(float2) * size_t(D));
+        L.y32 = take(sizeof(float2) * size_t(D));
     }
     L.total = off;
     return L;
-}
-
-int grid_for(int64_t n) {
-    const int64_t b = (n + kRB - 1) / kRB;
-    return static_cast<int>(b < 65536 ? (b < 1 ? 1 : b) : 65536);
 }
 
 }  // namespace
@@ -563,11 +752,11 @@ mrmf_status mrmf_dot_z(int64_t n, const void* d_a, const void* d_b, double* d_ou
     if (n < 0 || !d_a || !d_b || !d_out || !d_scratch) return MRMF_E_INVALID_ARG;
     if (scratch_bytes < sizeof(double2) * kMaxRedBlocks) return MRMF_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nb = red_blocks(n);
+    const int nb = red_blocks(n, kMaxRedBlocks);
     auto* part = static_cast<double2*>(d_scratch);
     hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(kRB), 0, s, n, static_cast<const double2*>(d_a),
-                       static_cast<const double2*>(d_b), part, nullptr);
-    hipLaunchKernelGGL(k_dot_finalize, dim3(1), dim3(1), 0, s, part, nb, d_out);
+                       static_cast<const double2*>(d_b), part);
+    hipLaunchKernelGGL(k_dot_finalize, dim3(1), dim3(kRB), 0, s, part, nb, d_out);
     return launch_status();
 }
 
@@ -576,11 +765,10 @@ mrmf_status mrmf_norm_z(int64_t n, const void* d_a, double* d_out, void* d_scrat
     if (n < 0 || !d_a || !d_out || !d_scratch) return MRMF_E_INVALID_ARG;
     if (scratch_bytes < sizeof(double) * kMaxRedBlocks) return MRMF_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nb = red_blocks(n);
+    const int nb = red_blocks(n, kMaxRedBlocks);
     auto* part = static_cast<double*>(d_scratch);
-    hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, n, static_cast<const double2*>(d_a), part,
-                       nullptr);
-    hipLaunchKernelGGL(k_scalar_finalize, dim3(1), dim3(1), 0, s, part, nb, d_out, 1);
+    hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, n, static_cast<const double2*>(d_a), part);
+    hipLaunchKernelGGL(k_scalar_finalize, dim3(1), dim3(kRB), 0, s, part, nb, d_out, 1);
     return launch_status();
 }
 
@@ -631,106 +819,100 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned char* sc = static_cast<unsigned char*>(d_scratch);
+    auto at = [&](size_t off) { return reinterpret_cast<double*>(sc + off); };
+    auto atz = [&](size_t off) { return reinterpret_cast<double2*>(sc + off); };
     auto* st = reinterpret_cast<LzState*>(sc + Lo.state);
-    const int32_t* stopped = &st->stopped;
-    auto* part_d = reinterpret_cast<double*>(sc + Lo.partial);
-    auto* part_z = reinterpret_cast<double2*>(sc + Lo.partial);
-    auto* coef = reinterpret_cast<double2*>(sc + Lo.coef);
-    auto* svec = reinterpret_cast<double2*>(sc + Lo.svec);
-    auto* work = reinterpret_cast<double*>(sc + Lo.work);
-    auto* omega = reinterpret_cast<double*>(sc + Lo.omega);
-    auto* tmp = reinterpret_cast<double2*>(sc + Lo.tmp);
+    auto* halt = reinterpret_cast<int32_t*>(sc + Lo.halt);
+    double *tnorm = at(Lo.tnorm), *pa = at(Lo.pa), *pn0 = at(Lo.pn0), *pn1 = at(Lo.pn1);
+    double2 *pc = atz(Lo.pc), *ps = atz(Lo.ps), *coef = atz(Lo.coef), *coef2 = atz(Lo.coef2), *svec = atz(Lo.svec);
+    double *work = at(Lo.work), *omega = at(Lo.omega);
+    auto* tmp = atz(Lo.tmp);
     auto* x32 = reinterpret_cast<float2*>(sc + Lo.x32);
     auto* y32 = reinterpret_cast<float2*>(sc + Lo.y32);
     auto* V = static_cast<double2*>(d_V);
     auto* u = static_cast<double2*>(d_u);
     const bool c32 = precision == MRMF_PREC_C_IN_Z;
-    const int nb = red_blocks(D);
-    const int g = grid_for(D);
+    const int nb = red_blocks(D, kVecBlocks);
+    const dim3 gv(nb), tb(kRB);
     auto row = [&](int j) { return V + int64_t(j) * D; };
 
-    // v_0 = v0 / ||v0||
-    hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, D, static_cast<const double2*>(d_v0), part_d,
-                       nullptr);
-    hipLaunchKernelGGL(k_init_finalize, dim3(1), dim3(1), 0, s, part_d, nb, st);
-    hipLaunchKernelGGL(k_scale, dim3(g), dim3(kRB), 0, s, D, static_cast<const double2*>(d_v0), row(0), &st->nrm0,
-                       c32 ? x32 : nullptr, stopped);
+    hipLaunchKernelGGL(k_norm2_partial, gv, tb, 0, s, D, static_cast<const double2*>(d_v0), pn0);
+    hipLaunchKernelGGL(k_start, gv, tb, 0, s, D, static_cast<const double2*>(d_v0), pn0, nb, row(0),
+                       c32 ? x32 : nullptr, st, halt);
     mrmf_status rc = launch_status();
     if (rc != MRMF_OK) return rc;
 
+    // One Gram-Schmidt pass of w against rows 0..k-1 (two: with the second pass of v = row k - 1 in the same
+    // reads of the basis).  second: the pass decides by itself whether it runs, from ||w||^2 before and after the
+    // first one; stop: the flag that skips it otherwise; pn: where the new ||w||^2 leaves its partial sums.
+    auto pass = [&](int k, double2* w, bool two, bool second, int count, const int32_t* stop, double* pn) {
+        const int nbg = gs_blocks(D, k);
+        const int32_t* after = second ? &st->skip2 : stop;  // the flag of the pass's later kernels
+        const dim3 gd(nbg, (k + kGroup - 1) / kGroup);
+        if (two)
+            hipLaunchKernelGGL(k_gs_dots<true>, gd, tb, 0, s, D, V, k, w, row(k - 1), pc, ps, nbg, nullptr, nullptr, nb,
+                               0, st, stop);
+        else
+            hipLaunchKernelGGL(k_gs_dots<false>, gd, tb, 0, s, D, V, k, w, nullptr, pc, nullptr, nbg,
+                               second ? pn0 : nullptr, pn1, nb, count, st, stop);
+        // few partial sums (a small vector): the update sums them itself
+        const bool inl = int64_t(k) * nbg <= 1024;
+        if (!inl)
+            hipLaunchKernelGGL(k_gs_finalize, dim3(two ? 2 * k : k), dim3(64), 0, s, k, nbg, pc, ps, coef, coef2, after);
+        const double2* c = inl ? pc : coef;
+        if (two)
+            hipLaunchKernelGGL(k_gs_update<true>, gv, tb, 0, s, D, V, k, c, inl ? ps : coef2, inl ? nbg : 0, w,
+                               row(k - 1), pn, after);
+        else
+            hipLaunchKernelGGL(k_gs_update<false>, gv, tb, 0, s, D, V, k, c, nullptr, inl ? nbg : 0, w, nullptr, pn,
+                               after);
+    };
+
+    const bool full = reorth == MRMF_REORTH_CGS2, cond = reorth == MRMF_REORTH_CGS2_COND;
     for (int j = 0; j < m; ++j) {
+        const int32_t* stopped = halt + j;
         double2* w = row(j + 1);
         // w = H v_j (the c64 form leaves H v_j in y32, read as it is by the next two kernels); alpha_j; then
-        // the three-term update in one pass that also leaves the partial sums of ||w||^2 in part_d
-        if (c32) {
-            rc = mv_c(x32, y32, s, stopped);
-            if (rc != MRMF_OK) return rc;
-            hipLaunchKernelGGL(k_dot_partial32, dim3(nb), dim3(kRB), 0, s, D, row(j), y32, part_z, stopped);
-        } else {
-            rc = mv_z(row(j), w, s, stopped);
-            if (rc != MRMF_OK) return rc;
-            hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(kRB), 0, s, D, row(j), w, part_z, stopped);
-        }
-        hipLaunchKernelGGL(k_alpha_finalize, dim3(1), dim3(1), 0, s, part_z, nb, d_alpha + j, stopped);
-        hipLaunchKernelGGL(k_three_term_norm, dim3(nb), dim3(kRB), 0, s, D, w, c32 ? y32 : nullptr, row(j),
-                           j > 0 ? row(j - 1) : nullptr, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr, part_d,
+        // the three-term update in one pass that also leaves the partial sums of ||w||^2 in pn0
+        rc = c32 ? mv_c(x32, y32, s, stopped) : mv_z(row(j), w, s, stopped);
+        if (rc != MRMF_OK) return rc;
+        hipLaunchKernelGGL(k_alpha_partial, gv, tb, 0, s, D, row(j), w, c32 ? y32 : nullptr, pa, stopped);
+        hipLaunchKernelGGL(k_three_term_norm, gv, tb, 0, s, D, w, c32 ? y32 : nullptr, row(j),
+                           j > 0 ? row(j - 1) : nullptr, pa, nb, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr, pn0,
                            stopped);
-        if (reorth == MRMF_REORTH_CGS2 || reorth == MRMF_REORTH_CGS2_COND) {
-            const int k = j + 1;
-            const bool cond = reorth == MRMF_REORTH_CGS2_COND;
-            if (cond) hipLaunchKernelGGL(k_cgs_norm, dim3(1), dim3(1), 0, s, part_d, nb, 1, st);
-            for (int pass = 0; pass < 2; ++pass) {
-                // the second pass of the conditional form runs (its kernels return at once otherwise)
-                // only when the device-side test after the first pass asked for it
-                const int32_t* stop = pass == 1 && cond ? &st->skip2 : stopped;
-                if (pass == 1 && cond) {
-                    hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, D, w, part_d, stopped);
-                    hipLaunchKernelGGL(k_cgs_norm, dim3(1), dim3(1), 0, s, part_d, nb, 0, st);
-                }
-                hipLaunchKernelGGL(k_gemvt_partial, dim3(nb, (k + kGroup - 1) / kGroup), dim3(kRB), 0, s, D, V, k,
-                                   w, part_z, nb, stop);
-                hipLaunchKernelGGL(k_gemvt_finalize, dim3((k + 63) / 64), dim3(64), 0, s, k, nb, part_z, coef,
-                                   stop);
-                hipLaunchKernelGGL(k_gemv_acc, dim3(g), dim3(kRB), 0, s, D, V, k, nullptr, coef, w, 0, -1.0, stop);
-            }
-            // ||w|| after the passes
-            hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, D, w, part_d, stopped);
+        const double* pn = pn0;  // where the partial sums of the final ||w||^2 are
+        if (full || cond) {
+            // Full form: v_j gets its second pass here, in the reads of the basis that w's first one needs, and w
+            // gets its own a step later.  Where the first pass shrank ||w|| by more than 1/sqrt(2) (the components
+            // it removed are then not rounding errors of w's size any more), the second one follows at once; so it
+            // does in the conditional form, which takes no other.
+            pass(j + 1, w, full && j > 0, false, 0, stopped, pn1);
+            pass(j + 1, w, false, true, cond ? 1 : 0, stopped, pn1);
+            pn = pn1;
         }
         if (reorth == MRMF_REORTH_PARTIAL) {
             // estimate the loss of orthogonality from ||w||; only when it calls for one, a Gram-Schmidt pass
-            // against v_0 .. v_j and a new norm (the skipped kernels return at once, and the partial sums of
-            // ||w||^2 from the three-term pass stay for k_beta_finalize)
-            const int k = j + 1;
+            // against v_0 .. v_j, which also leaves the new norm's partial sums over the old ones
             const double eps = c32 ? 1.1920928955078125e-07 : 2.220446049250313e-16;  // 2^-23 or 2^-52
-            hipLaunchKernelGGL(k_pro_estimate, dim3(1), dim3(kRB), 0, s, part_d, nb, j, m, D, eps, d_alpha,
-                               d_beta, omega, st);
-            const int32_t* stop = &st->skip_pro;
-            hipLaunchKernelGGL(k_gemvt_partial, dim3(nb, (k + kGroup - 1) / kGroup), dim3(kRB), 0, s, D, V, k, w,
-                               part_z, nb, stop);
-            hipLaunchKernelGGL(k_gemvt_finalize, dim3((k + 63) / 64), dim3(64), 0, s, k, nb, part_z, coef, stop);
-            hipLaunchKernelGGL(k_gemv_acc, dim3(g), dim3(kRB), 0, s, D, V, k, nullptr, coef, w, 0, -1.0, stop);
-            hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, D, w, part_d, stop);
+            hipLaunchKernelGGL(k_pro_estimate, dim3(1), tb, 0, s, pn0, nb, j, m, D, eps, d_alpha, d_beta, tnorm, omega,
+                               st, stopped);
+            pass(j + 1, w, false, false, 0, &st->skip_pro, pn0);
         }
-        hipLaunchKernelGGL(k_beta_finalize, dim3(1), dim3(1), 0, s, part_d, nb, j, j == m - 1 ? 1 : 0, d_alpha,
-                           d_beta, st);
-        if (j < m - 1)
-            hipLaunchKernelGGL(k_scale, dim3(g), dim3(kRB), 0, s, D, w, w, d_beta + j, c32 ? x32 : nullptr,
-                               stopped);
+        hipLaunchKernelGGL(k_next, gv, tb, 0, s, D, w, pn, nb, j, j == m - 1 ? 1 : 0, d_alpha, d_beta, tnorm,
+                           c32 ? x32 : nullptr, st, halt);
         rc = launch_status();
         if (rc != MRMF_OK) return rc;
     }
     // lowest Ritz pair of T, Ritz vector u = sum_i s_i v_i, explicit residual with the FP64 map
-    hipLaunchKernelGGL(k_tridiag_lowest, dim3(1), dim3(1), 0, s, d_alpha, d_beta, m, st, work, svec, d_result);
-    hipLaunchKernelGGL(k_gemv_acc, dim3(g), dim3(kRB), 0, s, D, V, m, &st->steps, svec, u, 1, 1.0, nullptr);
-    hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, D, u, part_d, nullptr);
-    hipLaunchKernelGGL(k_unorm_finalize, dim3(1), dim3(1), 0, s, part_d, nb, st);
-    hipLaunchKernelGGL(k_scale, dim3(g), dim3(kRB), 0, s, D, u, u, &st->unrm, nullptr, &st->skip_u);
+    hipLaunchKernelGGL(k_tridiag_lowest, dim3(1), dim3(64), 0, s, d_alpha, d_beta, m, st, work, svec, d_result);
+    hipLaunchKernelGGL(k_ritz_vector, gv, tb, 0, s, D, V, st, svec, u, pn0);
+    hipLaunchKernelGGL(k_unit, gv, tb, 0, s, D, u, pn0, nb);
     rc = launch_status();
     if (rc != MRMF_OK) return rc;
     rc = mv_z(u, tmp, s, nullptr);
     if (rc != MRMF_OK) return rc;
-    hipLaunchKernelGGL(k_resid_partial, dim3(nb), dim3(kRB), 0, s, D, tmp, u, st, part_d);
-    hipLaunchKernelGGL(k_resid_finalize, dim3(1), dim3(1), 0, s, part_d, nb, st, d_result);
+    hipLaunchKernelGGL(k_resid_partial, gv, tb, 0, s, D, tmp, u, st, pn0);
+    hipLaunchKernelGGL(k_resid_finalize, dim3(1), tb, 0, s, pn0, nb, st, d_result);
     return launch_status();
 }
 

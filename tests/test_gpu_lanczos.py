@@ -334,3 +334,29 @@ def test_lanczos_graph_replays_match_eager():
         assert torch.equal(out["alpha"], ref["alpha"]) and torch.equal(out["beta"], ref["beta"])
         assert torch.equal(out["result"], ref["result"])
         assert torch.isfinite(other["result"][0])
+
+
+@pytest.mark.parametrize("two_s,m_steps", [([1, 2, 3, 2, 1, 1], 17), ([2] * 5 + [1], 33), ([1, 2] * 6, 70), ([1] * 12, 300)])
+@pytest.mark.parametrize("reorth", ["cgs2", "cgs2_cond"])
+def test_basis_and_recurrence_over_sizes(two_s, m_steps, reorth):
+    """The Gram-Schmidt kernels where their launches change: 288 and 486 rows (a last block of 32 and 230 rows; few
+    partial sums, so the update sums them itself), 46656 rows (finalized coefficients, up to 70 vectors in groups of
+    eight), 300 steps (more vectors than one chunk of coefficients).  alpha and beta of the first steps against the
+    oracle's recurrence, the basis orthonormal to rounding: each of up to m passes leaves errors of a few eps, and
+    eps sqrt(D) m is below 1e-12 by an order of magnitude."""
+    N = len(two_s)
+    m = W.configs.open_xxz_chain(two_s, np.full(N - 1, 1.0), np.linspace(0.4, 1.1, N - 1))
+    x = W.random_state(m.dim, np.random.default_rng(31))
+    p = Plan(m)
+    th = torch.as_tensor(m.theta, dtype=torch.float64, device="cuda")
+    out = p.lanczos(th, torch.from_numpy(x).cuda(), m_steps, reorth=reorth, keep_basis=True)
+    torch.cuda.synchronize()
+    k = int(out["result"][3])
+    o = olz.lanczos(lambda v: mf.matvec(m, v), x, m_steps)
+    assert k == o["steps"] == m_steps
+    n = min(12, m_steps)
+    assert np.max(np.abs(out["alpha"].cpu().numpy()[:n] - o["alpha"][:n])) < 1e-11
+    assert np.max(np.abs(out["beta"].cpu().numpy()[:n] - o["beta"][:n])) < 1e-11
+    V = out["V"].reshape(m_steps + 1, -1)[:k].cpu().numpy()
+    assert np.max(np.abs(V.conj() @ V.T - np.eye(k))) <= 1e-12
+    assert abs(float(out["result"][0]) - o["theta"]) <= 1e-11 * abs(o["theta"])
