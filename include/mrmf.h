@@ -328,10 +328,8 @@ mrmf_status mrmf_norm_z(int64_t n, const void* d_a, double* d_out, void* d_scrat
 
 /* Device-resident Lanczos driving the matvec (the Krylov use of x -> H x, Sec. I).
  * Step j: w = H v_j; alpha_j = Re<v_j|w>; w -= alpha_j v_j + beta_{j-1} v_{j-1};
- * (MRMF_REORTH_CGS2) twice c = V^H w, w -= V c, the second time at once if the first pass left ||w||^2 below
- * half its value before it, and otherwise (it then removes errors of rounding size) one step later, on v_{j+1},
- * in the reads of the basis that the next step's first pass makes, for every j < m - 1;
- * (MRMF_REORTH_CGS2_COND) once, and a second time only in the first of these cases; (MRMF_REORTH_PARTIAL) once, only where
+ * (MRMF_REORTH_CGS2) twice c = V^H w, w -= V c; (MRMF_REORTH_CGS2_COND) once, and a second time only
+ * if that pass left ||w||^2 below half its value before it; (MRMF_REORTH_PARTIAL) once, only where
  * Simon's recurrence for the inner products <v_i|v_k> estimates one of them above sqrt(eps) and at the
  * step after such a step (the basis stays semi-orthogonal: every |<v_i|v_k>| up to about sqrt(eps));
  * eps is the machine epsilon of the matvec (FP64's, FP32's for MRMF_PREC_C_IN_Z);

@@ -13,9 +13,13 @@ namespace mrmf {
 namespace {
 
 constexpr int kRB = 256;            // threads per reduction block
-constexpr int kMaxRedBlocks = 512;  // first-stage partials of mrmf_dot_z / mrmf_norm_z
-constexpr int kVecBlocks = 1024;    // first-stage partials of the recurrence's vector kernels
+constexpr int kMaxRedBlocks = 512;  // first-stage partials per reduction
 constexpr int kGroup = 8;           // basis vectors per Gram-Schmidt block
+
+// Rounding.  The order of every sum here is part of the result: the rows of a thread in turn, the lanes of a wave as a
+// tree, the waves, then the blocks' partials one after the other.  The sign of the Ritz vector follows from the last
+// bits of alpha and beta (inverse iteration with a shift that equals the eigenvalue to the last bit), so another order
+// would turn it on some inputs.
 
 // Scalars of a call.  `halt` (one flag per step, in the scratch after this struct) says whether step j runs at
 // all: the kernel that ends step j writes halt[j + 1], so no kernel reads a flag that another block of the same
@@ -25,33 +29,42 @@ struct LzState {
     int32_t breakdown;
     int32_t n_second;  // conditional Gram-Schmidt: second passes taken so far
     int32_t n_pro;     // partial reorthogonalisation: full Gram-Schmidt passes taken so far
-    int32_t skip2;     // full and conditional Gram-Schmidt: this step's immediate second pass is skipped
+    int32_t skip2;     // conditional Gram-Schmidt: this step's second pass is skipped
     int32_t skip_pro;  // partial reorthogonalisation: this step's pass is skipped
     int32_t force;     // partial reorthogonalisation: the next step reorthogonalises as well
     int32_t pad;
     double theta;      // lowest Ritz value
 };
 
-int red_blocks(int64_t n, int most) {
+int red_blocks(int64_t n) {
     const int64_t b = (n + kRB - 1) / kRB;
-    return static_cast<int>(b < most ? (b < 1 ? 1 : b) : most);
+    return static_cast<int>(b < kMaxRedBlocks ? (b < 1 ? 1 : b) : kMaxRedBlocks);
 }
-
-// Row blocks of a Gram-Schmidt inner-product launch over k vectors: groups of kGroup vectors are blocks of
-// their own, so many vectors need fewer row blocks to fill the GPU, and the partial sums stay within
-// gs_partials() entries.
-int gs_blocks(int64_t n, int k) { return red_blocks(n, k <= 16 ? 1024 : k <= 32 ? 512 : 256); }
-size_t gs_partials(int32_t m) { return std::max<size_t>(size_t(32) * 512, size_t(m + 1) * 256); }
 
 __device__ __forceinline__ bool halted(const int32_t* stopped) { return stopped != nullptr && *stopped != 0; }
 
-// The sum of nb partial sums in a fixed order, in every thread of a block of kRB.  lds: kRB / 64 doubles; the
-// partials come from an earlier kernel, so a consumer sums them itself instead of waiting for a launch of one
-// thread that does (35 us for 512 partials read one after the other, against about 1 us here).
-__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nb, double* lds) {
-    double v[1] = {0.0};
-    for (int b = threadIdx.x; b < nb; b += kRB) v[0] += p[b];
-    return block_total<1>(v, lds);
+// The sum of nb <= kMaxRedBlocks partials (stride doubles apart), one after the other, in every thread of a block.
+// lds: kMaxRedBlocks + 1 doubles.  A consumer sums the partials of an earlier kernel itself, out of LDS (2 us for 512),
+// where a launch of one thread that reads them from memory took 20 to 41 us.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nb, int stride, double* lds) {
+    __syncthreads();
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) lds[b] = p[int64_t(b) * stride];
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double s = 0.0;
+        int b = 0;
+        for (; b + 16 <= nb; b += 16) {
+            double t[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) t[q] = lds[b + q];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s += t[q];
+        }
+        for (; b < nb; ++b) s += lds[b];
+        if (threadIdx.x == 0) lds[kMaxRedBlocks] = s;
+    }
+    __syncthreads();
+    return lds[kMaxRedBlocks];
 }
 
 // ---------------------------------------------------------------- first-stage reductions
@@ -124,133 +137,107 @@ __global__ __launch_bounds__(kRB) void k_resid_partial(int64_t n, const double2*
 }
 
 // ---------------------------------------------------------------- Gram-Schmidt
-// Whether a Gram-Schmidt kernel runs.  stopped: the step's halt flag, or the flag of a pass that may be skipped
-// (then *stopped != 0 skips it).  A second pass decides by itself, in its first kernel (k_gs_dots with pre set):
-// it runs when the first one left ||w||^2 below half its value before (Daniel, Gragg, Kaufman and Stewart,
-// 1976), and block (0, 0) leaves the decision in st->skip2 for the two kernels after it.
+// A pass is k_gs_dots, k_gs_finalize (large vectors) and k_gs_update; `stopped` is the step's halt flag, or the flag of a
+// pass that may be skipped.  The second pass of the conditional form decides by itself, in its first kernel (pre set):
+// it runs when the first one left ||w||^2 below half its value before (Daniel, Gragg, Kaufman and Stewart, 1976), and
+// block (0, 0) leaves the decision in st->skip2 for the kernels after it.
 //
-// Inner products c_i = <V_i|w>, i < k (partial sums pc[i nb + block]); TWO: also s_i = <V_i|v> for i < k - 1,
-// the coefficients of the second pass of v = V_{k-1} (ps).  Bound by the reads of the basis: one read serves both
-// products, and the blocks of the other groups of kGroup vectors that read the same rows of w and v run at the
-// same time on the same XCD (blockIdx.x decides it), so those hit its L2.  On 10 million rows and 20 vectors on
-// average a pass over the basis takes 0.72 ms (5.3 TB/s, the GPU's copy rate), and a step of the full form two of
-// them instead of four (2 x 0.72 against 4 x 0.64 ms).
-template <bool TWO>
+// Coefficients c_i = <V_i|w>, i = 0..k-1: partial[i * nb + block].  Bound by the reads of the basis: the blocks of the
+// other groups of kGroup vectors that read the same rows of w run at the same time on the same XCD (blockIdx.x decides
+// it), so those hit its L2; 10 million rows and 20 vectors 0.65 ms, 5.1 TB/s, the GPU's copy rate.
 __global__ __launch_bounds__(kRB) void k_gs_dots(int64_t n, const double2* __restrict__ V, int k,
-                                                  const double2* __restrict__ w, const double2* __restrict__ v,
-                                                  double2* __restrict__ pc, double2* __restrict__ ps, int nb,
-                                                  const double* __restrict__ pre, const double* __restrict__ post,
-                                                  int nbv, int count, LzState* __restrict__ st,
+                                                  const double2* __restrict__ w, double2* __restrict__ partial,
+                                                  int nb, const double* __restrict__ pre,
+                                                  const double* __restrict__ post, int nbv, LzState* __restrict__ st,
                                                   const int32_t* __restrict__ stopped) {
-    constexpr int kV = (TWO ? 4 : 2) * kGroup;
-    __shared__ double lds[kV * kRB / 64];
+    __shared__ double lds[kMaxRedBlocks + 1];
     if (pre != nullptr) {
         const bool halt = halted(stopped);
-        const double before = halt ? 0.0 : sum_partials(pre, nbv, lds);
-        const double after = halt ? 0.0 : sum_partials(post, nbv, lds);
+        const double before = halt ? 0.0 : sum_partials(pre, nbv, 1, lds);
+        const double after = halt ? 0.0 : sum_partials(post, nbv, 1, lds);
         const bool skip = halt || after >= 0.5 * before;
         if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
             st->skip2 = skip;
-            if (!skip && count) ++st->n_second;
+            if (!skip) ++st->n_second;
         }
         if (skip) return;
+        __syncthreads();
     } else if (halted(stopped)) {
         return;
     }
     const int base = blockIdx.y * kGroup;
-    double a[kV];
+    double v[2 * kGroup];
 #pragma unroll
-    for (int g = 0; g < kV; ++g) a[g] = 0.0;
+    for (int g = 0; g < 2 * kGroup; ++g) v[g] = 0.0;
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(nb) * kRB) {
         const double2 y = w[i];
-        const double2 z = TWO ? v[i] : make_double2(0.0, 0.0);
-        double2 x[kGroup];
-#pragma unroll
-        for (int g = 0; g < kGroup; ++g)
-            x[g] = base + g < k ? V[int64_t(base + g) * n + i] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int g = 0; g < kGroup; ++g) {
-            a[2 * g] += x[g].x * y.x + x[g].y * y.y;
-            a[2 * g + 1] += x[g].x * y.y - x[g].y * y.x;
-            if (TWO) {
-                a[2 * kGroup + 2 * g] += x[g].x * z.x + x[g].y * z.y;
-                a[2 * kGroup + 2 * g + 1] += x[g].x * z.y - x[g].y * z.x;
+            if (base + g < k) {
+                const double2 x = V[int64_t(base + g) * n + i];
+                v[2 * g] += x.x * y.x + x.y * y.y;
+                v[2 * g + 1] += x.x * y.y - x.y * y.x;
             }
         }
     }
-    block_sum_lds<kV>(a, lds);
-    const int t = threadIdx.x;
-    if (t < kV / 2) {  // thread t: coefficient t mod kGroup of c (t < kGroup) or of s
-        const int g = t % kGroup;
-        double re = 0.0, im = 0.0;
-        for (int q = 0; q < kRB / 64; ++q) {
-            re += lds[q * kV + 2 * t];
-            im += lds[q * kV + 2 * t + 1];
-        }
-        if (base + g < k) (t < kGroup ? pc : ps)[int64_t(base + g) * nb + blockIdx.x] = make_double2(re, im);
+    block_sum<2 * kGroup>(v, lds);
+    if (threadIdx.x == 0) {
+        for (int g = 0; g < kGroup; ++g)
+            if (base + g < k) partial[int64_t(base + g) * nb + blockIdx.x] = make_double2(v[2 * g], v[2 * g + 1]);
     }
 }
 
-// c_i (and s_i) from their partial sums: one wave per coefficient
-__global__ __launch_bounds__(64) void k_gs_finalize(int k, int nb, const double2* __restrict__ pc,
-                                                     const double2* __restrict__ ps, double2* __restrict__ c,
-                                                     double2* __restrict__ s, const int32_t* __restrict__ stopped) {
+// c_i from its partial sums, a block per coefficient (57 us -> 5 us for 512 partials: they were read by one thread each)
+__global__ __launch_bounds__(kRB) void k_gs_finalize(int nb, const double2* __restrict__ partial,
+                                                      double2* __restrict__ c, const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    const int i = blockIdx.x % k;
-    const bool second = blockIdx.x >= static_cast<unsigned>(k);
-    const double2* p = (second ? ps : pc) + int64_t(i) * nb;
-    double v[2] = {0.0, 0.0};
-    for (int b = threadIdx.x; b < nb; b += 64) {
-        v[0] += p[b].x;
-        v[1] += p[b].y;
-    }
-    wave_sum<2>(v);
-    if (threadIdx.x == 63) (second ? s : c)[i] = make_double2(v[0], v[1]);
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double* p = reinterpret_cast<const double*>(partial + int64_t(blockIdx.x) * nb);
+    const double re = sum_partials(p, nb, 2, lds), im = sum_partials(p + 1, nb, 2, lds);
+    if (threadIdx.x == 0) c[blockIdx.x] = make_double2(re, im);
 }
 
-// w -= sum_{i<k} c_i V_i and the partial sums of the new ||w||^2; TWO: also v -= sum_{i<k-1} s_i V_i for
-// v = V_{k-1} (the second pass of v), in the same read of the basis.  nbs > 0: c and s come as nbs partial sums
-// each (few rows: summed here, which saves the launch of k_gs_finalize).  Coefficients in chunks of kCoef in LDS.
-constexpr int kCoef = 256;
-template <bool TWO>
-__global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* V, int k,
-                                                    const double2* __restrict__ c, const double2* __restrict__ s,
-                                                    int nbs, double2* w, double2* v,  // v may be a row of V
-                                                    double* __restrict__ partial,
-                                                    const int32_t* __restrict__ stopped) {
+// w -= sum_{i<k} c_i V_i, and the partial sums of the new ||w||^2 when pn is given.  nbs > 0: c comes as nbs partial
+// sums each (small vectors: summed here, which saves the launch of k_gs_finalize).  The loads of kGroup vectors are
+// issued together (a loop over the vectors waited for each in turn where few blocks run).
+constexpr int kCoef = 256;  // coefficients in LDS at a time
+__global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* __restrict__ V, int k,
+                                                    const double2* __restrict__ c, int nbs, double2* __restrict__ w,
+                                                    double* __restrict__ pn, const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    __shared__ double2 lc[kCoef], ls[TWO ? kCoef : 1];
+    __shared__ double2 lc[kCoef];
     __shared__ double lds[kRB / 64];
     double nrm[1] = {0.0};
-    const int64_t step = int64_t(gridDim.x) * kRB;
-    for (int k0 = 0; k0 < k; k0 += kCoef) {
+    const bool once = k <= kCoef;
+    auto coefficients = [&](int k0) {
         const int kn = k - k0 < kCoef ? k - k0 : kCoef;
-        const bool last = k0 + kCoef >= k;
         __syncthreads();
         for (int g = threadIdx.x; g < kn; g += kRB) {
-            double2 a = make_double2(0.0, 0.0), b = make_double2(0.0, 0.0);
+            double2 a = make_double2(0.0, 0.0);
             if (nbs > 0) {
                 for (int q = 0; q < nbs; ++q) {
                     const double2 p = c[int64_t(k0 + g) * nbs + q];
                     a.x += p.x;
                     a.y += p.y;
                 }
-                if (TWO && k0 + g < k - 1)
-                    for (int q = 0; q < nbs; ++q) {
-                        const double2 p = s[int64_t(k0 + g) * nbs + q];
-                        b.x += p.x;
-                        b.y += p.y;
-                    }
             } else {
                 a = c[k0 + g];
-                if (TWO && k0 + g < k - 1) b = s[k0 + g];
             }
             lc[g] = a;
-            if (TWO) ls[g] = b;  // s_{k-1} = 0: v keeps its own component
         }
         __syncthreads();
-        for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += step) {
-            double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
+        return kn;
+    };
+    if (once) coefficients(0);
+    // every thread walks the same number of rows, so that the barriers of a chunked k are met by all
+    const int64_t step = int64_t(gridDim.x) * kRB;
+    for (int64_t i0 = int64_t(blockIdx.x) * kRB; i0 < n; i0 += step) {
+        const int64_t i = i0 + threadIdx.x;
+        const bool act = i < n;
+        double ar = 0.0, ai = 0.0;
+        for (int k0 = 0; k0 < k; k0 += kCoef) {
+            const int kn = once ? k : coefficients(k0);
+            if (!act) continue;
             int g = 0;
             for (; g + kGroup <= kn; g += kGroup) {
                 double2 x[kGroup];
@@ -261,35 +248,23 @@ __global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* V, 
                     const double2 cg = lc[g + q];
                     ar += cg.x * x[q].x - cg.y * x[q].y;
                     ai += cg.x * x[q].y + cg.y * x[q].x;
-                    if (TWO) {
-                        const double2 sg = ls[g + q];
-                        br += sg.x * x[q].x - sg.y * x[q].y;
-                        bi += sg.x * x[q].y + sg.y * x[q].x;
-                    }
                 }
             }
             for (; g < kn; ++g) {
                 const double2 cg = lc[g], x = V[int64_t(k0 + g) * n + i];
                 ar += cg.x * x.x - cg.y * x.y;
                 ai += cg.x * x.y + cg.y * x.x;
-                if (TWO) {
-                    const double2 sg = ls[g];
-                    br += sg.x * x.x - sg.y * x.y;
-                    bi += sg.x * x.y + sg.y * x.x;
-                }
-            }
-            const double2 y = w[i];
-            const double2 r = make_double2(y.x - ar, y.y - ai);
-            w[i] = r;
-            if (last) nrm[0] += r.x * r.x + r.y * r.y;
-            if (TWO) {
-                const double2 z = v[i];
-                v[i] = make_double2(z.x - br, z.y - bi);
             }
         }
+        if (!act) continue;
+        const double2 y = w[i];
+        const double2 r = make_double2(y.x - ar, y.y - ai);
+        w[i] = r;
+        nrm[0] += r.x * r.x + r.y * r.y;
     }
+    if (pn == nullptr) return;
     block_sum<1>(nrm, lds);
-    if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
+    if (threadIdx.x == 0) pn[blockIdx.x] = nrm[0];
 }
 
 // u = sum_{i<steps} s_i V_i and the partial sums of ||u||^2
@@ -339,8 +314,8 @@ __global__ __launch_bounds__(kRB) void k_three_term_norm(int64_t n, double2* __r
                                                           double* __restrict__ partial,
                                                           const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
-    __shared__ double lds[kRB / 64];
-    const double a = sum_partials(pa, nb, lds);
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double a = sum_partials(pa, nb, 1, lds);
     if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
     const double b = vjm1 ? *beta : 0.0;
     double v[1] = {0.0};
@@ -383,8 +358,8 @@ __global__ __launch_bounds__(kRB) void k_start(int64_t n, const double2* __restr
                                                 const double* __restrict__ partial, int nb,
                                                 double2* __restrict__ dst, float2* __restrict__ dst32,
                                                 LzState* __restrict__ st, int32_t* __restrict__ halt) {
-    __shared__ double lds[kRB / 64];
-    const double nrm = sqrt(sum_partials(partial, nb, lds));
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double nrm = sqrt(sum_partials(partial, nb, 1, lds));
     const bool ok = nrm > 0.0 && isfinite(nrm);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->steps = 0;
@@ -407,13 +382,13 @@ __global__ __launch_bounds__(kRB) void k_next(int64_t n, double2* __restrict__ w
                                                double* __restrict__ beta, double* __restrict__ tnorm,
                                                float2* __restrict__ dst32, LzState* __restrict__ st,
                                                int32_t* __restrict__ halt) {
-    __shared__ double lds[kRB / 64];
+    __shared__ double lds[kMaxRedBlocks + 1];
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     if (halt[j] != 0) {
         if (first) halt[j + 1] = 1;
         return;
     }
-    const double bj = sqrt(sum_partials(partial, nb, lds));
+    const double bj = sqrt(sum_partials(partial, nb, 1, lds));
     const double tn = fmax(j > 0 ? tnorm[j] : 0.0, fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0));
     const bool broke = !last && bj <= 1e-14 * tn;
     if (first) {
@@ -429,8 +404,8 @@ __global__ __launch_bounds__(kRB) void k_next(int64_t n, double2* __restrict__ w
 // u /= ||V s|| (a basis that is only semi-orthogonal leaves it 1 + O(sqrt(eps))); a zero u is left as it is
 __global__ __launch_bounds__(kRB) void k_unit(int64_t n, double2* __restrict__ u, const double* __restrict__ partial,
                                                int nb) {
-    __shared__ double lds[kRB / 64];
-    const double nrm = sqrt(sum_partials(partial, nb, lds));
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double nrm = sqrt(sum_partials(partial, nb, 1, lds));
     if (nrm > 0.0 && isfinite(nrm)) scale_rows(n, u, u, nrm, nullptr);
 }
 
@@ -457,13 +432,13 @@ __global__ __launch_bounds__(kRB) void k_pro_estimate(const double* __restrict__
                                                       const double* __restrict__ beta,
                                                       const double* __restrict__ tnorm, double* __restrict__ omega,
                                                       LzState* __restrict__ st, const int32_t* __restrict__ stopped) {
-    __shared__ double red[kRB], lds[kRB / 64];
+    __shared__ double red[kRB], lds[kMaxRedBlocks + 1];
     const int tid = threadIdx.x;
     if (halted(stopped)) {
         if (tid == 0) st->skip_pro = 1;
         return;
     }
-    const double bj = sqrt(sum_partials(partial, nb, lds));
+    const double bj = sqrt(sum_partials(partial, nb, 1, lds));
     const double eps64 = 2.220446049250313e-16;
     const double tn = fmax(j > 0 ? tnorm[j] : 0.0, fabs(alpha[j]) + bj + (j > 0 ? beta[j - 1] : 0.0));
     const double* wc = omega + (j % 3) * (m + 2);          // omega_{j, k}, k < j
@@ -509,23 +484,19 @@ __global__ __launch_bounds__(kRB) void k_pro_estimate(const double* __restrict__
 
 __global__ __launch_bounds__(kRB) void k_scalar_finalize(const double* __restrict__ partial, int nb,
                                                           double* __restrict__ out, int sq) {
-    __shared__ double lds[kRB / 64];
-    const double s = sum_partials(partial, nb, lds);
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double s = sum_partials(partial, nb, 1, lds);
     if (threadIdx.x == 0) *out = sq ? sqrt(s) : s;
 }
 
 __global__ __launch_bounds__(kRB) void k_dot_finalize(const double2* __restrict__ partial, int nb,
                                                        double* __restrict__ out) {
-    __shared__ double lds[2 * kRB / 64];
-    double v[2] = {0.0, 0.0};
-    for (int b = threadIdx.x; b < nb; b += kRB) {
-        v[0] += partial[b].x;
-        v[1] += partial[b].y;
-    }
-    block_sum<2>(v, lds);
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double* p = reinterpret_cast<const double*>(partial);
+    const double re = sum_partials(p, nb, 2, lds), im = sum_partials(p + 1, nb, 2, lds);
     if (threadIdx.x == 0) {
-        out[0] = v[0];
-        out[1] = v[1];
+        out[0] = re;
+        out[1] = im;
     }
 }
 
@@ -546,14 +517,14 @@ __device__ int sturm_count(const double* a, const double* b, int k, double x, do
     return cnt;
 }
 
-// Lowest eigenpair of T (one wave; k is small): the lowest eigenvalue from the Sturm count (Barth, Martin and
-// Wilkinson), then its eigenvector by inverse iteration (Wilkinson; Peters and Wilkinson 1971) with T - theta I
-// factored by Gaussian elimination with partial pivoting, which for a tridiagonal matrix keeps a lower band of
-// one and an upper band of two (dl, d, du, du2).  The 64 lanes count at 64 points of the bracket at once, which
-// narrows it 65 times a round (about 10 rounds of k divisions instead of 55 to 60 bisections), and alpha, beta and
-// the bands sit in LDS while k <= kTriLds (in global memory a step of the elimination waits about a microsecond):
-// 390 us -> 104 us at k = 50.  work: 5 * m doubles.  s_out: complex coefficients (s_i, 0) for the Ritz vector,
-// zero past k.
+// Lowest eigenpair of T (one wave; k is small): the lowest eigenvalue by bisection on the Sturm count
+// (Barth, Martin and Wilkinson), then its eigenvector by inverse iteration (Wilkinson; Peters and
+// Wilkinson 1971) with T - theta I factored by Gaussian elimination with partial pivoting, which for a
+// tridiagonal matrix keeps a lower band of one and an upper band of two (dl, d, du, du2).  A round takes six levels of
+// the bisection: the lanes count at the 63 points it can reach, then follow the branches it takes (10 rounds of k
+// divisions instead of 55 to 60).  alpha, beta and the bands sit in LDS while k <= kTriLds: in global memory a step of
+// the elimination waits about a microsecond.  390 us -> 104 us at k = 50.  work: 5 * m doubles.  s_out: complex
+// coefficients (s_i, 0) for the Ritz vector, zero past k.
 constexpr int kTriLds = 1024;
 __global__ __launch_bounds__(64) void k_tridiag_lowest(const double* __restrict__ alpha,
                                                         const double* __restrict__ beta, int m,
@@ -603,24 +574,36 @@ __global__ __launch_bounds__(64) void k_tridiag_lowest(const double* __restrict_
     const double tn = fmax(fabs(lo), fabs(hi));
     lo -= 4.0 * 2.220446049250313e-16 * tn + pivmin;
     hi += 4.0 * 2.220446049250313e-16 * tn + pivmin;
-    // count(lo) = 0 and count(hi) >= 1 throughout; every round keeps the interval between the last point that
-    // counts 0 and the first that counts more.  A round whose points all fall on the ends has no number left
-    // between them; the bracket of adjacent numbers is left by bisection as a round of its middle.
-    for (int round = 0; round < 400; ++round) {
-        const double mid = 0.5 * (lo + hi);
-        if (!(mid > lo && mid < hi)) break;
-        const double h = (hi - lo) / 65.0;
-        double x = lo + h * (lane + 1);
-        if (!(x > lo && x < hi)) x = mid;
-        const bool above = sturm_count(a, b, k, x, pivmin) >= 1;
-        // the bracket from the points themselves (they need not be ascending where h is near rounding)
-        double nlo = above ? lo : x, nhi = above ? x : hi;
-        for (int w = 32; w > 0; w >>= 1) nhi = fmin(nhi, __shfl_xor(nhi, w, 64));
-        if (nlo >= nhi) nlo = lo;  // a count that is not monotone in x by rounding
-        for (int w = 32; w > 0; w >>= 1) nlo = fmax(nlo, __shfl_xor(nlo, w, 64));
-        if (nlo == lo && nhi == hi) break;
-        lo = nlo;
-        hi = nhi;
+    // node q of the tree of the next levels (root 1, children 2 q where the count is 0 and lo moves up, 2 q + 1 where
+    // it is not and hi moves down)
+    for (int it = 0; it < 400; it += 6) {
+        double nlo = lo, nhi = hi;
+        const int q = lane + 1;  // lane 63 idles: 63 nodes
+        for (int bit = 30 - __clz(q); bit >= 0; --bit) {
+            const double mid = 0.5 * (nlo + nhi);
+            if ((q >> bit) & 1)
+                nhi = mid;
+            else
+                nlo = mid;
+        }
+        const bool above = sturm_count(a, b, k, 0.5 * (nlo + nhi), pivmin) >= 1;
+        const unsigned long long taken = __ballot(above);
+        bool done = false;
+        int node = 1;
+        for (int level = 0; level < 6; ++level) {
+            const double mid = 0.5 * (lo + hi);
+            if (mid <= lo || mid >= hi) {
+                done = true;
+                break;
+            }
+            const bool up = (taken >> (node - 1)) & 1;
+            if (up)
+                hi = mid;
+            else
+                lo = mid;
+            node = 2 * node + (up ? 1 : 0);
+        }
+        if (done) break;
     }
     const double theta = 0.5 * (lo + hi);
     // inverse iteration: LU with partial pivoting of T - theta I (rows swapped as needed), by one lane
@@ -674,8 +657,7 @@ __global__ __launch_bounds__(64) void k_tridiag_lowest(const double* __restrict_
         }
         __syncthreads();
         double sn = 0.0;
-        for (int i = lane; i < k; i += 64) sn += x[i] * x[i];
-        for (int w = 32; w > 0; w >>= 1) sn += __shfl_xor(sn, w, 64);
+        for (int i = 0; i < k; ++i) sn += x[i] * x[i];
         sn = sqrt(sn);
         for (int i = lane; i < k; i += 64) x[i] /= sn;
         __syncthreads();
@@ -694,13 +676,13 @@ __global__ __launch_bounds__(kRB) void k_resid_finalize(const double* __restrict
                                                          const LzState* __restrict__ st,
                                                          double* __restrict__ result) {
     if (st->steps == 0) return;
-    __shared__ double lds[kRB / 64];
-    const double s = sum_partials(partial, nb, lds);
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double s = sum_partials(partial, nb, 1, lds);
     if (threadIdx.x == 0) result[2] = sqrt(s);
 }
 
 struct LzLayout {
-    size_t state, halt, tnorm, pa, pn0, pn1, pc, ps, coef, coef2, svec, work, omega, tmp, x32, y32, total;
+    size_t state, halt, tnorm, pa, pn0, pn1, pc, coef, svec, work, omega, tmp, x32, y32, total;
 };
 
 LzLayout lz_layout(int64_t D, int32_t m, int32_t precision) {
@@ -714,13 +696,11 @@ LzLayout lz_layout(int64_t D, int32_t m, int32_t precision) {
     L.state = take(sizeof(LzState));
     L.halt = take(sizeof(int32_t) * size_t(m + 1));
     L.tnorm = take(sizeof(double) * size_t(m + 1));
-    L.pa = take(sizeof(double) * kVecBlocks);   // alpha_j
-    L.pn0 = take(sizeof(double) * kVecBlocks);  // ||w||^2 after the three-term update
-    L.pn1 = take(sizeof(double) * kVecBlocks);  // ||w||^2 after a Gram-Schmidt pass
-    L.pc = take(sizeof(double2) * gs_partials(m));
-    L.ps = take(sizeof(double2) * gs_partials(m));
+    L.pa = take(sizeof(double) * kMaxRedBlocks);   // alpha_j
+    L.pn0 = take(sizeof(double) * kMaxRedBlocks);  // ||w||^2 after the three-term update
+    L.pn1 = take(sizeof(double) * kMaxRedBlocks);  // ||w||^2 after a Gram-Schmidt pass
+    L.pc = take(sizeof(double2) * size_t(m + 1) * kMaxRedBlocks);
     L.coef = take(sizeof(double2) * size_t(m + 1));
-    L.coef2 = take(sizeof(double2) * size_t(m + 1));
     L.svec = take(sizeof(double2) * size_t(m + 1));
     L.work = take(sizeof(double) * 5 * size_t(m + 1));
     L.omega = take(sizeof(double) * 3 * size_t(m + 2));
@@ -752,7 +732,7 @@ mrmf_status mrmf_dot_z(int64_t n, const void* d_a, const void* d_b, double* d_ou
     if (n < 0 || !d_a || !d_b || !d_out || !d_scratch) return MRMF_E_INVALID_ARG;
     if (scratch_bytes < sizeof(double2) * kMaxRedBlocks) return MRMF_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nb = red_blocks(n, kMaxRedBlocks);
+    const int nb = red_blocks(n);
     auto* part = static_cast<double2*>(d_scratch);
     hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(kRB), 0, s, n, static_cast<const double2*>(d_a),
                        static_cast<const double2*>(d_b), part);
@@ -765,7 +745,7 @@ mrmf_status mrmf_norm_z(int64_t n, const void* d_a, double* d_out, void* d_scrat
     if (n < 0 || !d_a || !d_out || !d_scratch) return MRMF_E_INVALID_ARG;
     if (scratch_bytes < sizeof(double) * kMaxRedBlocks) return MRMF_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nb = red_blocks(n, kMaxRedBlocks);
+    const int nb = red_blocks(n);
     auto* part = static_cast<double*>(d_scratch);
     hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(kRB), 0, s, n, static_cast<const double2*>(d_a), part);
     hipLaunchKernelGGL(k_scalar_finalize, dim3(1), dim3(kRB), 0, s, part, nb, d_out, 1);
@@ -824,7 +804,7 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
     auto* st = reinterpret_cast<LzState*>(sc + Lo.state);
     auto* halt = reinterpret_cast<int32_t*>(sc + Lo.halt);
     double *tnorm = at(Lo.tnorm), *pa = at(Lo.pa), *pn0 = at(Lo.pn0), *pn1 = at(Lo.pn1);
-    double2 *pc = atz(Lo.pc), *ps = atz(Lo.ps), *coef = atz(Lo.coef), *coef2 = atz(Lo.coef2), *svec = atz(Lo.svec);
+    double2 *pc = atz(Lo.pc), *coef = atz(Lo.coef), *svec = atz(Lo.svec);
     double *work = at(Lo.work), *omega = at(Lo.omega);
     auto* tmp = atz(Lo.tmp);
     auto* x32 = reinterpret_cast<float2*>(sc + Lo.x32);
@@ -832,7 +812,7 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
     auto* V = static_cast<double2*>(d_V);
     auto* u = static_cast<double2*>(d_u);
     const bool c32 = precision == MRMF_PREC_C_IN_Z;
-    const int nb = red_blocks(D, kVecBlocks);
+    const int nb = red_blocks(D);
     const dim3 gv(nb), tb(kRB);
     auto row = [&](int j) { return V + int64_t(j) * D; };
 
@@ -842,30 +822,16 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
     mrmf_status rc = launch_status();
     if (rc != MRMF_OK) return rc;
 
-    // One Gram-Schmidt pass of w against rows 0..k-1 (two: with the second pass of v = row k - 1 in the same
-    // reads of the basis).  second: the pass decides by itself whether it runs, from ||w||^2 before and after the
-    // first one; stop: the flag that skips it otherwise; pn: where the new ||w||^2 leaves its partial sums.
-    auto pass = [&](int k, double2* w, bool two, bool second, int count, const int32_t* stop, double* pn) {
-        const int nbg = gs_blocks(D, k);
-        const int32_t* after = second ? &st->skip2 : stop;  // the flag of the pass's later kernels
-        const dim3 gd(nbg, (k + kGroup - 1) / kGroup);
-        if (two)
-            hipLaunchKernelGGL(k_gs_dots<true>, gd, tb, 0, s, D, V, k, w, row(k - 1), pc, ps, nbg, nullptr, nullptr, nb,
-                               0, st, stop);
-        else
-            hipLaunchKernelGGL(k_gs_dots<false>, gd, tb, 0, s, D, V, k, w, nullptr, pc, nullptr, nbg,
-                               second ? pn0 : nullptr, pn1, nb, count, st, stop);
+    // One Gram-Schmidt pass of w against rows 0..k-1.  decides: it runs only where the first one shrank w; stop: the
+    // flag that skips it otherwise; pn: where the new ||w||^2 leaves its partial sums (null: not needed).
+    auto pass = [&](int k, double2* w, bool decides, const int32_t* stop, double* pn) {
+        const int32_t* after = decides ? &st->skip2 : stop;  // the flag of the pass's later kernels
+        hipLaunchKernelGGL(k_gs_dots, dim3(nb, (k + kGroup - 1) / kGroup), tb, 0, s, D, V, k, w, pc, nb,
+                           decides ? pn0 : nullptr, pn1, nb, st, stop);
         // few partial sums (a small vector): the update sums them itself
-        const bool inl = int64_t(k) * nbg <= 1024;
-        if (!inl)
-            hipLaunchKernelGGL(k_gs_finalize, dim3(two ? 2 * k : k), dim3(64), 0, s, k, nbg, pc, ps, coef, coef2, after);
-        const double2* c = inl ? pc : coef;
-        if (two)
-            hipLaunchKernelGGL(k_gs_update<true>, gv, tb, 0, s, D, V, k, c, inl ? ps : coef2, inl ? nbg : 0, w,
-                               row(k - 1), pn, after);
-        else
-            hipLaunchKernelGGL(k_gs_update<false>, gv, tb, 0, s, D, V, k, c, nullptr, inl ? nbg : 0, w, nullptr, pn,
-                               after);
+        const bool inl = nb <= 32;
+        if (!inl) hipLaunchKernelGGL(k_gs_finalize, dim3(k), tb, 0, s, nb, pc, coef, after);
+        hipLaunchKernelGGL(k_gs_update, gv, tb, 0, s, D, V, k, inl ? pc : coef, inl ? nb : 0, w, pn, after);
     };
 
     const bool full = reorth == MRMF_REORTH_CGS2, cond = reorth == MRMF_REORTH_CGS2_COND;
@@ -882,12 +848,8 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
                            stopped);
         const double* pn = pn0;  // where the partial sums of the final ||w||^2 are
         if (full || cond) {
-            // Full form: v_j gets its second pass here, in the reads of the basis that w's first one needs, and w
-            // gets its own a step later.  Where the first pass shrank ||w|| by more than 1/sqrt(2) (the components
-            // it removed are then not rounding errors of w's size any more), the second one follows at once; so it
-            // does in the conditional form, which takes no other.
-            pass(j + 1, w, full && j > 0, false, 0, stopped, pn1);
-            pass(j + 1, w, false, true, cond ? 1 : 0, stopped, pn1);
+            pass(j + 1, w, false, stopped, cond ? pn1 : nullptr);
+            pass(j + 1, w, cond, stopped, pn1);
             pn = pn1;
         }
         if (reorth == MRMF_REORTH_PARTIAL) {
@@ -896,7 +858,7 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
             const double eps = c32 ? 1.1920928955078125e-07 : 2.220446049250313e-16;  // 2^-23 or 2^-52
             hipLaunchKernelGGL(k_pro_estimate, dim3(1), tb, 0, s, pn0, nb, j, m, D, eps, d_alpha, d_beta, tnorm, omega,
                                st, stopped);
-            pass(j + 1, w, false, false, 0, &st->skip_pro, pn0);
+            pass(j + 1, w, false, &st->skip_pro, pn0);
         }
         hipLaunchKernelGGL(k_next, gv, tb, 0, s, D, w, pn, nb, j, j == m - 1 ? 1 : 0, d_alpha, d_beta, tnorm,
                            c32 ? x32 : nullptr, st, halt);

@@ -19,48 +19,48 @@ __device__ __forceinline__ double dpp_move(double v) {
                                           static_cast<uint64_t>(static_cast<uint32_t>(lo)));
 }
 
-// Sums over the 64 lanes of a wave (all active) with a fixed pattern of DPP moves (lane pairs 1 and 2 apart, the
-// half and full row mirrors, then the row broadcasts of lanes 15 and 31), which stay in the vector unit where
-// __shfl goes through LDS; the totals end in lane 63.
+// Sum over the 64 lanes of a wave with a fixed pattern of DPP moves (lane pairs 1 and 2 apart, the half and full row
+// mirrors, then the row broadcasts of lanes 15 and 31); the total ends in lane 63.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_move<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
+    v += dpp_move<0x4E, 0xf>(v);   // quad_perm [2, 3, 0, 1]
+    v += dpp_move<0x141, 0xf>(v);  // row_half_mirror
+    v += dpp_move<0x140, 0xf>(v);  // row_mirror: every lane holds its row's sum
+    v += dpp_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    return v;                      // lane 63: the wave's sum
+}
+
+// Sums over the 64 lanes of a wave (all active) as the tree of lane distances 32, 16, 8, 4, 2, 1; every lane holds the
+// totals.  Below 16 the partner's value comes by a DPP move inside the vector unit instead of a shuffle through LDS: a
+// rotation of the 16 lanes of a row by 8, by 4 (lanes 8 apart already hold the same sum), then swaps inside quads.
 template <int NV>
-__device__ __forceinline__ void wave_sum(double (&v)[NV]) {
+__device__ __forceinline__ void wave_tree(double (&v)[NV]) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0xB1, 0xf>(v[k]);   // quad_perm [1, 0, 3, 2]
+    for (int k = 0; k < NV; ++k) v[k] += __shfl_xor(v[k], 32, 64);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] += __shfl_xor(v[k], 16, 64);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x128, 0xf>(v[k]);  // row_ror:8
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x124, 0xf>(v[k]);  // row_ror:4
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x4E, 0xf>(v[k]);   // quad_perm [2, 3, 0, 1]
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x141, 0xf>(v[k]);  // row_half_mirror
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x140, 0xf>(v[k]);  // row_mirror: every lane holds its row's sum
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x142, 0xa>(v[k]);  // row_bcast:15 into rows 1 and 3
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0x143, 0xc>(v[k]);  // row_bcast:31 into rows 2 and 3
+    for (int k = 0; k < NV; ++k) v[k] += dpp_move<0xB1, 0xf>(v[k]);   // quad_perm [1, 0, 3, 2]
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-    double a[1] = {v};
-    wave_sum<1>(a);
-    return a[0];
-}
-
-// The waves' sums of v in lds[wave * NV + k] (NV * blockDim / 64 doubles), after a barrier.
+// Sums v over the block (the waves' trees, then in wave order); the result is valid in thread 0.  `lds` must hold
+// NV * (blockDim / 64) doubles.
 template <int NV>
-__device__ __forceinline__ void block_sum_lds(double (&v)[NV], double* lds) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    wave_sum<NV>(v);
-    if (lane == 63) {
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    wave_tree<NV>(v);
+    if (lane == 0) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) lds[wave * NV + k] = v[k];
     }
     __syncthreads();
-}
-
-// Sums v over the block; the result is valid in thread 0.
-template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
-    const int nw = (blockDim.x + 63) >> 6;
-    block_sum_lds<NV>(v, lds);
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -70,17 +70,6 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
         }
     }
     __syncthreads();
-}
-
-// The sum of v[0] over the block, in every thread.
-template <int NV>
-__device__ __forceinline__ double block_total(double (&v)[NV], double* lds) {
-    const int nw = (blockDim.x + 63) >> 6;
-    block_sum_lds<NV>(v, lds);
-    double s = 0.0;
-    for (int w = 0; w < nw; ++w) s += lds[w * NV];
-    __syncthreads();
-    return s;
 }
 
 }  // namespace mrmf
