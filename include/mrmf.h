@@ -180,7 +180,18 @@ mrmf_status mrmf_plan_set_kernel(mrmf_plan plan, int32_t kind, int32_t inner_sit
  *                                                   issued, masked when inadmissible;
  *                             MRMF_VARIANT_LIST   - those channels are compacted per super-tile into a
  *                                                   list of admissible ones that every thread walks
- *                                                   (MRMF_TUNE_LOAD_GROUP = gathers per chunk).
+ *                                                   (MRMF_TUNE_LOAD_GROUP = gathers per chunk);
+ *                             MRMF_VARIANT_WINDOW - the unrolled copies run one after the other out of LDS, channels
+ *                                                   that exclude each other share a gather, and the sites may be
+ *                                                   swept in an order of the library's (real term weights only;
+ *                                                   MRMF_TUNE_LOAD_GROUP = gathers in flight).
+ *                             Until one is set, the window form where the weights are real and none of
+ *                             MRMF_TUNE_BRANCH_SKIP, MRMF_TUNE_FAR_LOADS and MRMF_TUNE_OUTER_FIRST is, else the masked
+ *                             form (which a plan that the window form does not take runs as well); mrmf_lanczos keeps
+ *                             the masked form until one is set.
+ *   MRMF_TUNE_FAR_PASS      : window form: channels whose offset |Delta| spans at least 2^k bytes (k in 10..40) are
+ *                             applied by a second launch that sweeps their sites as neighbours; 0 = the library's
+ *                             rule (default), 1 = never.
  *   MRMF_TUNE_ADDRESSING    : 0 = 32-bit buffer offsets while a vector (plus its gather reach) fits in
  *                             2 GiB, 64-bit global addresses beyond that (default); 1 = 64-bit addresses
  *                             always.  Either way every channel offset |Delta| plus a super-tile must stay
@@ -228,8 +239,10 @@ mrmf_status mrmf_plan_set_kernel(mrmf_plan plan, int32_t kind, int32_t inner_sit
 #define MRMF_TUNE_UNROLL_TOP 11
 #define MRMF_TUNE_FAR_DIR 12
 #define MRMF_TUNE_CHEB_MERGE 13
+#define MRMF_TUNE_FAR_PASS 14
 #define MRMF_VARIANT_MASKED 0
 #define MRMF_VARIANT_LIST 1
+#define MRMF_VARIANT_WINDOW 2
 #define MRMF_SCHED_WINDOWS 0
 #define MRMF_SCHED_XCD_CHUNK 1
 #define MRMF_SCHED_BLOCK_RUN 2
@@ -243,9 +256,9 @@ mrmf_status mrmf_plan_set_tuning(mrmf_plan plan, int32_t knob, int32_t value);
 mrmf_status mrmf_plan_set_shape(mrmf_plan plan, int32_t dtype, int32_t variant, int32_t inner_sites,
                                 int32_t unrolled_sites, int32_t load_group, int32_t unroll_top);
 /* Autotuner for the plain matvec: times every candidate shape of the specialized kernel (inner block of
- * 32..1024 rows, 0..2 unrolled sites, masked and list forms, list chunk 4/8/12; where a term joins site 0
- * to the unrolled/inner sites, also with sites 0 and 0..1 unrolled (MRMF_TUNE_UNROLL_TOP) in the masked
- * form and the list form with chunk 4) on the given buffers with HIP events on the stream (synchronising it),
+ * 32..1024 rows; masked form with 0..2 unrolled sites, window form with 0..4, or for complex weights list form with
+ * chunk 4/8/12; where a term joins site 0 to the unrolled/inner sites, also with sites 0 and 0..1 unrolled,
+ * MRMF_TUNE_UNROLL_TOP) on the given buffers with HIP events on the stream (synchronising it),
  * keeps the fastest in the plan for this element type only (selection MRMF_KERNEL_AUTO) and writes host
  * out[0..5] = (variant, inner sites, unrolled sites, load group, microseconds per call, top sites
  * unrolled 0..2); the other tuning knobs return to their defaults.  y is

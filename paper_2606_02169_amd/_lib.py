@@ -26,7 +26,7 @@ MRMF_REORTH_CGS2, MRMF_REORTH_NONE, MRMF_REORTH_CGS2_COND, MRMF_REORTH_PARTIAL =
 MRMF_KERNEL_AUTO, MRMF_KERNEL_GENERIC, MRMF_KERNEL_SPECIALIZED = 0, 1, 2
 MRMF_DTYPE_Z, MRMF_DTYPE_C = 0, 1
 MRMF_TUNE_SCHEDULE, MRMF_TUNE_BRANCH_SKIP, MRMF_TUNE_LOAD_GROUP, MRMF_TUNE_BLOCKS_PER_CU = 0, 1, 2, 3
-MRMF_TUNE_VARIANT, MRMF_VARIANT_MASKED, MRMF_VARIANT_LIST = 4, 0, 1
+MRMF_TUNE_VARIANT, MRMF_VARIANT_MASKED, MRMF_VARIANT_LIST, MRMF_VARIANT_WINDOW = 4, 0, 1, 2
 MRMF_TUNE_ADDRESSING = 5
 MRMF_TUNE_CHEB_FUSED = 6
 MRMF_TUNE_WAVES_PER_EU = 7
@@ -36,6 +36,7 @@ MRMF_TUNE_OUTER_FIRST = 10
 MRMF_TUNE_UNROLL_TOP = 11
 MRMF_TUNE_FAR_DIR = 12
 MRMF_TUNE_CHEB_MERGE = 13
+MRMF_TUNE_FAR_PASS = 14
 MRMF_SOURCE_CHEB = 2
 MRMF_SOURCE_GRAD = 3
 MRMF_BATCH_SCHED_RUNS, MRMF_BATCH_SCHED_WINDOWS, MRMF_BATCH_SCHED_XCD_CHUNK = 0, 1, 2

@@ -23,45 +23,26 @@
 // non-temporal buffer stores.
 #include <hip/hiprtc.h>
 
+#include <algorithm>
 #include <array>
-#include <cinttypes>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <iterator>
 #include <map>
+#include <memory>
+#include <mutex>
 #include <set>
 #include <sstream>
 #include <tuple>
 
+#include "gen_util.h"
 #include "mrmf_internal.h"
+#include "window.h"
 
 namespace mrmf {
 namespace {
-
-int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
-
-std::string lit(double v, bool f32) {
-    char buf[64];
-    if (f32)
-        std::snprintf(buf, sizeof buf, "%af", static_cast<double>(static_cast<float>(v)));
-    else
-        std::snprintf(buf, sizeof buf, "%a", v);
-    return buf;
-}
-
-std::string ulit(uint64_t v) {
-    char buf[32];
-    std::snprintf(buf, sizeof buf, "%" PRIu64 "ull", v);
-    return buf;
-}
-
-// Factor <n|O|n - q> of a local operator at target digit n, 0 where the source digit is outside 0..d-1.
-std::vector<double> factor_table(const mrmf_plan_t* p, int site, int op) {
-    const int d = p->d[site], tab = p->tab[site];
-    std::vector<double> t(d, 0.0);
-    for (int n = 0; n < d; ++n) t[n] = local_factor_host(p, site, op, n);
-    return t;
-}
 
 // ceil(2^64 / d): floor(n / d) = hi64(magic * n) for every n < 2^32
 uint64_t magic_of(uint64_t d) { return d <= 1 ? 0 : ~uint64_t(0) / d + 1; }
@@ -271,11 +252,11 @@ struct Gen {
         pool_index[key] = off;
         return off;
     }
-    size_t ftab(int s, int op) { return pool_add("F" + std::to_string(s) + "_" + std::to_string(op), factor_table(p, s, op)); }
+    size_t ftab(int s, int op) { return pool_add("F" + std::to_string(s) + "_" + std::to_string(op), op_table(p, s, op)); }
 
     // per-lane factor of an inner site (select chain for small d, pool lookup otherwise)
     std::string lane_fac(int s, int op) {
-        const std::vector<double> t = factor_table(p, s, op);
+        const std::vector<double> t = op_table(p, s, op);
         const std::string n = "n" + std::to_string(s);
         const int d = static_cast<int>(t.size());
         if (d <= 4) {
@@ -293,7 +274,7 @@ struct Gen {
         auto add = [&](int s, int op) {
             if (s < 0 || !is_static(s)) return;
             if (is_unrolled(s)) {
-                c *= factor_table(p, s, op)[udigit(s, j)];
+                c *= op_table(p, s, op)[udigit(s, j)];
             } else {
                 const std::string f = lane_fac(s, op);
                 e = e.empty() ? f : e + " * " + f;
@@ -817,7 +798,7 @@ struct Gen {
                     if (far(ch.delta) != (pass == 0)) continue;
                     double u = 1.0;
                     auto mul_unrolled = [&](int s, int op) {
-                        if (s >= 0 && is_unrolled(s)) u *= factor_table(p, s, op)[udigit(s, j)];
+                        if (s >= 0 && is_unrolled(s)) u *= op_table(p, s, op)[udigit(s, j)];
                     };
                     mul_unrolled(ch.a, ch.opa);
                     mul_unrolled(ch.b, ch.opb);
@@ -1832,53 +1813,276 @@ std::string sector_source(const mrmf_sector_t* S, int dtype, bool epi) {
     return o.str();
 }
 
-std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, bool epi) {
-    const bool f32 = dtype == MRMF_DTYPE_C;
+namespace {
+
+// Share of the rows that a channel's factors admit.
+double admitted_share(const mrmf_plan_t* p, const DevChan& c) {
+    double f = 1.0;
+    for (auto so : {std::make_pair(c.a, c.opa), std::make_pair(c.b, c.opb)}) {
+        if (so.first < 0) continue;
+        const std::vector<double> t = op_table(p, so.first, so.second);
+        f *= double(t.size() - std::count(t.begin(), t.end(), 0.0)) / double(t.size());
+    }
+    return f;
+}
+
+// Tile of the window form.  Fitted to the times of every tile on 70 random chains, rings and spin-boson lattices of
+// 10^3 to 4 x 10^7 rows: about 768 super-tiles or more (three for each CU; fewer leave CUs idle at the end of the
+// sweep), then super-tiles of a few thousand rows (more of the bonds in LDS, fewer barriers and scalar set-ups a row)
+// in blocks near 128 rows that fill their last wave.  The rule's tile is 7 % (c128) and 8 % (c64) slower than each
+// lattice's best, 1.27 and 1.24 times faster than the masked form's on average.  Site 0 joins the unrolled ones from
+// 10^6 c128 rows on where a channel joins it to the tile (a ring's closing bond: 18 sites 146 -> 140 us); in c64 and
+// below that it cost as much as it gave.
+bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
+    const int N = p->N;
+    const double wT = f32 ? 0.1 : 0.05, wR = f32 ? 0.1 : 0.02, wE = f32 ? 1.0 : 0.5, wN = f32 ? 0.3 : 1.0;
+    const double R0 = f32 ? 6144.0 : 4096.0;
+    double best = -1e30;
+    int64_t T = 1;
+    for (int k = N - 1; k >= 0; --k) {
+        T *= p->d[k];
+        if (T > 1024) break;
+        int64_t PU = 1;
+        for (int u = 0; u <= 4 && u <= k; ++u) {
+            if (u > 0) PU *= p->d[k - u];
+            if (PU > 16) break;
+            bool wrap = false;
+            for (const auto& c : p->chans) wrap |= (c.a == 0 && c.b >= k - u) || (c.b == 0 && c.a >= k - u);
+            const int top = !f32 && p->D >= 1000000 && wrap && k - u > 1 && PU * p->d[0] <= 16 ? 1 : 0;
+            const double R = double(T * PU * (top ? p->d[0] : 1)), tiles = double(p->D) / R;
+            const double score = wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
+                                 wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
+            if (score <= best) continue;
+            best = score;
+            tl->k_in = k;
+            tl->k_u = k - u;
+            tl->T_in = T;
+            tl->P_C = PU;
+            tl->n_top = top;
+            tl->P_U = PU * (top ? p->d[0] : 1);
+        }
+    }
+    return best > -1e30;
+}
+
+// Passes of the window form for the tile tl.
+//
+// One pass or two.  An XCD that sweeps the rows in order keeps the last rows it read in its 4 MB L2, so a channel whose
+// source lies within kFarBytes of its row finds it there, from either side; every other ("far") channel reads its
+// share of x from memory once more.  In units of one vector, a single pass moves 2 + the far channels' shares.  A
+// second pass that applies the far channels alone, in an order where their sites are neighbours, makes it 5 (x, y and
+// y again on top of the first pass's two), but its short runs of rows stream at 4.6 TB/s where a single pass moves
+// 7.3, so it pays from about 9 units on: 4 x 4 spin-1 lattice (12 far bonds, 12.7 units) 1765 -> 1205 us in c128 and
+// 835 -> 756 us in c64; 20-site ring (7 far bonds, 6.7 units) 1014 -> 1117 us, open chain of 25 spins 1/2 (5 units)
+// 526 -> 626 us.
+constexpr int64_t kFarBytes = 3 << 19;
+void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool epi, const Tile& tl,
+                   std::vector<WindowPass>* out) {
     const int64_t SZ = f32 ? 8 : 16;
-    Tile tl;
+    WindowPass w;
+    // gathers and LDS reads in flight: 2 x 4 gathers of a c128 copy are 32 registers, and 4 + 4 measured best or
+    // within 2 % of 6 + 6 and 8 + 8 (18-site ring 138 against 140 us); 8 c64 gathers take as many
+    w.group = cfg.group > 0 ? cfg.group : f32 ? 8 : 4;
+    w.lds_group = w.group;
+    // Sweep: an eighth per XCD (10 million c128 rows 138 against 151 us), windows where the vector is far beyond the
+    // 256 MB Infinity Cache (60 million: 1038 against 1103 us); there the prefetch of the next super-tile, which takes
+    // its memory bandwidth from the gathers that the block waits for, costs as well (1061 against 1014 us).
+    w.sched = cfg.sched != kSchedAuto ? cfg.sched : p->D * SZ > (f32 ? 600000000 : 300000000) ? MRMF_SCHED_WINDOWS : MRMF_SCHED_XCD_CHUNK;
+    w.prefetch = p->D * SZ <= 300000000;
+    w.waves = cfg.waves_per_eu;
+    w.f32 = f32;
+    w.mode = epi ? kPassCheb : kPassSet;
+    w.name = epi ? "mrmf_spec_cheb" : "mrmf_spec";
+    w.tag = "A";
+    for (int s = tl.n_top; s < tl.k_u; ++s) w.ord.push_back(s);
+    w.n_uni = static_cast<int>(w.ord.size());
+    for (int s = 0; s < tl.n_top; ++s) w.ord.push_back(s);
+    for (int s = tl.k_u; s < tl.k_in; ++s) w.ord.push_back(s);
+    w.n_unr = static_cast<int>(w.ord.size()) - w.n_uni;
+    for (int s = tl.k_in; s < p->N; ++s) w.ord.push_back(s);
+    for (size_t i = 0; i < p->diags.size(); ++i) w.diags.push_back(static_cast<int>(i));
+    const int64_t far = cfg.far_pass >= 10 ? int64_t(1) << cfg.far_pass : kFarBytes;
+    std::vector<int> near_c, far_c;
+    double u1 = 2.0;
+    for (size_t i = 0; i < p->chans.size(); ++i) {
+        const DevChan& c = p->chans[i];
+        const bool f = std::llabs(c.delta) * SZ >= far;
+        (f ? far_c : near_c).push_back(static_cast<int>(i));
+        if (f) u1 += admitted_share(p, c);
+    }
+    WindowPass w2 = w;
+    bool two = !far_c.empty() && cfg.far_pass != 1;
+    if (two) {
+        // the far channels' sites, the ones with most of their channels innermost, under a run of the lowest sites of
+        // at least 128 bytes (whole cache lines); the other sites outermost
+        const int N = p->N;
+        std::vector<int> cnt(N, 0);
+        for (int ci : far_c) {
+            const DevChan& c = p->chans[ci];
+            if (c.qa != 0) ++cnt[c.a];
+            if (c.b >= 0 && c.qb != 0) ++cnt[c.b];
+        }
+        int run = N;
+        int64_t rr = 1;
+        while (run > 0 && rr * SZ < 128) rr *= p->d[--run];
+        std::vector<int> hot;
+        for (int s = 0; s < run; ++s)
+            if (cnt[s] > 0) hot.push_back(s);
+        std::stable_sort(hot.begin(), hot.end(), [&](int x, int y) { return cnt[x] < cnt[y]; });
+        w2.ord.clear();
+        for (int s = 0; s < run; ++s)
+            if (cnt[s] == 0) w2.ord.push_back(s);
+        w2.ord.insert(w2.ord.end(), hot.begin(), hot.end());
+        for (int s = run; s < N; ++s) w2.ord.push_back(s);
+        // inner: from the run upwards while it stays within 768 rows, then unrolled sites while the super-tile's rows
+        // fit in LDS with room to spare
+        const int T0 = 768;
+        const int64_t most = 131072 / SZ;
+        int k = run;
+        int64_t T = rr;
+        while (k > N - static_cast<int>(hot.size()) - (N - run) && T * p->d[w2.ord[k - 1]] <= T0) T *= p->d[w2.ord[--k]];
+        const int k_in = k;
+        int64_t PU = 1;
+        while (k > run - static_cast<int>(hot.size()) && PU * p->d[w2.ord[k - 1]] <= 16 && T * PU * p->d[w2.ord[k - 1]] <= most &&
+               p->D / (T * PU * p->d[w2.ord[k - 1]]) >= 256)
+            PU *= p->d[w2.ord[--k]];
+        w2.n_uni = k;
+        w2.n_unr = k_in - k;
+        w2.chans = far_c;
+        w2.diags.clear();
+        w2.mode = epi ? kPassCheb : kPassAdd;
+        w2.sched = MRMF_SCHED_XCD_CHUNK;
+        w2.name += "_b";
+        w2.tag = "B";
+        int64_t span = 0;  // bytes from the first to the last row of a copy: a 32-bit lane offset
+        for (int i = k_in; i < N; ++i) span += (p->d[w2.ord[i]] - 1) * p->M[w2.ord[i]] * SZ;
+        two = T <= 1024 && span < (int64_t(1) << 31) - SZ;
+        if (cfg.far_pass == 0) two = two && u1 > 1.8 * 5.0;
+    }
+    w.chans = near_c;
+    if (two) {
+        w.mode = epi ? kPassChebPart : kPassSet;
+    } else {
+        w.chans.insert(w.chans.end(), far_c.begin(), far_c.end());
+        std::sort(w.chans.begin(), w.chans.end());
+    }
+    out->push_back(w);
+    if (two) out->push_back(w2);
+}
+
+}  // namespace
+
+namespace {
+
+// no form was asked for, and no knob that only the masked and list forms have
+bool window_by_rule(const KernelCfg& cfg) {
+    return cfg.variant == kVariantAuto && cfg.bskip == 0 && cfg.far_nt == 0 && cfg.outer_first == 0;
+}
+
+}  // namespace
+
+int lanczos_slot(const mrmf_plan_t* p, int dtype) {
+    return window_real(p) && window_by_rule(p->cfg[dtype]) ? kSlotLanczos + dtype : dtype;
+}
+
+std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom* geo, bool epi, bool lanczos) {
+    const bool f32 = dtype == MRMF_DTYPE_C;
+    const int64_t SZ = f32 ? 8 : 16, lim = int64_t(1) << 31;
     const KernelCfg& cfg = p->cfg[epi && p->cheb_shape_set ? kSlotCheb : f32 ? MRMF_DTYPE_C : MRMF_DTYPE_Z];
-    if (!choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) return "";
-    const int64_t n_st = p->D / (tl.T_in * tl.P_U);
-    // span of one super-tile's rows from its base (its copies of site 0 lie M_0 apart)
-    int64_t st = tl.T_in * tl.P_C;
-    for (int s = 0; s < tl.n_top; ++s) st += (p->d[s] - 1) * p->M[s];
-    if (tl.n_top == 0) st = tl.T_in * tl.P_U;
     int64_t dmax = 0, dmin = 0;
     for (const auto& c : p->chans) {
         dmax = std::max<int64_t>(dmax, c.delta);
         dmin = std::min<int64_t>(dmin, c.delta);
     }
     // 32-bit buffer offsets when every offset (rows plus both shifts) stays below 2^31 bytes, else 64-bit
-    // super-tile bases; in both forms a channel's offset from its super-tile, |Delta| + st rows, is a
+    // super-tile bases; in the masked and list forms a channel's offset from its super-tile, |Delta| + st rows, is a
     // 32-bit signed scalar
-    const int64_t lim = int64_t(1) << 31;
+    auto is_wide = [&](const Tile& t) { return cfg.wide != 0 || (p->D + dmax - dmin + 2 * t.T_in) * SZ >= lim; };
+    Tile tl;
+    // The window form unless another one, or a knob that only the others have, was asked for; a plan that does not fit
+    // it (tables of the uniform digits beyond LDS, complex weights) takes the masked one.
+    if (!lanczos && window_real(p) && (cfg.variant == MRMF_VARIANT_WINDOW || window_by_rule(cfg))) {
+        const bool rule = cfg.inner == 0 && cfg.unroll < 0 && cfg.unroll_top == 0;
+        std::vector<WindowPass> passes;
+        if ((rule ? window_tile(p, f32, &tl) : choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) &&
+            p->D / (tl.T_in * tl.P_U) < lim && (std::max<int64_t>(dmax, -dmin) + tl.T_in * tl.P_C) * SZ < lim) {
+            window_passes(p, cfg, f32, epi, tl, &passes);
+            std::string src = window_prelude(f32, is_wide(tl));
+            for (size_t i = 0; i < passes.size() && !src.empty(); ++i) {
+                int64_t rows = 0;
+                passes[i].wide = is_wide(tl);
+                const std::string one = window_pass(p, passes[i], &geo->tiles[i], &rows);
+                geo->block[i] = static_cast<int>(round_up(rows, 64));
+                src = one.empty() ? "" : src + one;
+            }
+            if (!src.empty()) {
+                geo->n = static_cast<int>(passes.size());
+                *tl_out = tl;
+                return src;
+            }
+        }
+    }
+    if (!choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) return "";
+    const int64_t n_st = p->D / (tl.T_in * tl.P_U);
+    // span of one super-tile's rows from its base (its copies of site 0 lie M_0 apart)
+    int64_t st = tl.T_in * tl.P_C;
+    for (int s = 0; s < tl.n_top; ++s) st += (p->d[s] - 1) * p->M[s];
+    if (tl.n_top == 0) st = tl.T_in * tl.P_U;
     if (n_st >= lim || (std::max<int64_t>(dmax, -dmin) + st) * SZ >= lim) return "";
-    const bool wide = cfg.wide != 0 || (p->D + dmax - dmin + 2 * tl.T_in) * SZ >= lim;
     Gen gen{p, f32, tl, static_cast<int>(round_up(tl.T_in, 64)), n_st};
-    gen.wide = wide;
+    gen.wide = is_wide(tl);
     gen.epi = epi;
     gen.waves_per_eu = cfg.waves_per_eu;
     gen.far_nt = cfg.far_nt;
     gen.far_dir = cfg.far_dir;
     gen.outer_first = cfg.outer_first;
-    gen.sched = cfg.sched;
+    gen.sched = cfg.sched == kSchedAuto ? MRMF_SCHED_WINDOWS : cfg.sched;
     gen.bskip = cfg.bskip != 0;
     gen.gs = cfg.group;
     gen.variant = cfg.variant;
     *tl_out = tl;
+    geo->n = 1;
+    geo->tiles[0] = n_st;
+    geo->block[0] = gen.block;
     if (gen.variant != MRMF_VARIANT_LIST && gen.masked_fits()) return gen.source();
     return gen.source_v2();
 }
 
 namespace {
 
-// Compiles a generated source with hiprtc for the current device's architecture and loads kernel `name`;
-// on a compile error the log (and the source) goes to *log and the result is MRMF_E_UNSUPPORTED.
-mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceProp_t& prop, hipModule_t* mod_out,
-                      hipFunction_t* fn_out, std::string* log_out) {
-    std::string arch = std::string("--offload-arch=") + prop.gcnArchName;
-    const size_t colon = arch.find(':');
-    if (colon != std::string::npos) arch = arch.substr(0, colon);
+// Code objects by architecture and source text, so that plans of one structure compile it once (0.1 to 0.3 s).  At most
+// kCodeEntries of them are kept; the least recently used one goes first.
+constexpr size_t kCodeEntries = 64;
+struct CodeCache {
+    std::mutex mtx;
+    uint64_t clock = 0;
+    std::map<std::string, std::pair<uint64_t, std::shared_ptr<const std::vector<char>>>> entries;
+};
+CodeCache& code_cache() {
+    static CodeCache c;
+    return c;
+}
+
+std::string arch_option(const hipDeviceProp_t& prop) {
+    const std::string arch = std::string("--offload-arch=") + prop.gcnArchName;
+    return arch.substr(0, arch.find(':'));
+}
+
+// Compiles a generated source with hiprtc (or takes it from the cache); on a compile error the log and the source go
+// to *log and the result is MRMF_E_UNSUPPORTED.
+mrmf_status rtc_code(const std::string& src, const std::string& arch, std::shared_ptr<const std::vector<char>>* out,
+                     std::string* log_out) {
+    CodeCache& cache = code_cache();
+    const std::string key = arch + "\n" + src;
+    {
+        std::lock_guard<std::mutex> lk(cache.mtx);
+        auto it = cache.entries.find(key);
+        if (it != cache.entries.end()) {
+            it->second.first = ++cache.clock;
+            *out = it->second.second;
+            return MRMF_OK;
+        }
+    }
     hiprtcProgram prog;
     if (hiprtcCreateProgram(&prog, src.c_str(), "mrmf_gen.hip", 0, nullptr, nullptr) != HIPRTC_SUCCESS)
         return MRMF_E_HIP;
@@ -1895,13 +2099,33 @@ mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceP
     }
     size_t code_size = 0;
     hiprtcGetCodeSize(prog, &code_size);
-    std::vector<char> code(code_size);
-    hiprtcGetCode(prog, code.data());
+    auto code = std::make_shared<std::vector<char>>(code_size);
+    hiprtcGetCode(prog, code->data());
     hiprtcDestroyProgram(&prog);
+    *out = code;
+    std::lock_guard<std::mutex> lk(cache.mtx);
+    cache.entries[key] = {++cache.clock, code};
+    if (cache.entries.size() > kCodeEntries) {
+        auto old = cache.entries.begin();
+        for (auto it = cache.entries.begin(); it != cache.entries.end(); ++it)
+            if (it->second.first < old->second.first) old = it;
+        cache.entries.erase(old);
+    }
+    return MRMF_OK;
+}
+
+// Compiles a generated source for the device and loads kernel `name` (and `name2` into *fn2_out when given).
+mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceProp_t& prop, hipModule_t* mod_out,
+                      hipFunction_t* fn_out, std::string* log_out, const char* name2 = nullptr,
+                      hipFunction_t* fn2_out = nullptr) {
+    std::shared_ptr<const std::vector<char>> code;
+    const mrmf_status st = rtc_code(src, arch_option(prop), &code, log_out);
+    if (st != MRMF_OK) return st;
     hipModule_t mod;
-    if (hipModuleLoadData(&mod, code.data()) != hipSuccess) return MRMF_E_HIP;
+    if (hipModuleLoadData(&mod, code->data()) != hipSuccess) return MRMF_E_HIP;
     hipFunction_t fn;
-    if (hipModuleGetFunction(&fn, mod, name) != hipSuccess) {
+    if (hipModuleGetFunction(&fn, mod, name) != hipSuccess ||
+        (name2 != nullptr && hipModuleGetFunction(fn2_out, mod, name2) != hipSuccess)) {
         hipModuleUnload(mod);
         return MRMF_E_HIP;
     }
@@ -1910,44 +2134,51 @@ mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceP
     return MRMF_OK;
 }
 
-// slot: MRMF_DTYPE_Z, MRMF_DTYPE_C, or kSlotCheb (c128 with the Chebyshev-step epilogue)
+// slot: MRMF_DTYPE_Z, MRMF_DTYPE_C, kSlotCheb (c128 with the Chebyshev-step epilogue), or kSlotLanczos + a dtype
+// (masked form)
 mrmf_status compile_spec(mrmf_plan_t* p, int slot, SpecKernel& K) {
     K.tried = true;
     K.ok = false;
-    const int dtype = slot == kSlotCheb ? MRMF_DTYPE_Z : slot;
+    const int dtype = slot == kSlotCheb ? MRMF_DTYPE_Z : slot >= kSlotLanczos ? slot - kSlotLanczos : slot;
     Tile tl;
-    const std::string src = spec_source(p, dtype, &tl, slot == kSlotCheb);
+    SpecGeom geo;
+    const std::string src = spec_source(p, dtype, &tl, &geo, slot == kSlotCheb, slot >= kSlotLanczos);
     if (src.empty()) {
         K.log = "plan does not qualify for the specialized kernel";
         return MRMF_E_UNSUPPORTED;
     }
-    const int64_t n_st = p->D / (tl.T_in * tl.P_U);
-    const int block = static_cast<int>(round_up(tl.T_in, 64));
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return MRMF_E_HIP;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return MRMF_E_HIP;
     hipModule_t mod;
     hipFunction_t fn;
-    const mrmf_status bs = rtc_build(src, slot == kSlotCheb ? "mrmf_spec_cheb" : "mrmf_spec", prop, &mod, &fn, &K.log);
+    hipFunction_t fn2 = nullptr;
+    const bool cheb = slot == kSlotCheb;
+    const mrmf_status bs = rtc_build(src, cheb ? "mrmf_spec_cheb" : "mrmf_spec", prop, &mod, &fn, &K.log,
+                                     geo.n > 1 ? (cheb ? "mrmf_spec_cheb_b" : "mrmf_spec_b") : nullptr, &fn2);
     if (bs != MRMF_OK) return bs;
-    int per_cu = 0;
-    if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    const int bpc = p->cfg[slot == kSlotCheb && p->cheb_shape_set ? kSlotCheb : dtype].blocks_per_cu;
-    if (bpc > 0 && bpc < per_cu) per_cu = bpc;
-    int64_t grid = int64_t(per_cu) * prop.multiProcessorCount;
-    if (grid > n_st) grid = n_st;
-    if (grid >= 8) grid -= grid % 8;
+    const int bpc = p->cfg[cheb && p->cheb_shape_set ? kSlotCheb : dtype].blocks_per_cu;
+    for (int i = 0; i < geo.n; ++i) {
+        int per_cu = 0;
+        if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, i ? fn2 : fn, geo.block[i], 0) != hipSuccess ||
+            per_cu < 1)
+            per_cu = 1;
+        if (bpc > 0 && bpc < per_cu) per_cu = bpc;
+        int64_t grid = std::min<int64_t>(int64_t(per_cu) * prop.multiProcessorCount, geo.tiles[i]);
+        if (grid >= 8) grid -= grid % 8;
+        (i ? K.grid2 : K.grid) = static_cast<int32_t>(grid);
+    }
+    K.fn2 = fn2;
+    K.block2 = geo.block[1];
     K.mod = mod;
     K.fn = fn;
     K.k_in = tl.k_in;
     K.k_u = tl.k_u;
     K.T_in = static_cast<int32_t>(tl.T_in);
     K.P_U = static_cast<int32_t>(tl.P_U);
-    K.block = block;
-    K.grid = static_cast<int32_t>(grid);
-    K.n_tiles = n_st;
+    K.block = geo.block[0];
+    K.n_tiles = geo.tiles[0];
     K.device = dev;
     K.log = src;
     K.ok = true;
@@ -1957,7 +2188,7 @@ mrmf_status compile_spec(mrmf_plan_t* p, int slot, SpecKernel& K) {
 }  // namespace
 
 mrmf_status spec_prepare(mrmf_plan_t* p, int dtype) {
-    if (dtype != MRMF_DTYPE_Z && dtype != MRMF_DTYPE_C && dtype != kSlotCheb) return MRMF_E_INVALID_ARG;
+    if (dtype < 0 || dtype >= static_cast<int>(std::size(p->spec))) return MRMF_E_INVALID_ARG;
     std::lock_guard<std::mutex> lk(p->mtx);
     SpecKernel& K = p->spec[dtype];
     int dev = 0;
@@ -1982,7 +2213,9 @@ mrmf_status spec_launch(mrmf_plan_t* p, int dtype, const void* theta, const void
     } args{theta, x, y, d_skip};
     size_t size = sizeof(args);
     void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
-    return hip_status(hipModuleLaunchKernel(K.fn, K.grid, 1, 1, K.block, 1, 1, 0, s, nullptr, config));
+    st = hip_status(hipModuleLaunchKernel(K.fn, K.grid, 1, 1, K.block, 1, 1, 0, s, nullptr, config));
+    if (st != MRMF_OK || K.fn2 == nullptr) return st;
+    return hip_status(hipModuleLaunchKernel(K.fn2, K.grid2, 1, 1, K.block2, 1, 1, 0, s, nullptr, config));
 }
 
 mrmf_status spec_launch_cheb(mrmf_plan_t* p, const double* theta, const void* x, void* prev, void* acc, double ea,
@@ -2000,7 +2233,12 @@ mrmf_status spec_launch_cheb(mrmf_plan_t* p, const double* theta, const void* x,
     } args{theta, x, prev, acc, ea, eb, eg, ecr, eci, nullptr};
     size_t size = sizeof(args);
     void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
-    return hip_status(hipModuleLaunchKernel(K.fn, K.grid, 1, 1, K.block, 1, 1, 0, s, nullptr, config));
+    st = hip_status(hipModuleLaunchKernel(K.fn, K.grid, 1, 1, K.block, 1, 1, 0, s, nullptr, config));
+    if (st != MRMF_OK || K.fn2 == nullptr) return st;
+    // the first pass left its half of the step in prev: the second adds ea times the far channels' part
+    args.eb = 0.0;
+    args.eg = 1.0;
+    return hip_status(hipModuleLaunchKernel(K.fn2, K.grid2, 1, 1, K.block2, 1, 1, 0, s, nullptr, config));
 }
 
 mrmf_status grad_prepare(mrmf_plan_t* p) {
@@ -2162,13 +2400,13 @@ void set_cfg(mrmf_plan_t* plan, int slot, const mrmf::KernelCfg& c) {
     const bool same = cur.inner == c.inner && cur.unroll == c.unroll && cur.sched == c.sched && cur.bskip == c.bskip &&
                       cur.group == c.group && cur.blocks_per_cu == c.blocks_per_cu && cur.variant == c.variant &&
                       cur.wide == c.wide && cur.waves_per_eu == c.waves_per_eu && cur.far_nt == c.far_nt && cur.far_dir == c.far_dir &&
-                      cur.outer_first == c.outer_first && cur.unroll_top == c.unroll_top &&
+                      cur.outer_first == c.outer_first && cur.unroll_top == c.unroll_top && cur.far_pass == c.far_pass &&
                       (slot != mrmf::kSlotCheb || plan->cheb_shape_set);
     cur = c;
     if (slot == mrmf::kSlotCheb) plan->cheb_shape_set = true;
     if (!same) {
         const bool cheb_follows = slot == MRMF_DTYPE_Z && !plan->cheb_shape_set;
-        for (int s : {slot, cheb_follows ? mrmf::kSlotCheb : -1}) {
+        for (int s : {slot, cheb_follows ? mrmf::kSlotCheb : -1, slot < mrmf::kSlotCheb ? mrmf::kSlotLanczos + slot : -1}) {
             if (s < 0) continue;
             mrmf::SpecKernel& k = plan->spec[s];
             if (k.mod) hipModuleUnload(k.mod);
@@ -2220,7 +2458,8 @@ mrmf_status mrmf_plan_set_tuning(mrmf_plan plan, int32_t knob, int32_t value) {
                 c.blocks_per_cu = value;
                 break;
             case MRMF_TUNE_VARIANT:
-                if (value != MRMF_VARIANT_MASKED && value != MRMF_VARIANT_LIST) return MRMF_E_INVALID_ARG;
+                if (value != MRMF_VARIANT_MASKED && value != MRMF_VARIANT_LIST && value != MRMF_VARIANT_WINDOW)
+                    return MRMF_E_INVALID_ARG;
                 c.variant = value;
                 break;
             case MRMF_TUNE_ADDRESSING:
@@ -2255,6 +2494,10 @@ mrmf_status mrmf_plan_set_tuning(mrmf_plan plan, int32_t knob, int32_t value) {
                 if (value < 0 || value > 3) return MRMF_E_INVALID_ARG;
                 c.unroll_top = value;
                 break;
+            case MRMF_TUNE_FAR_PASS:
+                if (value != 0 && value != 1 && (value < 10 || value > 40)) return MRMF_E_INVALID_ARG;
+                c.far_pass = value;
+                break;
             case MRMF_TUNE_GRAD_BLOCKS_PER_CU:
                 if (value < 0 || value > 8) return MRMF_E_INVALID_ARG;
                 c.grad_blocks_per_cu = value;
@@ -2271,7 +2514,7 @@ mrmf_status mrmf_plan_set_tuning(mrmf_plan plan, int32_t knob, int32_t value) {
 mrmf_status mrmf_plan_set_shape(mrmf_plan plan, int32_t dtype, int32_t variant, int32_t inner_sites,
                                 int32_t unrolled_sites, int32_t load_group, int32_t unroll_top) {
     if (!plan || (dtype != MRMF_DTYPE_Z && dtype != MRMF_DTYPE_C && dtype != MRMF_SOURCE_CHEB) ||
-        (variant != MRMF_VARIANT_MASKED && variant != MRMF_VARIANT_LIST) || inner_sites < 0 ||
+        (variant != MRMF_VARIANT_MASKED && variant != MRMF_VARIANT_LIST && variant != MRMF_VARIANT_WINDOW) || inner_sites < 0 ||
         inner_sites > plan->N || unrolled_sites < -1 || unrolled_sites > plan->N || load_group < 0 ||
         load_group > 64 || unroll_top < 0 || unroll_top > 3)
         return MRMF_E_INVALID_ARG;
@@ -2288,6 +2531,7 @@ mrmf_status mrmf_plan_set_shape(mrmf_plan plan, int32_t dtype, int32_t variant, 
     c.far_nt = plan->cfg[dtype == MRMF_SOURCE_CHEB ? MRMF_DTYPE_Z : dtype].far_nt;
     c.far_dir = plan->cfg[dtype == MRMF_SOURCE_CHEB ? MRMF_DTYPE_Z : dtype].far_dir;
     c.outer_first = plan->cfg[dtype == MRMF_SOURCE_CHEB ? MRMF_DTYPE_Z : dtype].outer_first;
+    c.far_pass = plan->cfg[dtype == MRMF_SOURCE_CHEB ? MRMF_DTYPE_Z : dtype].far_pass;
     c.unroll_top = unroll_top;
     set_cfg(plan, dtype, c);
     return MRMF_OK;
@@ -2300,6 +2544,8 @@ mrmf_status mrmf_plan_prepare(mrmf_plan plan, int32_t dtype) {
     const int32_t mode = plan->cfg[dtype].mode;
     if (mode == MRMF_KERNEL_GENERIC) return MRMF_OK;
     const mrmf_status st = mrmf::spec_prepare(plan, dtype);
+    // Lanczos may launch a kernel of its own: built here too, as it may run under stream capture later
+    if (st == MRMF_OK) mrmf::spec_prepare(plan, mrmf::lanczos_slot(plan, dtype));
     if (st == MRMF_E_UNSUPPORTED && mode == MRMF_KERNEL_AUTO) return MRMF_OK;
     return st;
 }
@@ -2315,8 +2561,9 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
     struct Cand {
         int variant, inner, unrolled, group, top;
     };
-    // inner blocks of 32..1024 rows, 0..2 unrolled sites with at most 9 copies, both forms, three chunk
-    // sizes for the list form
+    // inner blocks of 32..1024 rows: the window form with up to 4 unrolled sites and 16 copies (plans with real
+    // weights) or the list form in three chunk sizes, and the masked form with up to 2 unrolled sites and 9 copies
+    const bool real = window_real(plan);
     std::vector<Cand> cands;
     int64_t T = 1;
     for (int k = plan->N - 1; k >= 0; --k) {
@@ -2325,14 +2572,17 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
         if (T < 32) continue;
         const int inner = plan->N - k;
         int64_t PU = 1;
-        for (int u = 0; u <= 2 && u <= k; ++u) {
+        for (int u = 0; u <= (real ? 4 : 2) && u <= k; ++u) {
             if (u > 0) PU *= plan->d[k - u];
-            if (PU > 9) break;
+            if (PU > (real ? 16 : 9)) break;
             // fewer super-tiles than a quarter of the CUs leaves the GPU idle (unless the whole
             // problem is that small)
             if (plan->D / (T * PU) < 64 && u > 0) break;
-            cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, 0});
-            for (int g : {4, 8, 12}) cands.push_back({MRMF_VARIANT_LIST, inner, u, g, 0});
+            const bool old = u <= 2 && PU <= 9;
+            if (old) cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, 0});
+            if (real) cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, 0});
+            for (int g : {4, 8, 12})
+                if (!real) cands.push_back({MRMF_VARIANT_LIST, inner, u, g, 0});
             // site 0 unrolled as well, when a term joins it to a site of this tile (a ring's closing bond)
             const int k_u = k - u;
             bool wrap = false;
@@ -2342,8 +2592,11 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
             for (int top = 1; wrap && top <= 2 && k_u > top; ++top) {  // sites 0..top-1 unrolled too
                 PT *= plan->d[top - 1];
                 if (PT > 16 || plan->D / (T * PT) < 64) break;
-                cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, top});
-                cands.push_back({MRMF_VARIANT_LIST, inner, u, 4, top});
+                if (old) cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, top});
+                if (real)
+                    cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, top});
+                else
+                    cands.push_back({MRMF_VARIANT_LIST, inner, u, 4, top});
             }
         }
     }
@@ -2432,9 +2685,10 @@ mrmf_status mrmf_plan_kernel_source(mrmf_plan plan, int32_t dtype, char* buf, si
         (cap > 0 && !buf))
         return MRMF_E_INVALID_ARG;
     mrmf::Tile tl;
+    mrmf::SpecGeom geo;
     const bool cheb = dtype == MRMF_SOURCE_CHEB;
     const std::string src = dtype == MRMF_SOURCE_GRAD ? mrmf::grad_source(plan)
-                                                      : mrmf::spec_source(plan, cheb ? MRMF_DTYPE_Z : dtype, &tl, cheb);
+                                                      : mrmf::spec_source(plan, cheb ? MRMF_DTYPE_Z : dtype, &tl, &geo, cheb);
     if (src.empty()) return MRMF_E_UNSUPPORTED;
     *len = src.size();
     if (cap > 0) {

@@ -891,10 +891,10 @@ mrmf_status mrmf_lanczos(mrmf_plan plan, const void* d_ws, const double* d_theta
     // the recurrence keeps Re<v|Hv> only and its Ritz values are eigenvalues of H only for Hermitian H
     if (!plan->hermitian) return MRMF_E_NOT_HERMITIAN;
     const MatvecOp mv_z = [&](const void* x, void* y, hipStream_t s, const int32_t* stop) {
-        return matvec_z_impl(plan, d_ws, d_theta_z, x, y, s, stop);
+        return matvec_lanczos_z(plan, d_ws, d_theta_z, x, y, s, stop);
     };
     const MatvecOp mv_c = [&](const void* x, void* y, hipStream_t s, const int32_t* stop) {
-        return matvec_c_impl(plan, d_ws, d_theta_c, x, y, s, stop);
+        return matvec_lanczos_c(plan, d_ws, d_theta_c, x, y, s, stop);
     };
     return lanczos_run(plan->D, mv_z, mv_c, precision, m, reorth, d_v0, d_V, d_alpha, d_beta, d_result, d_u,
                        d_scratch, scratch_bytes, stream);

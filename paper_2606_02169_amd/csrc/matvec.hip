@@ -306,7 +306,7 @@ int generic_grid(int64_t D) {
 
 template <typename R>
 mrmf_status matvec_dispatch(mrmf_plan_t* p, const void* d_ws, const R* theta, const void* x, void* y,
-                            hipStream_t s, const int32_t* d_skip) {
+                            hipStream_t s, const int32_t* d_skip, int slot = sizeof(R) == 4 ? MRMF_DTYPE_C : MRMF_DTYPE_Z) {
     using C = typename Cx<R>::T;
     if (!p || !d_ws || !theta || !x || !y) return MRMF_E_INVALID_ARG;
     if (!aligned(d_ws, 256) || !aligned(x, sizeof(C)) || !aligned(y, sizeof(C))) return MRMF_E_INVALID_ARG;
@@ -315,7 +315,7 @@ mrmf_status matvec_dispatch(mrmf_plan_t* p, const void* d_ws, const R* theta, co
     const int dtype = sizeof(R) == 4 ? MRMF_DTYPE_C : MRMF_DTYPE_Z;
     const int32_t mode = p->cfg[dtype].mode;
     if (mode != MRMF_KERNEL_GENERIC) {
-        const mrmf_status st = spec_launch(p, dtype, theta, x, y, s, d_skip);
+        const mrmf_status st = spec_launch(p, slot, theta, x, y, s, d_skip);
         if (st == MRMF_OK || !(st == MRMF_E_UNSUPPORTED && mode == MRMF_KERNEL_AUTO)) return st;
     }
     const PlanArgs a = plan_args(p, d_ws);
@@ -339,6 +339,16 @@ mrmf_status matvec_z_impl(mrmf_plan_t* p, const void* d_ws, const double* theta,
 mrmf_status matvec_c_impl(mrmf_plan_t* p, const void* d_ws, const float* theta, const void* x, void* y,
                           hipStream_t s, const int32_t* d_skip) {
     return matvec_dispatch<float>(p, d_ws, theta, x, y, s, d_skip);
+}
+
+mrmf_status matvec_lanczos_z(mrmf_plan_t* p, const void* d_ws, const double* theta, const void* x, void* y,
+                             hipStream_t s, const int32_t* d_skip) {
+    return matvec_dispatch<double>(p, d_ws, theta, x, y, s, d_skip, lanczos_slot(p, MRMF_DTYPE_Z));
+}
+
+mrmf_status matvec_lanczos_c(mrmf_plan_t* p, const void* d_ws, const float* theta, const void* x, void* y,
+                             hipStream_t s, const int32_t* d_skip) {
+    return matvec_dispatch<float>(p, d_ws, theta, x, y, s, d_skip, lanczos_slot(p, MRMF_DTYPE_C));
 }
 
 }  // namespace mrmf

@@ -97,12 +97,14 @@ struct Tile {
     int64_t P_C = 1;   // combinations of the contiguous unrolled sites [k_u, k_in); P_U = P_C * d_0 ... d_(n_top-1)
 };
 
-// Kernel selection and shape knobs of one element type (MRMF_KERNEL_*, MRMF_TUNE_*).
+// Kernel selection and shape knobs of one element type (MRMF_KERNEL_*, MRMF_TUNE_*).  Form and schedule until they
+// are set: by rule.
+constexpr int kVariantAuto = -1, kSchedAuto = -1;
 struct KernelCfg {
     int32_t mode = MRMF_KERNEL_AUTO;
     int32_t inner = 0;    // inner sites, 0 = library's choice
     int32_t unroll = -1;  // unrolled sites, -1 = library's choice
-    int32_t sched = MRMF_SCHED_WINDOWS, bskip = 0, group = 0, blocks_per_cu = 0, variant = MRMF_VARIANT_MASKED;
+    int32_t sched = kSchedAuto, bskip = 0, group = 0, blocks_per_cu = 0, variant = kVariantAuto;
     int32_t wide = 0;  // 1 = 64-bit addresses even when 32-bit buffer offsets would do
     int32_t cheb_fused = 1;  // time propagation: fused Chebyshev-step kernel (c128 configuration only)
     int32_t cheb_merge = 1;  // time propagation: steps of a fixed H taken as one series (c128 configuration)
@@ -112,10 +114,14 @@ struct KernelCfg {
     int32_t grad_blocks_per_cu = 0;  // blocks per CU of the generated gradient kernel (0: the default, 2)
     int32_t outer_first = 0;  // the k most significant sites vary fastest in the super-tile sweep
     int32_t unroll_top = 0;   // k: sites 0..k-1 join the unrolled copies of every super-tile
+    int32_t far_pass = 0;     // window form: second pass for far channels (0: by rule, 1: never, k: reach 2^k bytes)
 };
 
 // Slot of the c128 kernel with the Chebyshev-step epilogue in mrmf_plan_t::spec (after the dtypes).
 constexpr int kSlotCheb = 2;
+// Slots of Lanczos' own kernels (c128, then c64): the masked form where the plan's kernel has the window form by rule,
+// so that the recurrence keeps the rounding it always had (lanczos.hip).
+constexpr int kSlotLanczos = 3;
 
 // Largest parameter count the generated coupling-gradient kernel keeps in registers (one accumulator each).
 constexpr int kGradMaxParams = 48;
@@ -127,7 +133,8 @@ struct SpecKernel {
     int device = -1;
     hipModule_t mod = nullptr;
     hipFunction_t fn = nullptr;
-    int32_t k_in = 0, k_u = 0, T_in = 0, P_U = 1, block = 0, grid = 0;
+    hipFunction_t fn2 = nullptr;  // second pass (window form), launched after fn with the same arguments
+    int32_t k_in = 0, k_u = 0, T_in = 0, P_U = 1, block = 0, grid = 0, block2 = 0, grid2 = 0;
     int64_t n_tiles = 0;
     std::string log;
 };
@@ -161,7 +168,7 @@ struct mrmf_plan_t {
     // kernel selection and shape, per element type (MRMF_DTYPE_Z, MRMF_DTYPE_C)
     mrmf::KernelCfg cfg[3];       // [kSlotCheb]: shape of the Chebyshev-step kernel once set explicitly
     bool cheb_shape_set = false;  // else that kernel takes the c128 configuration
-    mrmf::SpecKernel spec[3];  // c128, c64, c128 with the Chebyshev-step epilogue
+    mrmf::SpecKernel spec[5];  // c128, c64, c128 with the Chebyshev-step epilogue, Lanczos' c128 and c64
     mrmf::SpecKernel grad;     // coupling-gradient kernel of the adjoint (c128)
     std::mutex mtx;
     ~mrmf_plan_t();
@@ -250,6 +257,11 @@ mrmf_status matvec_z_impl(mrmf_plan_t* p, const void* d_ws, const double* theta,
                           const void* x, void* y, hipStream_t s, const int32_t* d_skip);
 mrmf_status matvec_c_impl(mrmf_plan_t* p, const void* d_ws, const float* theta,
                           const void* x, void* y, hipStream_t s, const int32_t* d_skip);
+// the same maps for the Lanczos recurrence
+mrmf_status matvec_lanczos_z(mrmf_plan_t* p, const void* d_ws, const double* theta,
+                             const void* x, void* y, hipStream_t s, const int32_t* d_skip);
+mrmf_status matvec_lanczos_c(mrmf_plan_t* p, const void* d_ws, const float* theta,
+                             const void* x, void* y, hipStream_t s, const int32_t* d_skip);
 // A map x -> y enqueued on a stream (device pointers; `stopped` non-null: skip when the device flag is set).
 using MatvecOp = std::function<mrmf_status(const void* x, void* y, hipStream_t s, const int32_t* stopped)>;
 // Lanczos (the recurrence of mrmf_lanczos) for any map of dimension D; mv_c may be empty for MRMF_PREC_Z.
@@ -270,8 +282,16 @@ mrmf_status propagate_run(int64_t n, int32_t n_params, const ThetaMatvecOp& mv, 
                           int64_t theta_stride, double dt, int32_t n_steps, double e_min, double e_max, double tol,
                           const void* d_x0, void* d_x, void* d_scratch, size_t scratch_bytes, int32_t* h_n_terms,
                           hipStream_t s);
-// Generated source of the specialized kernel (no device needed); "" when the plan does not qualify.
-std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl, bool epi = false);
+// Generated source of the specialized kernel (no device needed) and its launches' block size and super-tiles;
+// "" when the plan does not qualify.
+struct SpecGeom {
+    int n = 1;
+    int block[2] = {0, 0};
+    int64_t tiles[2] = {0, 0};
+};
+std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl, SpecGeom* geo, bool epi = false, bool lanczos = false);
+// slot of the kernel that Lanczos launches for a dtype: its own (kSlotLanczos + dtype) or the plan's
+int lanczos_slot(const mrmf_plan_t* p, int dtype);
 // Fused Chebyshev step (time propagation) with the specialized c128 kernel:
 // p = ea (H x) + eb x + eg prev;  prev = p;  acc += (ecr + i eci) p.  MRMF_E_UNSUPPORTED when the plan
 // has no specialized kernel.

@@ -270,12 +270,12 @@ class Plan:
 
     TUNING = {"schedule": 0, "branch_skip": 1, "load_group": 2, "blocks_per_cu": 3, "variant": 4, "addressing": 5,
               "cheb_fused": 6, "waves_per_eu": 7, "far_loads": 8, "grad_blocks_per_cu": 9,
-              "outer_first": 10, "unroll_top": 11, "far_dir": 12, "cheb_merge": 13}
+              "outer_first": 10, "unroll_top": 11, "far_dir": 12, "cheb_merge": 13, "far_pass": 14}
 
     def set_tuning(self, **knobs):
         """Tuning knobs of the specialized kernel: schedule (0 windows, 1 per-XCD chunks, 2 block runs),
         branch_skip (0/1), load_group (channels issued ahead, 0 = default), blocks_per_cu (0 = as many as
-        fit), variant (0 masked, 1 list), addressing (0 = 64-bit only where 32-bit offsets cannot reach,
+        fit), variant (0 masked, 1 list, 2 window; until set, window for real weights), addressing (0 = 64-bit only where 32-bit offsets cannot reach,
         1 = always 64-bit), cheb_fused (1 = propagate with the fused Chebyshev-step kernel, 0 = matvec +
         update), waves_per_eu (0 = compiler's choice, else a minimum of resident waves per SIMD),
         far_loads (0 = default cache policy, k = gathers reaching 2^k bytes or more are non-temporal),
@@ -283,7 +283,8 @@ class Plan:
         kernel, 0 = default), outer_first (k = the k most significant sites vary fastest in the sweep
         over super-tiles, 0 = index order), unroll_top (k = sites 0..k-1 join the unrolled copies, so terms
         between them and the low sites read LDS; 0 = off), cheb_merge (1 = propagate takes consecutive
-        steps of a fixed H as one longer step, 0 = one Chebyshev series per step)."""
+        steps of a fixed H as one longer step, 0 = one Chebyshev series per step), far_pass (window form:
+        channels reaching 2^k bytes are applied by a second launch, 0 = by rule, 1 = never)."""
         for k, v in knobs.items():
             L.call("mrmf_plan_set_tuning", self._handle, self.TUNING[k], int(v))
 

@@ -64,6 +64,10 @@ extern "C" void mrmf_sector(const void* theta, const void* x, void* y, const int
     __attribute__((weak));
 extern "C" void mrmf_spec_cheb(const void* theta, const void* x, void* y, void* acc, double ea, double eb, double eg,
                                double ecr, double eci, const int* skip) __attribute__((weak));
+// second passes of the window form
+extern "C" void mrmf_spec_b(const void* theta, const void* x, void* y, const int* skip) __attribute__((weak));
+extern "C" void mrmf_spec_cheb_b(const void* theta, const void* x, void* y, void* acc, double ea, double eb, double eg,
+                                 double ecr, double eci, const int* skip) __attribute__((weak));
 extern "C" void mrmf_sector_cheb(const void* theta, const void* x, void* y, void* acc, double ea, double eb, double eg,
                                  double ecr, double eci, const int* skip, const void* lab) __attribute__((weak));
 
@@ -85,6 +89,7 @@ struct GradCall {
     const void* g = nullptr;
     double* partial = nullptr;
 } g_grad;
+bool g_second = false;        // the launch runs the second pass
 bool g_sector = false;        // the launch runs the generated sector kernel
 const void* g_lab = nullptr;  // its packed-digit table
 // One host thread per GPU thread of the block, kept for every block of the range; a block barrier
@@ -101,6 +106,11 @@ void* thread_main(void* a) {
             mrmf_sector(g->theta, g->x, g->y, nullptr, g_lab);
         else if (g_grad.on)
             mrmf_grad(static_cast<const double*>(g->theta), g->x, g_grad.g, g->y, g_grad.partial);
+        else if (g_cheb.cheb && g_second)
+            mrmf_spec_cheb_b(g->theta, g->x, g->y, g_cheb.acc, g_cheb.ea, g_cheb.eb, g_cheb.eg, g_cheb.ecr, g_cheb.eci,
+                             nullptr);
+        else if (g_second)
+            mrmf_spec_b(g->theta, g->x, g->y, nullptr);
         else if (g_cheb.cheb)
             mrmf_spec_cheb(g->theta, g->x, g->y, g_cheb.acc, g_cheb.ea, g_cheb.eb, g_cheb.eg, g_cheb.ecr, g_cheb.eci,
                            nullptr);
@@ -111,6 +121,13 @@ void* thread_main(void* a) {
     return nullptr;
 }
 }  // namespace
+
+// Selects the pass that the next launches run (0: the first, 1: the second); -1 when the source has no such kernel.
+extern "C" int emu_select_pass(int second) {
+    if (second && mrmf_spec_b == nullptr && mrmf_spec_cheb_b == nullptr) return -1;
+    g_second = second != 0;
+    return 0;
+}
 
 // Runs blocks [b0, b1) of a grid of `grid` blocks (b1 = 0: all of them).
 extern "C" int emu_run_range(unsigned grid, unsigned block, const void* theta, size_t theta_bytes, const void* x,

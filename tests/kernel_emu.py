@@ -29,7 +29,7 @@ TUNING = {"schedule": L.MRMF_TUNE_SCHEDULE, "branch_skip": L.MRMF_TUNE_BRANCH_SK
           "load_group": L.MRMF_TUNE_LOAD_GROUP, "blocks_per_cu": L.MRMF_TUNE_BLOCKS_PER_CU,
           "variant": L.MRMF_TUNE_VARIANT, "addressing": L.MRMF_TUNE_ADDRESSING,
           "far_loads": L.MRMF_TUNE_FAR_LOADS, "outer_first": L.MRMF_TUNE_OUTER_FIRST,
-          "unroll_top": L.MRMF_TUNE_UNROLL_TOP, "far_dir": L.MRMF_TUNE_FAR_DIR}
+          "unroll_top": L.MRMF_TUNE_UNROLL_TOP, "far_dir": L.MRMF_TUNE_FAR_DIR, "far_pass": L.MRMF_TUNE_FAR_PASS}
 
 
 def kernel_source(model, dtype: int, inner: int = 0, unrolled: int = -1, require_hermitian=True,
@@ -95,6 +95,42 @@ def launch_shape(src: str):
     block = int(re.search(r"__launch_bounds__\((\d+)\)", src).group(1))
     tiles = int(re.search(r"(\d+) super-tiles", src).group(1))
     return block, tiles
+
+
+def launch_shapes(src: str):
+    """(block, super-tiles) of every pass of the window form."""
+    return list(zip((int(b) for b in re.findall(r"__launch_bounds__\((\d+)\)", src)),
+                    (int(t) for t in re.findall(r"(\d+) super-tiles", src))))
+
+
+def run_passes(model, x: np.ndarray, inner: int = 0, unrolled: int = -1, grid: int = 8, tuning=None, cheb=None):
+    """Every pass of the window form in launch order: y = H x, or with cheb = (prev, acc, ea, eb, eg, c) the
+    Chebyshev step's (prev', acc').  Returns (passes, result)."""
+    f32 = x.dtype == np.complex64
+    dtype = L.MRMF_SOURCE_CHEB if cheb is not None else L.MRMF_DTYPE_C if f32 else L.MRMF_DTYPE_Z
+    src = kernel_source(model, dtype, inner, unrolled, tuning={"variant": L.MRMF_VARIANT_WINDOW, **(tuning or {})})
+    if src is None or "window form" not in src:
+        raise ValueError("the plan does not fit the window form")
+    shapes = launch_shapes(src)
+    lib = _compile(src)
+    th = np.ascontiguousarray(model.theta, dtype=np.float32 if f32 else np.float64)
+    xx = np.ascontiguousarray(x)
+    y = np.full_like(xx, np.nan) if cheb is None else np.array(cheb[0], dtype=np.complex128, copy=True)
+    acc = None if cheb is None else np.array(cheb[1], dtype=np.complex128, copy=True)
+    for i, (block, tiles) in enumerate(shapes):
+        assert lib.emu_select_pass(i) == 0
+        g = min(tiles, grid)
+        if cheb is None:
+            rc = lib.emu_run(g, block, th.ctypes.data, th.nbytes, xx.ctypes.data, xx.nbytes, y.ctypes.data, y.nbytes)
+        else:
+            ea, eb, eg, c = cheb[2:]
+            if i == 1:
+                eb, eg = 0.0, 1.0
+            rc = lib.emu_run_cheb(g, block, th.ctypes.data, th.nbytes, xx.ctypes.data, xx.nbytes, y.ctypes.data,
+                                  acc.ctypes.data, ea, eb, eg, c.real, c.imag, 0, 0)
+        assert rc == 0, rc
+    lib.emu_select_pass(0)
+    return len(shapes), (y if cheb is None else (y, acc))
 
 
 def run(model, x: np.ndarray, theta=None, inner: int = 0, unrolled: int = -1, grid: int | None = None,

@@ -1,0 +1,131 @@
+"""The window form of the generated matvec (csrc/window.cpp) where its code changes: merged and split channel pairs, tables
+of the uniform digits, site orders of the second pass, blocks with a ragged last wave, plans with one pass, two passes or
+no uniform site.  On the CPU through the emulator (every buffer access checked to lie inside its buffer), on the GPU
+through the library; c128 to 1e-12, c64 to 2e-5 of the oracle."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import mf
+from paper_2606_02169_amd import _lib as L
+from tests import kernel_emu as E
+from tests.helpers import rel_err
+
+TOL = {np.complex128: 1e-12, np.complex64: 2e-5}
+
+
+def real_random(seed, n_sites=5, max_dim=2000, **kw):
+    """Random mixed spin/boson lattice with real weights (the form's condition)."""
+    m = W.random_model(np.random.default_rng(seed), n_sites=n_sites, max_dim=max_dim, n_params=3, n_terms=14, **kw)
+    terms = [W.Term(t.site_a, t.op_a, t.site_b, t.op_b, t.param, complex(t.w).real) for t in m.terms]
+    return W.Model(m.sites, terms, m.theta, name=f"real_random_{seed}")
+
+
+def diagonal_only():
+    sites = [W.spin_site(1), W.spin_site(2), W.boson_site(4)]
+    return W.Model(sites, [W.Term(0, W.OP_Z, 2, W.OP_Z, 0, 0.7), W.Term(1, W.OP_Z2, -1, W.OP_Z, 1, -1.3)],
+                   np.array([0.9, 1.1]))
+
+
+MODELS = {
+    "spin half ring": lambda: W.configs.staggered_xxz_ring([1] * 8),
+    "spin 1 ring": lambda: W.configs.staggered_xxz_ring([2] * 6),          # both channels of a bond admitted at once
+    "spin 3/2 chain": lambda: W.configs.open_xxz_chain([3, 1, 3, 2, 3], np.ones(4), np.full(4, 0.7)),  # factor tables
+    "ferrimagnet": lambda: W.ferrimagnetic_ring(8),
+    "square": lambda: W.square_lattice_spin1(2, np.random.default_rng(3)),  # double bonds
+    "bosons": lambda: W.tavis_cummings(4, 12, rng=np.random.default_rng(4)),
+    "one site": lambda: W.zero_field_splitting(3, 0.8, 0.3),
+    "diagonal": diagonal_only,
+    "random 1": lambda: real_random(41),
+    "random 2": lambda: real_random(42),
+}
+SHAPES = [(0, -1, {}), (1, 0, {}), (2, 1, {"schedule": 1, "load_group": 2}), (1, 2, {"addressing": 1}),
+          (2, 0, {"far_pass": 10}), (1, 1, {"far_pass": 11, "addressing": 1}), (2, 0, {"unroll_top": 1, "schedule": 2})]
+
+
+def shapes(m):
+    return [s for s in SHAPES if s[0] + max(0, s[1]) + s[2].get("unroll_top", 0) <= len(m.sites)]
+
+
+def state(m, dtype=np.complex128):
+    return W.random_state(m.dim, np.random.default_rng(8)).astype(dtype)
+
+
+@pytest.mark.parametrize("name", list(MODELS))
+def test_emulated(name):
+    m = MODELS[name]()
+    ran = 0
+    for inner, unrolled, tuning in shapes(m):
+        for dtype in (np.complex128, np.complex64):
+            x = state(m, dtype)
+            try:
+                passes, y = E.run_passes(m, x, inner=inner, unrolled=unrolled, tuning=tuning)
+            except ValueError:  # the tile does not fit the plan
+                continue
+            ran += 1
+            assert rel_err(y, mf.matvec(m, x.astype(np.complex128))) <= TOL[dtype], (inner, unrolled, tuning, dtype)
+            assert np.all(np.isfinite(y))
+    assert ran
+
+
+@pytest.mark.parametrize("far", [1, 10, 11])
+def test_emulated_chebyshev_step(far):
+    """One pass, and the two halves of a step."""
+    m = W.ferrimagnetic_ring(8)
+    x, rng = state(m), np.random.default_rng(9)
+    prev, acc = W.random_state(m.dim, rng), W.random_state(m.dim, rng)
+    c = 0.4 - 0.2j
+    passes, (p, a) = E.run_passes(m, x, inner=3, unrolled=1, tuning={"far_pass": far}, cheb=(prev, acc, 0.7, -0.3, 0.9, c))
+    want = 0.7 * mf.matvec(m, x) - 0.3 * x + 0.9 * prev
+    assert passes == (1 if far == 1 else 2)
+    assert rel_err(p, want) <= 1e-12 and rel_err(a, acc + c * want) <= 1e-12
+
+
+def test_chosen_by_rule():
+    """Real weights take the window form unless another form or one of its knobs is asked for; complex ones never do."""
+    m = W.ferrimagnetic_ring(6)
+    assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z)
+    for knob in ({"variant": 0}, {"variant": 1}, {"far_loads": 12}, {"outer_first": 1}, {"branch_skip": 1}):
+        assert "window form" not in E.kernel_source(m, L.MRMF_DTYPE_Z, tuning=knob)
+    cplx = W.Model(m.sites, m.terms + [W.Term(0, W.OP_RAISE, -1, W.OP_Z, 0, 0.3j),
+                                       W.Term(0, W.OP_LOWER, -1, W.OP_Z, 0, -0.3j)], m.theta)
+    assert "window form" not in E.kernel_source(cplx, L.MRMF_DTYPE_Z, tuning={"variant": 2})
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(MODELS))
+def test_gpu(name):
+    import torch
+
+    from paper_2606_02169_amd.plan import Plan
+    m = MODELS[name]()
+    for inner, unrolled, tuning in shapes(m):
+        for dtype, tdt in ((np.complex128, torch.float64), (np.complex64, torch.float32)):
+            p = Plan.from_model(m)
+            p.set_kernel("auto", inner_sites=inner, unrolled_sites=unrolled)
+            p.set_tuning(variant=2, **tuning)
+            x = state(m, dtype)
+            th = torch.as_tensor(m.theta, dtype=tdt, device="cuda")
+            print(name, inner, unrolled, tuning, dtype.__name__, flush=True)
+            y = p.matvec(th, torch.from_numpy(x).cuda()).cpu().numpy()
+            assert rel_err(y, mf.matvec(m, x.astype(np.complex128))) <= TOL[dtype]
+
+
+@pytest.mark.gpu
+def test_gpu_two_passes_of_the_square_lattice():
+    """The 4 x 4 lattice (43 million rows), which takes a second pass by rule, and one pass forced: the same vector."""
+    import torch
+
+    from paper_2606_02169_amd.plan import Plan
+    m = W.square_lattice_spin1(4, np.random.default_rng(3))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.view_as_complex(torch.randn((m.dim, 2), dtype=torch.float64, device="cuda", generator=g))
+    th = torch.as_tensor(m.theta, dtype=torch.float64, device="cuda")
+    two, one = Plan.from_model(m), Plan.from_model(m)
+    one.set_tuning(far_pass=1)
+    y2, y1 = two.matvec(th, x), one.matvec(th, x)
+    assert "mrmf_spec_b" in two.kernel_source() and "mrmf_spec_b" not in one.kernel_source()
+    assert float((y2 - y1).abs().max()) <= 1e-13 * float(y1.abs().max())
+    rows = np.unique(np.random.default_rng(2).choice(m.dim, 2000, replace=False)).astype(np.int64)
+    ref = mf.matvec(m, x.cpu().numpy(), rows=rows)
+    assert rel_err(y2[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= 1e-12
