@@ -531,6 +531,9 @@ mrmf_status mrmf_sector_propagate_z(mrmf_sector sector, const void* d_ws, const 
  * couplings, with D_b * nvec < 2^30.
  * The batch copies what it needs from the plans at creation; the plans may be destroyed afterwards. */
 mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, mrmf_batch* out);
+/* A batch of n_params lattices of one plan with a shared input (mrmf_batch_share_input): lattice p holds the terms of
+ * coupling p alone, so that with unit coupling vectors block p is the group product h_p X of a sweep by linearity. */
+mrmf_status mrmf_batch_create_groups(mrmf_plan plan, int32_t nvec, mrmf_batch* out);
 void mrmf_batch_destroy(mrmf_batch batch);
 mrmf_status mrmf_batch_total_elems(mrmf_batch batch, int64_t* elems); /* sum over b of D_b * nvec, padded */
 mrmf_status mrmf_batch_offsets(mrmf_batch batch, int64_t* out);       /* host int64[n] */
@@ -562,7 +565,7 @@ mrmf_status mrmf_batch_set_shape(mrmf_batch batch, int32_t tile_rows_max, int32_
  * one XCD adjacent; MRMF_BATCH_SCHED_WINDOWS - the grid sweeps windows of consecutive items, each XCD
  * taking one eighth of every window, so that the items one XCD holds at a time are neighbours (their
  * cross-tile gathers meet in that XCD's L2); MRMF_BATCH_SCHED_XCD_CHUNK - each XCD sweeps its own
- * contiguous eighth of the items with its blocks side by side.  Results are identical. */
+ * contiguous eighth of every lattice's items with its blocks side by side.  Results are identical. */
 #define MRMF_BATCH_SCHED_RUNS 0
 #define MRMF_BATCH_SCHED_WINDOWS 1
 #define MRMF_BATCH_SCHED_XCD_CHUNK 2
@@ -581,7 +584,7 @@ mrmf_status mrmf_batch_share_input(mrmf_batch batch, int32_t on);
 /* Parameter sweep by linearity: H(theta) = sum_p theta_p h_p (each term carries one coupling, Sec. I), so
  * the products of one structure at K coupling vectors are Y_k = sum_p theta_kp G_p with G_p = h_p X.
  * Given the P group products G_p (c64, n entries each, G_p at d_G + p * g_stride elements; e.g. the output
- * of a batch of P copies of the plan with a shared input and unit coupling vectors), this writes
+ * of mrmf_batch_create_groups' batch at unit coupling vectors), this writes
  * Y_k[i] = sum_p d_theta[k * P + p] G_p[i] to d_Y + k * y_stride for k < K (c64; d_theta: float[K][P] on
  * the device).  One pass, bound by the writes of the K outputs; results equal the direct products up to
  * the order of the FP32 sums.  1 <= P <= 16, K >= 1, strides >= n; 8-byte aligned, G and Y not

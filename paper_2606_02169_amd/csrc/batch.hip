@@ -10,27 +10,39 @@
 // Shared input (parameter sweeps: the same vectors under many couplings): every lattice reads block 0 of X,
 // and the items are numbered tile by tile across the lattices instead of lattice by lattice.
 //
-// Work.  For a launch shape (R_max, block B), lattice b's rows are cut into tiles spanned by its low
-// sites (T_b = prod of the low d_i, the largest such product <= R_max), and an item is the P = max(1,
-// B / T_b) consecutive tiles that one block holds in LDS at a time (rows stored vector-major, so that
-// consecutive threads read consecutive 8-byte words).  Items are numbered lattice by lattice.  Three
-// schedules: runs - block v of the grid takes the contiguous item range [v I / G, (v+1) I / G), v chosen
-// so that the blocks of one XCD (block b runs on XCD b mod 8) hold neighbouring ranges; windows - the
-// grid sweeps windows of G consecutive items, the blocks of one XCD taking one eighth of each window side
-// by side, so that the items an XCD works on at one time are neighbours and the gathers of one item find
-// the rows its neighbours have just read in the XCD's L2 (at the price of reloading a lattice's
-// descriptors whenever a block moves to another lattice); XCD chunks - XCD x sweeps the x-th eighth of
-// the items with its blocks side by side, so that its L2 also holds the rows it read further back.  Every thread owns rows of the item; for each
-// row it decodes the digits once into LDS, then for every channel forms the coefficient from the
-// per-site factor tables (zero where a source digit is inadmissible, App. A) and, where it is nonzero,
-// reads the nvec source amplitudes of row F - Delta: from LDS when both sites of the channel lie in the
-// tile (the source is then in the same tile), else from global memory.  A nonzero factor means both
-// source digits are in range, so no read leaves the lattice.
+// Work.  For a launch shape (R_max, block B), lattice b's rows are cut into tiles of T c rows: all states of its low
+// sites (T = prod of the low d_i, the largest such product <= R_max) for c neighbouring digits of the next site (c = 1
+// unless T <= R_max / 2, so that a tile is more than half full however large one site is).  An item is a tile; a block
+// holds it in LDS (rows stored vector-major, so that consecutive threads read consecutive 8-byte words).  Items are
+// numbered lattice by lattice.  Three schedules: runs - block v of the grid takes the contiguous item range
+// [v I / G, (v+1) I / G), v chosen so that the blocks of one XCD (block b runs on XCD b mod 8) hold neighbouring ranges;
+// windows - the grid sweeps windows of G consecutive items, the blocks of one XCD taking one eighth of each window side
+// by side, so that the items an XCD works on at one time are neighbours and the gathers of one item find the rows its
+// neighbours have just read in the XCD's L2 (at the price of reloading a lattice's descriptors whenever a block moves to
+// another lattice); XCD chunks - XCD x sweeps the x-th eighth of every lattice's items with its blocks side by side, so
+// that its L2 also holds the rows it read further back, while all XCDs work on one lattice, whose vectors the memory-side
+// cache then holds (eighths of the whole list, each XCD in another lattice: 2.73 ms against 2.33 for windows in the case
+// below, now 1.92 against 1.93).  With a shared input the strides are multiples of the lattice count, so that a block
+// stays with one lattice.
+//
+// What a row costs.  The digits above the tile are the same for all its rows, so a wave works them out once per tile,
+// one lane per site and then one lane per term: a channel whose sites lie above the tile is then either left out for the
+// whole tile or a plain contiguous load with one coefficient, without work per row.  Digits inside the tile and the sums
+// of its diagonal terms depend on the row of the tile alone and are laid out once per lattice.  Only the other terms
+// (both sites in the tile: source in LDS; one inside, one above: gather) look their factors up per row.  The sums run in
+// one order of the terms, whatever the tile, so every launch shape gives the same bits.
+//
+// Bound.  64 open chains of 8 to 16 sites (29.3 M rows, eight vectors; 10.5 GB fetched and 1.9 written, against 3.8 that
+// every vector costs once): 2.39 ms with digits, factors and skips per row (2045 vector instructions per 64 rows, two
+// waves per SIMD), 1.92 ms now, limited by the serial chain of a wave's item and by the gathers that miss the L2
+// (6.4 TB/s).  What counts is waves: at 16 per CU (128 registers; two gathers at a time, as three or four spill: 2.25 and
+// 3.4 ms) against 12, 1.92 and 2.12 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "mrmf_internal.h"
@@ -46,25 +58,34 @@ constexpr int kBatchTileWords = 4096;  // 8-byte words of the LDS tile (32 KB): 
 constexpr int kBatchRmaxCands = 4;     // tile-row limits R_max = (64, 128, 256, 512) * 8 / nvec
 constexpr int kBatchMaxTerms = 128;    // terms (channels + diagonal) of one lattice, held in LDS
 constexpr int kBatchMaxParams = 128;   // couplings of one lattice, held in LDS
-constexpr int kBatchGather = 5;        // global-memory channels whose gathers are issued together (124 VGPRs:
-                                       // still 4 waves per SIMD; 6 or 8 fall to 3 or 2 and run slower)
+constexpr int kBatchGather = 2;        // gathers issued together
 
 struct alignas(16) BLat {
     int32_t N, n_chan, n_diag, theta_off;
-    int32_t D, chan_off, diag_off, site_off;
-    int32_t pool_off, pool_n, n_params, pad1;
+    int32_t D, term_off, site_off, n_params;
+    int32_t pool_off, pool_n, pad0, pad1;
     int64_t x_off, pad2;
-    int32_t tile_rows[kBatchRmaxCands];   // T_b for each R_max candidate
-    int32_t tile_sites[kBatchRmaxCands];  // number of low sites spanning T_b
+    int32_t item_beg[kBatchRmaxCands];    // per R_max candidate: first item of the lattice
+    int32_t part_beg[kBatchRmaxCands];    // the same count of items per eighth of a lattice (rounded up)
+    int32_t low_rows[kBatchRmaxCands];    // T
+    int32_t low_sites[kBatchRmaxCands];   // number of low sites that T spans
+    int32_t chunk[kBatchRmaxCands];       // c
+    int32_t n_chunks[kBatchRmaxCands];    // ceil(d / c) of the next site d, 1 when c = 1
     int32_t n_local[kBatchRmaxCands];     // channels whose source lies in the tile (a prefix of the list)
+    int32_t n_ldiag[kBatchRmaxCands];     // diagonal terms of the T rows' digits alone (a prefix of the list)
 };
-static_assert(sizeof(BLat) == 112, "BLat layout");
+static_assert(sizeof(BLat) == 192, "BLat layout");
+
+// n / m for n < 2^31 is umulhi(2 n, mul) >> shift (mul = ceil(2^(31 + shift) / m), shift = ceil(log2 m))
+struct BDiv {
+    uint32_t mul, shift;
+};
 
 struct alignas(16) BSite {
     int32_t d, pad;
-    uint64_t magic;  // ceil(2^64 / d)
+    BDiv by_d, by_m, by_md;  // division by d, by the site's stride, by d times the stride
 };
-static_assert(sizeof(BSite) == 16, "BSite layout");
+static_assert(sizeof(BSite) == 32, "BSite layout");
 
 // One term: coefficient theta[param] * (wr + i wi) * pool[ta + n_a] * pool[tb + n_b]; source F - delta.
 // A one-site term has b = -1 (its second factor is the pool's 1.0 entry at tb, digit 0).  low = number of
@@ -77,7 +98,7 @@ struct alignas(16) BTerm {
 static_assert(sizeof(BTerm) == 48, "BTerm layout");
 
 struct BatchArgs {
-    const BLat* lat;
+    const BLat* lat;     // n_lat entries and one that holds the item counts
     const BSite* site;
     const BTerm* term;   // channels and diagonal terms of every lattice
     const float* pool;   // factor tables of every lattice
@@ -86,112 +107,203 @@ struct BatchArgs {
     int32_t shared;  // every lattice reads its input rows from the one block at the start of X; items tile-major
 };
 
-__device__ __forceinline__ uint32_t umulhi_div(uint32_t n, uint64_t magic) {
-    return static_cast<uint32_t>(__umul64hi(magic, static_cast<uint64_t>(n)));
+__device__ __forceinline__ uint32_t div_by(uint32_t n, BDiv m) { return __umulhi(n << 1, m.mul) >> m.shift; }
+
+__device__ __forceinline__ int lane_of(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ float lane_of(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// The NV amplitudes of one row (NV * 8 contiguous bytes; 16-byte aligned when NV >= 2) in 16-byte loads
-// and stores where the row allows it.
+// a product and a sum that are rounded each, never contracted, so that a term has one value wherever it is formed
+__device__ __forceinline__ float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+__device__ __forceinline__ float add_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
+// digit of a field (shift | width << 5) of a row word; 0 for an empty field
+__device__ __forceinline__ uint32_t digit_of(uint32_t word, int f) {
+    return __builtin_amdgcn_ubfe(word, f & 31, f >> 5);
+}
+
+// Terms of the current lattice, lane k holding term k (a second set holds terms 64 and up).
+struct LaneTerms {
+    int tab;         // factor-table entries of the two sites at digit 0: a | b << 16
+    int sites;       // a | b << 8 (b = a for a one-site term)
+    int field;       // field of each site in the row word (shift | width << 5; width 0: the site is above the tile),
+                     // a | b << 16; bit 31: one-site term
+    int delta;
+    float wr, wi;    // theta wr, theta wi
+    // of the current tile
+    int at;          // table entries at the digits of the tile's first row, a | b << 16
+    float vr, vi;    // coefficient when both sites are above the tile
+};
+
+// f at the constants 0 .. N - 1
+template <int N, typename F>
+__device__ __forceinline__ void each(F&& f) {
+    f(std::integral_constant<int, 0>{});
+    if constexpr (N > 1) f(std::integral_constant<int, 1>{});
+    if constexpr (N > 2) {
+        f(std::integral_constant<int, 2>{});
+        f(std::integral_constant<int, 3>{});
+    }
+}
+
+// Two layouts of a wave's 64 rows.  By rows: lane l holds the NV amplitudes of one row (factors and LDS reads are per
+// row).  By pieces: a row is NP pieces of two amplitudes (16 bytes; one of 8 bytes when NV = 1), NP neighbouring lanes
+// hold a row and every lane NP rows, so that one load or store of the wave moves 64 consecutive pieces.  Loads by rows
+// touch every line NP times, far enough apart in time that the L1 has lost it.  The lane groups of a row hold the same
+// NP rows in both layouts, so that a transposition inside them leads from one to the other.
 template <int NV>
-__device__ __forceinline__ void load_row(const float2* __restrict__ src, float2 (&v)[NV]) {
-    if constexpr (NV == 1) {
-        v[0] = src[0];
-    } else {
-        const float4* s4 = reinterpret_cast<const float4*>(src);
+struct Wave {
+    static constexpr int NP = NV < 2 ? 1 : NV / 2;
+    static constexpr int PW = NV < 2 ? 2 : 4;  // floats of a piece
+    // padding of a vector's rows in LDS: the pieces of NP lanes then fall into different banks
+    static constexpr int kPad = NV == 8 ? 4 : NV == 4 ? 8 : 0;
+    // row i of lane group a; the rows of half a wave are distinct modulo 32 (no bank conflicts by rows)
+    static __device__ __forceinline__ int row(int a, int i) { return (64 / NP) * i + (2 * i >= NP && NP > 1 ? a ^ (32 / NP) : a); }
+    // what lane i of the lane group holds
+    template <int I>
+    static __device__ __forceinline__ int from(int v) {
+        if constexpr (NP == 1) return v;
+        constexpr int ctrl = NP == 4 ? I * 0x55 : I == 0 ? 0xA0 : 0xF5;  // quad_perm
+        return __builtin_amdgcn_mov_dpp(v, ctrl, 0xf, 0xf, true);
+    }
+    // e[p] of lane j becomes e[j] of lane p
+    static __device__ __forceinline__ void transpose(float (&e)[NP][PW], int lane) {
+        if constexpr (NP >= 2) step<1, 0xB1>(e, lane);
+        if constexpr (NP >= 4) step<2, 0x4E>(e, lane);
+    }
+    template <int S, int CTRL>
+    static __device__ __forceinline__ void step(float (&e)[NP][PW], int lane) {
+        const bool up = (lane & S) != 0;
 #pragma unroll
-        for (int q = 0; q < NV / 2; ++q) {
-            const float4 w = s4[q];
-            v[2 * q] = make_float2(w.x, w.y);
-            v[2 * q + 1] = make_float2(w.z, w.w);
+        for (int p = 0; p < NP; ++p)
+            if ((p & S) == 0) {
+#pragma unroll
+                for (int w = 0; w < PW; ++w) {
+                    const float send = up ? e[p][w] : e[p + S][w];
+                    const float got = __int_as_float(
+                        __builtin_amdgcn_mov_dpp(__float_as_int(send), CTRL, 0xf, 0xf, true));
+                    e[p][w] = up ? got : e[p][w];
+                    e[p + S][w] = up ? e[p + S][w] : got;
+                }
+            }
+    }
+    static __device__ __forceinline__ void load(const float2* __restrict__ src, float (&v)[PW]) {
+        if constexpr (PW == 2) {
+            const float2 w = *src;
+            v[0] = w.x;
+            v[1] = w.y;
+        } else {
+            const float4 w = *reinterpret_cast<const float4*>(src);
+            v[0] = w.x;
+            v[1] = w.y;
+            v[2] = w.z;
+            v[3] = w.w;
         }
     }
-}
-
-template <int NV>
-__device__ __forceinline__ void store_row(float2* __restrict__ dst, const float (&re)[NV], const float (&im)[NV]) {
-    if constexpr (NV == 1) {
-        dst[0] = make_float2(re[0], im[0]);
-    } else {
-        float4* d4 = reinterpret_cast<float4*>(dst);
+    static __device__ __forceinline__ void store(float2* __restrict__ dst, const float (&v)[PW], bool stream) {
+        using Vec = __attribute__((__vector_size__(PW * sizeof(float)))) float;
+        Vec w;
 #pragma unroll
-        for (int q = 0; q < NV / 2; ++q) d4[q] = make_float4(re[2 * q], im[2 * q], re[2 * q + 1], im[2 * q + 1]);
+        for (int e = 0; e < PW; ++e) w[e] = v[e];
+        if (stream) __builtin_nontemporal_store(w, reinterpret_cast<Vec*>(dst));
+        else *reinterpret_cast<Vec*>(dst) = w;
     }
-}
+};
 
-template <int NV, bool CPLX>
-__global__ __launch_bounds__(kBatchMaxBlock) void k_batch(BatchArgs A, const float* __restrict__ theta_all,
+template <int NV, bool CPLX, int kSets>
+__global__ __launch_bounds__(kBatchMaxBlock, 4) void k_batch(BatchArgs A, const float* __restrict__ theta_all,
                                                         const float2* __restrict__ X, float2* __restrict__ Y,
                                                         int32_t rc, int32_t sched) {
     constexpr int kRows = kBatchTileWords / NV;
-    __shared__ int32_t ibeg[kBatchMaxLattices + 1];
-    __shared__ float pool[kBatchPoolMax];
-    __shared__ uint8_t dig[kBatchMaxSites][kBatchMaxBlock];
-    __shared__ float2 xt[NV][kRows];
-    __shared__ BTerm tl[kBatchMaxTerms];  // the current lattice's diagonal terms, then its channels
-    __shared__ BSite sl[kBatchMaxSites];
-    __shared__ float thl[kBatchMaxParams];
-    const int tid = threadIdx.x, B = blockDim.x;
-    // items: ibeg[b] = sum over b' < b of ceil(D_b' / (P_b' T_b')); counts in parallel, then a serial scan
-    // over LDS by thread 0 (n <= 2048)
-    for (int b = tid; b < A.n_lat; b += B) {
-        const int32_t T = A.lat[b].tile_rows[rc];
-        const int32_t rows = T >= B ? T : (B / T) * T;
-        ibeg[b + 1] = (A.lat[b].D + rows - 1) / rows;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int32_t s = 0;
-        ibeg[0] = 0;
-        for (int b = 1; b <= A.n_lat; ++b) {
-            s += ibeg[b];
-            ibeg[b] = s;
-        }
-    }
-    __syncthreads();
-    const int64_t I = ibeg[A.n_lat];
-    const unsigned G = gridDim.x, bid = blockIdx.x;
-    const unsigned v = (G % 8u == 0u) ? (bid % 8u) * (G / 8u) + bid / 8u : bid;
+    using W = Wave<NV>;
+    constexpr int NP = W::NP, PW = W::PW;
+    extern __shared__ float pool[];              // factor tables of the current lattice
+    __shared__ float2 xt[NV][kRows + W::kPad];
+    __shared__ uint32_t rw[kRows];              // digits inside the tile, one field per site
+    __shared__ float rd[CPLX ? 2 : 1][kRows];   // diagonal terms of the low digits
+    __shared__ int32_t field[kBatchMaxSites];   // field of each site in the row word
+    const int tid = threadIdx.x, B = blockDim.x, lane = tid & 63;
+    const int la = lane / NP, lp = lane % NP;     // lane group, piece
+    const int lrow = W::row(la, lp);              // by rows: row of the lane
+    const int G = gridDim.x, bid = blockIdx.x, nl = A.n_lat;
+    const bool shared = A.shared != 0;
+    const int v = (G % 8 == 0) ? (bid % 8) * (G / 8) + bid / 8 : bid;
+    // parts: XCD x sweeps the x-th eighth of every lattice
+    const bool parts = sched == 2 && !shared && G % 8 == 0;
+    const int32_t I = parts ? A.lat[nl].part_beg[rc] : A.lat[nl].item_beg[rc];
     int32_t i0, i1, step;
-    if (sched == 1) {  // windows
-        i0 = static_cast<int32_t>(v);
-        i1 = static_cast<int32_t>(I);
-        step = static_cast<int32_t>(G);
-    } else if (sched == 2) {  // XCD x sweeps the x-th eighth of the items with its blocks side by side
-        const unsigned nx = (G % 8u == 0u) ? 8u : 1u, xcd = bid % nx;
-        const int64_t C = (I + nx - 1) / nx;
-        i0 = static_cast<int32_t>(xcd * C + bid / nx);
+    // blocks side by side: with a shared input a stride that is a multiple of the lattice count keeps a block with one
+    // lattice (the few blocks beyond it have no work), where the lattices are few enough for that
+    const auto stride = [&](int n) { return shared && nl * 4 <= n ? n / nl * nl : n; };
+    if (parts) {
+        step = G / 8;
+        i0 = bid / 8;
+        i1 = I;
+    } else if (sched == 2 && G % 8 == 0) {  // shared input: an eighth of the tiles, every lattice
+        const int xcd = bid % 8;
+        const int64_t C = (I / nl + 7) / 8 * nl;
+        step = stride(G / 8);
         i1 = static_cast<int32_t>((xcd + 1) * C < I ? (xcd + 1) * C : I);
-        step = static_cast<int32_t>(G / nx);
+        i0 = bid / 8 < step ? static_cast<int32_t>(xcd * C < I ? xcd * C + bid / 8 : I) : I;
+    } else if (sched != 0) {  // windows
+        step = stride(G);
+        i0 = v < step ? v : I;
+        i1 = I;
     } else {  // runs
         i0 = static_cast<int32_t>(int64_t(v) * I / G);
         i1 = static_cast<int32_t>(int64_t(v + 1) * I / G);
         step = 1;
     }
-    // the current lattice's descriptor, kept in scalar registers (every field is block-uniform)
+    const auto first_item = [&](int l) { return parts ? A.lat[l].part_beg[rc] : A.lat[l].item_beg[rc]; };
     int lb = -1;
-    int32_t N = 0, n_chan = 0, n_diag = 0, D = 0, rows = 1, ks = 0, n_loc = 0;
+    // the current lattice's descriptor, kept in scalar registers (every field is block-uniform)
+    int32_t N = 0, n_chan = 0, n_diag = 0, D = 0, T = 1, ks = 0, n_loc = 0, n_ld = 0, chunk = 1, nch = 1, dp = 1;
     const float2* xb = X;
     float2* yb = Y;
+    BSite site{};  // lane i: site i
+    LaneTerms lt[kSets];
     int b = 0;
-    const bool shared = A.shared != 0;
+    int32_t beg = 0, end = 0, count = 0;  // items of lattice b (of an eighth of it), tiles of lattice b
+    const auto tiles = [&](int l) {
+        return __builtin_amdgcn_readfirstlane(A.lat[l + 1].item_beg[rc] - A.lat[l].item_beg[rc]);
+    };
     if (!shared) {
-        int lo = 0, hi = A.n_lat - 1;  // last lattice with ibeg[b] <= i0
+        int lo = 0, hi = nl - 1;  // last lattice with its first item <= i0
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (ibeg[mid] <= i0) lo = mid; else hi = mid - 1;
+            if (first_item(mid) <= i0) lo = mid; else hi = mid - 1;
         }
         b = lo;
+        beg = __builtin_amdgcn_readfirstlane(first_item(b));
+        end = __builtin_amdgcn_readfirstlane(first_item(b + 1));
+        count = tiles(b);
     }
     for (int32_t it = i0; it < i1; it += step) {
         // shared input: every lattice has the same tiles; item it is tile it / n of lattice it mod n, so the
         // items worked on together read the same input rows
         int32_t li;
         if (shared) {
-            b = it % A.n_lat;
-            li = it / A.n_lat;
+            b = it % nl;
+            li = it / nl;
         } else {
-            while (it >= ibeg[b + 1]) ++b;
-            li = it - ibeg[b];
+            while (it >= end) {
+                ++b;
+                beg = end;
+                end = __builtin_amdgcn_readfirstlane(first_item(b + 1));
+                count = tiles(b);
+            }
+            li = it - beg;
+            if (parts) {
+                li += bid % 8 * (end - beg);
+                if (li >= count) continue;  // the last part is shorter
+            }
         }
         b = __builtin_amdgcn_readfirstlane(b);
         li = __builtin_amdgcn_readfirstlane(li);
@@ -202,120 +314,258 @@ __global__ __launch_bounds__(kBatchMaxBlock) void k_batch(BatchArgs A, const flo
             n_chan = __builtin_amdgcn_readfirstlane(L->n_chan);
             n_diag = __builtin_amdgcn_readfirstlane(L->n_diag);
             D = __builtin_amdgcn_readfirstlane(L->D);
-            const int32_t T = __builtin_amdgcn_readfirstlane(L->tile_rows[rc]);
-            ks = __builtin_amdgcn_readfirstlane(L->tile_sites[rc]);
+            T = __builtin_amdgcn_readfirstlane(L->low_rows[rc]);
+            ks = __builtin_amdgcn_readfirstlane(L->low_sites[rc]);
+            chunk = __builtin_amdgcn_readfirstlane(L->chunk[rc]);
+            nch = __builtin_amdgcn_readfirstlane(L->n_chunks[rc]);
             n_loc = __builtin_amdgcn_readfirstlane(L->n_local[rc]);
-            rows = T >= B ? T : (B / T) * T;
+            n_ld = __builtin_amdgcn_readfirstlane(L->n_ldiag[rc]);
             const int64_t xo = L->x_off;
             xb = shared ? X : X + xo;
             yb = Y + xo;
-            const int32_t po = __builtin_amdgcn_readfirstlane(L->pool_off), pn = __builtin_amdgcn_readfirstlane(L->pool_n);
+            const int32_t po = L->pool_off, pn = L->pool_n, s0 = L->site_off, t0 = L->term_off, th0 = L->theta_off;
             for (int k = tid; k < pn; k += B) pool[k] = A.pool[po + k];
-            // descriptors into LDS: diagonal terms then channels (stored contiguously), sites, couplings
-            const int32_t t0 = L->diag_off, nt = n_diag + n_chan, s0 = L->site_off, th0 = L->theta_off;
-            for (int k = tid; k < nt; k += B) tl[k] = A.term[t0 + k];
-            for (int k = tid; k < N; k += B) sl[k] = A.site[s0 + k];
-            for (int k = tid; k < A.lat[b].n_params; k += B) thl[k] = theta_all[th0 + k];
-            lb = b;
+            site = A.site[s0 + (lane < N ? lane : 0)];
+            const int inner = ks + (chunk > 1 ? 1 : 0);  // sites whose digit differs between the tile's rows
+            dp = chunk > 1 ? lane_of(site.d, N - 1 - ks) : 1;
+            if (tid < N) {
+                int sh = 0, w = 0;
+                for (int i = N - 1; i >= tid && i >= N - inner; --i) {
+                    const int top = i == N - 1 - ks ? chunk : A.site[s0 + i].d;  // digits of the field: below top
+                    sh += w;
+                    w = 32 - __clz(top - 1);
+                }
+                field[tid] = tid >= N - inner ? sh | w << 5 : 0;
+            }
             __syncthreads();
-        }
-        const int32_t r0 = li * rows;
-        const int32_t nr = r0 + rows < D ? rows : D - r0;
-        for (int32_t r = tid; r < nr; r += B) {
-            float2 v[NV];
-            load_row<NV>(xb + int64_t(r0 + r) * NV, v);
+            for (int r = tid; r < T * chunk; r += B) {
+                uint32_t f = r, word = 0;
+                for (int i = N - 1; i >= N - ks; --i) {
+                    const BSite s = A.site[s0 + i];
+                    const uint32_t q = div_by(f, s.by_d);
+                    word |= (f - q * static_cast<uint32_t>(s.d)) << (field[i] & 31);
+                    f = q;
+                }
+                if (chunk > 1) word |= f << (field[N - 1 - ks] & 31);
+                rw[r] = word;
+                float dr = 0.f, di = 0.f;
+                for (int k = 0; k < n_ld; ++k) {
+                    const BTerm t = A.term[t0 + k];
+                    const int fa = field[t.a], fb = t.b >= 0 ? field[t.b] : 0;
+                    const float f2 = mul_rn(pool[t.ta + digit_of(word, fa)], pool[t.tb + digit_of(word, fb)]);
+                    const float th = theta_all[th0 + t.param];
+                    dr = add_rn(dr, mul_rn(mul_rn(th, t.wr), f2));
+                    if (CPLX) di = add_rn(di, mul_rn(mul_rn(th, t.wi), f2));
+                }
+                rd[0][r] = dr;
+                if constexpr (CPLX) rd[1][r] = di;
+            }
 #pragma unroll
-            for (int q = 0; q < NV; ++q) xt[q][r] = v[q];
+            for (int q = 0; q < kSets; ++q) {
+                const int k = q * 64 + lane;
+                LaneTerms t{};
+                t.field = 1 << 21 | 1 << 5;  // a lane without a term reads no factor
+                if (k < n_diag + n_chan) {
+                    const BTerm g = A.term[t0 + k];
+                    t.tab = g.ta | g.tb << 16;
+                    t.sites = g.a | (g.b >= 0 ? g.b : g.a) << 8;
+                    t.field = field[g.a] | (g.b >= 0 ? field[g.b] << 16 : int(0x80000000u));
+                    t.delta = g.delta;
+                    t.wr = mul_rn(theta_all[th0 + g.param], g.wr);
+                    if (CPLX) t.wi = mul_rn(theta_all[th0 + g.param], g.wi);
+                }
+                lt[q] = t;
+            }
+            lb = b;
+        }
+        const int32_t h = nch > 1 ? li / nch : li, g0 = (li - h * nch) * chunk;
+        const int32_t r0 = (chunk > 1 ? h * dp + g0 : h) * T;
+        const int32_t nr = (chunk > 1 && dp - g0 < chunk ? dp - g0 : chunk) * T;
+        const float2* xr = xb + int64_t(r0) * NV;
+        const auto fetch = [&](int32_t rb, float (&w)[NP][PW]) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int32_t r = rb + W::row(la, i) < nr ? rb + W::row(la, i) : nr - 1;
+                W::load(xr + uint32_t(r * NV + 2 * lp), w[i]);
+            }
+        };
+        const auto put = [&](int32_t rb, const float (&w)[NP][PW]) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {  // rows beyond the last one repeat it
+                const int32_t r = rb + W::row(la, i) < nr ? rb + W::row(la, i) : nr - 1;
+#pragma unroll
+                for (int e = 0; e < PW / 2; ++e) xt[2 * lp + e][r] = make_float2(w[i][2 * e], w[i][2 * e + 1]);
+            }
+        };
+        const int32_t wave0 = __builtin_amdgcn_readfirstlane(tid - lane);
+        float w0[NP][PW];
+        if (wave0 < nr) fetch(wave0, w0);
+        // the tile's first row: lane i its digit at site i, then every lane its terms
+        const uint32_t qm = div_by(r0, site.by_m), qd = div_by(r0, site.by_md);
+        const int dig = static_cast<int>(qm - qd * static_cast<uint32_t>(site.d));
+        uint64_t todo[kSets], dtodo[kSets], uni[kSets];  // gathers, diagonal terms, terms without a digit in the tile
+#pragma unroll
+        for (int q = 0; q < kSets; ++q) {
+            todo[q] = dtodo[q] = uni[q] = 0;
+            if (q * 64 >= n_diag + n_chan) continue;
+            LaneTerms& t = lt[q];
+            const int k = q * 64 + lane;
+            const int da = __shfl(dig, t.sites & 255, 64), db = __shfl(dig, t.sites >> 8, 64);
+            t.at = t.tab + (t.field < 0 ? da : da | db << 16);
+            const int wa = t.field >> 5 & 15, wb = t.field >> 21 & 15;
+            const float f1 = wa ? 1.f : pool[t.at & 0xffff], f2 = wb ? 1.f : pool[t.at >> 16];
+            const float f = mul_rn(f1, f2);
+            t.vr = mul_rn(t.wr, f);
+            if (CPLX) t.vi = mul_rn(t.wi, f);
+            const bool on = f != 0.f;  // else a source digit above the tile is out of range (App. A)
+            uni[q] = __ballot(!(wa | wb));
+            dtodo[q] = __ballot(k >= n_ld && k < n_diag);
+            todo[q] = __ballot(on && k >= n_diag + n_loc && k < n_diag + n_chan);
+        }
+        if (wave0 < nr) put(wave0, w0);
+        for (int32_t rb = wave0 + B; rb < nr; rb += B) {
+            fetch(rb, w0);
+            put(rb, w0);
         }
         __syncthreads();
-        for (int32_t r = tid; r < nr; r += B) {
-            const int32_t F = r0 + r;
-            // digits, least significant site first (Eq. decode)
-            uint32_t f = static_cast<uint32_t>(F);
-            for (int i = N - 1; i >= 0; --i) {
-                const BSite s = sl[i];
-                const uint32_t q = umulhi_div(f, s.magic);
-                dig[i][tid] = static_cast<uint8_t>(f - q * static_cast<uint32_t>(s.d));
-                f = q;
-            }
-            float ar[NV], ai[NV];
-            float dr = 0.f, di = 0.f;
-            for (int k = 0; k < n_diag; ++k) {
-                const BTerm t = tl[k];
-                const float fa = pool[t.ta + dig[t.a][tid]] * (t.b >= 0 ? pool[t.tb + dig[t.b][tid]] : 1.f);
-                const float c = thl[t.param] * fa;
-                dr += c * t.wr;
-                if (CPLX) di += c * t.wi;
-            }
+        // whole waves (terms are read across lanes); lanes beyond the last row repeat it
+        for (int32_t rb = wave0; rb < nr; rb += B) {
+            const int32_t r = rb + lrow < nr ? rb + lrow : nr - 1;
+            int32_t pr[NP];  // by pieces: rows of the lane
 #pragma unroll
-            for (int q = 0; q < NV; ++q) {
-                const float2 s = xt[q][r];
-                ar[q] = dr * s.x;
-                ai[q] = dr * s.y;
-                if (CPLX) {
-                    ar[q] -= di * s.y;
-                    ai[q] += di * s.x;
-                }
-            }
-            // channels whose sites both lie in the tile (the first n_loc): the source row is in LDS
-            // (Eq. sourceoffset)
-            for (int k = 0; k < n_loc; ++k) {
-                const BTerm t = tl[n_diag + k];
-                const float fa = pool[t.ta + dig[t.a][tid]] * (t.b >= 0 ? pool[t.tb + dig[t.b][tid]] : 1.f);
-                if (fa == 0.f) continue;  // an inadmissible source digit has factor 0 (App. A)
-                const float c = thl[t.param] * fa;
-                const float cr = c * t.wr, ci = CPLX ? c * t.wi : 0.f;
-                const int32_t rs = r - t.delta;
+            for (int i = 0; i < NP; ++i) pr[i] = rb + W::row(la, i) < nr ? rb + W::row(la, i) : nr - 1;
+            const uint32_t word = rw[r];
+            const auto factor = [&](int at, int field) {  // of a term at this row
+                return mul_rn(pool[(at & 0xffff) + digit_of(word, field & 0xffff)],
+                                 pool[(at >> 16) + digit_of(word, field >> 16 & 0x7fff)]);
+            };
+            const auto factor_of = [&](const LaneTerms& t, int k) { return factor(lane_of(t.at, k), lane_of(t.field, k)); };
+            uint64_t left[kSets];
+#pragma unroll
+            for (int q = 0; q < kSets; ++q) left[q] = todo[q];
+            float v[kBatchGather][NP][PW], acc[NP][PW];
+            float cr[kBatchGather], ci[kBatchGather];  // by rows
+            static_assert(kSets <= 2, "up to two sets of terms");
+            {
+                // diagonal: the low digits' sum, then the other terms
+                float ar[NV], ai[NV];
+                const auto add = [&](float c, float d, float2 s, int q) {
+                    ar[q] = fmaf(c, s.x, ar[q]);
+                    ai[q] = fmaf(c, s.y, ai[q]);
+                    if (CPLX) {
+                        ar[q] = fmaf(-d, s.y, ar[q]);
+                        ai[q] = fmaf(d, s.x, ai[q]);
+                    }
+                };
+                float dr = rd[0][r], di = CPLX ? rd[CPLX ? 1 : 0][r] : 0.f;
+#pragma unroll
+                for (int q = 0; q < kSets; ++q)
+                    for (uint64_t m = dtodo[q]; m; m &= m - 1) {
+                        const int k = __builtin_ctzll(m);
+                        float er = lane_of(lt[q].vr, k), ei = CPLX ? lane_of(lt[q].vi, k) : 0.f;
+                        if (!(uni[q] >> k & 1)) {
+                            const float f = factor_of(lt[q], k);
+                            er = mul_rn(lane_of(lt[q].wr, k), f);
+                            ei = CPLX ? mul_rn(lane_of(lt[q].wi, k), f) : 0.f;
+                        }
+                        dr = add_rn(dr, er);
+                        if (CPLX) di = add_rn(di, ei);
+                    }
 #pragma unroll
                 for (int q = 0; q < NV; ++q) {
-                    const float2 s = xt[q][rs];
-                    ar[q] += cr * s.x;
-                    ai[q] += cr * s.y;
+                    const float2 s = xt[q][r];
+                    ar[q] = mul_rn(dr, s.x);
+                    ai[q] = mul_rn(dr, s.y);
                     if (CPLX) {
-                        ar[q] -= ci * s.y;
-                        ai[q] += ci * s.x;
+                        ar[q] = fmaf(-di, s.y, ar[q]);
+                        ai[q] = fmaf(di, s.x, ai[q]);
                     }
                 }
+                // channels whose sites both lie among the low ones (the first n_loc): the source row is in LDS
+                // (Eq. sourceoffset); an inadmissible source reads the row itself with coefficient 0
+#pragma unroll
+                for (int q = 0; q < kSets; ++q) {
+                    const int k0 = q * 64 > n_diag ? q * 64 : n_diag;
+                    const int k1 = (q + 1) * 64 < n_diag + n_loc ? (q + 1) * 64 : n_diag + n_loc;
+                    float next = k0 < k1 ? factor_of(lt[q], k0 & 63) : 0.f;
+#pragma unroll 1
+                    for (int k = k0; k < k1; ++k) {
+                        const float f = next;
+                        if (k + 1 < k1) next = factor_of(lt[q], k + 1 & 63);  // under way during this term
+                        const bool in = f != 0.f;
+                        const float c = in ? mul_rn(lane_of(lt[q].wr, k & 63), f) : 0.f;
+                        const float d = CPLX && in ? mul_rn(lane_of(lt[q].wi, k & 63), f) : 0.f;
+                        const int32_t rs = in ? r - lane_of(lt[q].delta, k & 63) : r;
+#pragma unroll
+                        for (int e = 0; e < NV; ++e) add(c, d, xt[e][rs], e);
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                    for (int e = 0; e < PW; ++e) acc[p][e] = e & 1 ? ai[2 * p + e / 2] : ar[2 * p + e / 2];
+                W::transpose(acc, lane);
             }
-            // the others read global memory, kBatchGather channels at a time: every gather of a group is
-            // issued (masked where the factor is 0) before any of them is used
-            for (int k0 = n_loc; k0 < n_chan; k0 += kBatchGather) {
-                float cr[kBatchGather], ci[kBatchGather];
-                float2 v[kBatchGather][NV];
+            while (left[0] | left[kSets - 1]) {
+                // the next gathers of the list, in its order
+                int have = 0;
 #pragma unroll
                 for (int u = 0; u < kBatchGather; ++u) {
-                    cr[u] = 0.f;
-                    ci[u] = 0.f;
-                    if (k0 + u < n_chan) {
-                        const BTerm t = tl[n_diag + k0 + u];
-                        const float fa =
-                            pool[t.ta + dig[t.a][tid]] * (t.b >= 0 ? pool[t.tb + dig[t.b][tid]] : 1.f);
-                        const float c = thl[t.param] * fa;
-                        cr[u] = c * t.wr;
-                        ci[u] = CPLX ? c * t.wi : 0.f;
-                        if (fa != 0.f) {  // a nonzero factor: both source digits in range (App. A)
-                            load_row<NV>(xb + int64_t(F - t.delta) * NV, v[u]);
-                            continue;
-                        }
-                    }
+                    constexpr int kLast = kSets - 1;
+                    const bool z = kSets == 1 || left[0] != 0;
+                    const uint64_t m = z ? left[0] : left[kLast];
+                    if (m == 0) continue;
+                    const int k = __builtin_ctzll(m);
+                    if (z) left[0] = m & (m - 1);
+                    else left[kLast] = m & (m - 1);
+                    const auto pick = [&](auto x) {
+                        if constexpr (kSets == 1) return lane_of(x(lt[0]), k);
+                        else return z ? lane_of(x(lt[0]), k) : lane_of(x(lt[kLast]), k);
+                    };
+#define MRMF_OF(field) pick([](const LaneTerms& t) { return t.field; })
+                    const int delta = MRMF_OF(delta);
+                    if ((z ? uni[0] : uni[kLast]) >> k & 1) {
+                        const float2* src = xb + (int64_t(r0) - delta) * NV;
+                        cr[u] = MRMF_OF(vr);
+                        ci[u] = CPLX ? MRMF_OF(vi) : 0.f;
 #pragma unroll
-                    for (int q = 0; q < NV; ++q) v[u][q] = make_float2(0.f, 0.f);
+                        for (int i = 0; i < NP; ++i) W::load(src + uint32_t(pr[i] * NV + 2 * lp), v[u][i]);
+                    } else {  // an inadmissible source reads the row itself with coefficient 0
+                        const float f = factor(MRMF_OF(at), MRMF_OF(field));
+                        const bool in = f != 0.f;
+                        cr[u] = in ? mul_rn(MRMF_OF(wr), f) : 0.f;
+                        ci[u] = CPLX && in ? mul_rn(MRMF_OF(wi), f) : 0.f;
+                        const int off = in ? delta : 0;
+                        each<NP>([&](auto I) {
+                            const int64_t row = int64_t(r0) + pr[I] - W::template from<I>(off);
+                            W::load(xb + row * NV + 2 * lp, v[u][I]);
+                        });
+                    }
+                    have = u + 1;
+#undef MRMF_OF
                 }
 #pragma unroll
-                for (int u = 0; u < kBatchGather; ++u) {
+                for (int u = 0; u < kBatchGather; ++u)
+                    if (u < have) {
+                        each<NP>([&](auto I) {
+                            constexpr int i = I;
+                            const float c = __int_as_float(W::template from<i>(__float_as_int(cr[u])));
+                            const float d = CPLX ? __int_as_float(W::template from<i>(__float_as_int(ci[u]))) : 0.f;
 #pragma unroll
-                    for (int q = 0; q < NV; ++q) {
-                        const float2 s = v[u][q];
-                        ar[q] += cr[u] * s.x;
-                        ai[q] += cr[u] * s.y;
-                        if (CPLX) {
-                            ar[q] -= ci[u] * s.y;
-                            ai[q] += ci[u] * s.x;
-                        }
+                            for (int e = 0; e < PW; e += 2) {
+                                acc[i][e] = fmaf(c, v[u][i][e], acc[i][e]);
+                                acc[i][e + 1] = fmaf(c, v[u][i][e + 1], acc[i][e + 1]);
+                                if (CPLX) {
+                                    acc[i][e] = fmaf(-d, v[u][i][e + 1], acc[i][e]);
+                                    acc[i][e + 1] = fmaf(d, v[u][i][e], acc[i][e + 1]);
+                                }
+                            }
+                        });
                     }
-                }
             }
-            store_row<NV>(yb + int64_t(F) * NV, ar, ai);
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                if (rb + W::row(la, i) < nr) W::store(yb + int64_t(r0 + pr[i]) * NV + 2 * lp, acc[i], !shared);
         }
     }
 }
@@ -366,16 +616,18 @@ void launch_combine(const float* theta, int32_t K, int64_t n, const float2* G, i
 }
 
 template <int NV>
-void* batch_kernel_ptr(bool cplx) {
-    return cplx ? reinterpret_cast<void*>(&k_batch<NV, true>) : reinterpret_cast<void*>(&k_batch<NV, false>);
+void* batch_kernel_ptr(bool cplx, bool many) {
+    if (many) return cplx ? reinterpret_cast<void*>(&k_batch<NV, true, 2>) : reinterpret_cast<void*>(&k_batch<NV, false, 2>);
+    return cplx ? reinterpret_cast<void*>(&k_batch<NV, true, 1>) : reinterpret_cast<void*>(&k_batch<NV, false, 1>);
 }
 
-void* batch_kernel(int nvec, bool cplx) {
+// many: a lattice of more than 64 terms
+void* batch_kernel(int nvec, bool cplx, bool many) {
     switch (nvec) {
-        case 1: return batch_kernel_ptr<1>(cplx);
-        case 2: return batch_kernel_ptr<2>(cplx);
-        case 4: return batch_kernel_ptr<4>(cplx);
-        default: return batch_kernel_ptr<8>(cplx);
+        case 1: return batch_kernel_ptr<1>(cplx, many);
+        case 2: return batch_kernel_ptr<2>(cplx, many);
+        case 4: return batch_kernel_ptr<4>(cplx, many);
+        default: return batch_kernel_ptr<8>(cplx, many);
     }
 }
 
@@ -391,6 +643,13 @@ struct Shape {
 const Shape kShapes[] = {{1, 128}, {2, 128}, {2, 256}, {3, 256}, {3, 512}, {0, 64}, {1, 256}, {0, 128}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
+BDiv div_of(int64_t m) {  // 1 <= m < 2^30
+    BDiv v{0, 0};
+    while ((int64_t(1) << v.shift) < m) ++v.shift;
+    v.mul = static_cast<uint32_t>(((uint64_t(1) << (31 + v.shift)) + m - 1) / m);
+    return v;
+}
+
 int32_t rmax_of(int rc, int nvec) { return (64 << rc) * 8 / nvec; }
 
 }  // namespace
@@ -402,6 +661,7 @@ struct mrmf_batch_t {
     std::vector<int32_t> th_off;   // n + 1
     int64_t total = 0;             // elements, padded
     bool all_real = true;
+    int32_t max_terms = 0, max_pool = 0;  // of a lattice
     std::vector<unsigned char> image;
     size_t off_lat = 0, off_site = 0, off_term = 0, off_pool = 0, ws_bytes = 0;
     int32_t rc = 2, block = 256;  // R_max candidate index and block threads
@@ -435,21 +695,23 @@ mrmf::BatchArgs batch_args(const mrmf_batch_t* b, const void* d_ws) {
 int batch_grid(const mrmf_batch_t* b) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    // two resident blocks per CU (LDS: tile 32 KB, item table 8 KB, digits, factor pool, descriptors)
-    const int per_cu = 2;
+    // resident blocks per CU: 16 waves (four per SIMD at 128 registers), 160 KB of LDS
+    const int rows = mrmf::kBatchTileWords / b->nvec;
+    const int lds = mrmf::kBatchTileWords * 8 + 4 * (b->all_real ? 2 : 3) * rows + 1024 + 4 * b->max_pool;
+    const int per_cu = std::max(1, std::min(16 * 64 / b->block, 163840 / lds));
     return cus * per_cu;
 }
 
 mrmf_status launch(mrmf_batch_t* b, const void* d_ws, const float* theta, const void* X, void* Y, hipStream_t s) {
     const mrmf::BatchArgs a = batch_args(b, d_ws);
-    void* fn = mrmf::batch_kernel(b->nvec, !b->all_real);
+    void* fn = mrmf::batch_kernel(b->nvec, !b->all_real, b->max_terms > 64);
     const int grid = batch_grid(b);
     b->grid = grid;
     int32_t rc = b->rc, sched = b->sched;
     const float2* xp = static_cast<const float2*>(X);
     float2* yp = static_cast<float2*>(Y);
     void* args[] = {const_cast<mrmf::BatchArgs*>(&a), &theta, &xp, &yp, &rc, &sched};
-    return mrmf::hip_status(hipLaunchKernel(fn, dim3(grid), dim3(b->block), args, 0, s));
+    return mrmf::hip_status(hipLaunchKernel(fn, dim3(grid), dim3(b->block), args, 4 * size_t(b->max_pool), s));
 }
 
 mrmf_status check_call(const mrmf_batch_t* b, const void* d_ws, const float* th, const void* X, const void* Y) {
@@ -462,11 +724,8 @@ mrmf_status check_call(const mrmf_batch_t* b, const void* d_ws, const float* th,
     return MRMF_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, mrmf_batch* out) {
+// groups: lattice i keeps the terms of coupling i alone
+mrmf_status create(int32_t n, const mrmf_plan* plans, int32_t nvec, bool groups, mrmf_batch* out) {
     using namespace mrmf;
     if (!out) return MRMF_E_INVALID_ARG;
     *out = nullptr;
@@ -476,11 +735,11 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
     if (!b) return MRMF_E_INVALID_ARG;
     b->n = n;
     b->nvec = nvec;
-    std::vector<BLat> lats(n);
+    std::vector<BLat> lats(n + 1);  // the last one holds the item counts
     std::vector<BSite> sites;
     std::vector<BTerm> terms;
     std::vector<float> pool;
-    int64_t off = 0;
+    int64_t off = 0, items[kBatchRmaxCands] = {}, parts[kBatchRmaxCands] = {};
     int32_t th = 0;
     for (int i = 0; i < n; ++i) {
         const mrmf_plan_t* p = plans[i];
@@ -495,8 +754,17 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
             int64_t T = 1;
             int k = 0;
             while (k < p->N && T * p->d[p->N - 1 - k] <= rmax) T *= p->d[p->N - 1 - k++];
-            L.tile_rows[rc] = static_cast<int32_t>(T);
-            L.tile_sites[rc] = k;
+            L.low_rows[rc] = static_cast<int32_t>(T);
+            L.low_sites[rc] = k;
+            const int64_t d = k < p->N ? p->d[p->N - 1 - k] : 1, most = rmax / T;
+            const int64_t nch = most >= 2 ? (d + most - 1) / most : d;
+            L.chunk[rc] = most >= 2 ? static_cast<int32_t>((d + nch - 1) / nch) : 1;
+            L.n_chunks[rc] = L.chunk[rc] > 1 ? static_cast<int32_t>(nch) : 1;
+            L.item_beg[rc] = static_cast<int32_t>(items[rc]);
+            const int64_t own = L.chunk[rc] > 1 ? p->D / (T * d) * nch : p->D / T;
+            items[rc] += own;
+            L.part_beg[rc] = static_cast<int32_t>(parts[rc]);
+            parts[rc] += (own + 7) / 8;
         }
         b->dims.emplace_back(p->d.begin(), p->d.end());
         L.N = p->N;
@@ -508,7 +776,9 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
         for (int s = 0; s < p->N; ++s) {
             BSite bs{};
             bs.d = p->d[s];
-            bs.magic = ~uint64_t(0) / uint64_t(p->d[s]) + 1;
+            bs.by_d = div_of(p->d[s]);
+            bs.by_m = div_of(p->M[s]);
+            bs.by_md = div_of(p->M[s] * p->d[s]);
             sites.push_back(bs);
         }
         // factor pool of this lattice: entry 0 is 1.0 (second factor of a one-site term)
@@ -532,20 +802,25 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
             if (wi != 0.0) b->all_real = false;
             terms.push_back(t);
         };
-        L.diag_off = static_cast<int32_t>(terms.size());
-        for (const auto& g : p->diags) add_term(g.a, g.opa, g.b, g.opb, g.param, g.wr, g.wi, 0);
-        L.n_diag = static_cast<int32_t>(p->diags.size());
-        L.chan_off = static_cast<int32_t>(terms.size());
-        for (const auto& c : p->chans) add_term(c.a, c.opa, c.b, c.opb, c.param, c.wr, c.wi, c.delta);
-        L.n_chan = static_cast<int32_t>(p->chans.size());
-        // channels by the number of low sites a tile must span (stable), so that for every tile size the
-        // channels whose source lies in the tile are a prefix of the list
-        std::stable_sort(terms.begin() + L.chan_off, terms.end(),
-                         [](const BTerm& u, const BTerm& v) { return u.low < v.low; });
+        const size_t t0 = terms.size();
+        L.term_off = static_cast<int32_t>(t0);
+        for (const auto& g : p->diags)
+            if (!groups || g.param == i) add_term(g.a, g.opa, g.b, g.opb, g.param, g.wr, g.wi, 0);
+        const size_t t1 = terms.size();
+        L.n_diag = static_cast<int32_t>(t1 - t0);
+        for (const auto& c : p->chans)
+            if (!groups || c.param == i) add_term(c.a, c.opa, c.b, c.opb, c.param, c.wr, c.wi, c.delta);
+        L.n_chan = static_cast<int32_t>(terms.size() - t1);
+        b->max_terms = std::max(b->max_terms, L.n_diag + L.n_chan);
+        // by the number of low sites a tile must span (stable), so that for every tile size the diagonal terms of the
+        // low digits and the channels whose source lies in the tile are prefixes of their lists
+        const auto by_low = [](const BTerm& u, const BTerm& v) { return u.low < v.low; };
+        std::stable_sort(terms.begin() + t0, terms.begin() + t1, by_low);
+        std::stable_sort(terms.begin() + t1, terms.end(), by_low);
         for (int rc = 0; rc < kBatchRmaxCands; ++rc) {
-            int32_t nl = 0;
-            for (size_t k = L.chan_off; k < terms.size(); ++k) nl += terms[k].low <= L.tile_sites[rc];
-            L.n_local[rc] = nl;
+            L.n_ldiag[rc] = L.n_local[rc] = 0;
+            for (size_t k = t0; k < terms.size(); ++k)
+                if (terms[k].low <= L.low_sites[rc]) ++(k < t1 ? L.n_ldiag[rc] : L.n_local[rc]);
         }
         if (lp.size() > size_t(kBatchPoolMax)) {
             delete b;
@@ -553,6 +828,7 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
         }
         L.pool_off = static_cast<int32_t>(pool.size());
         L.pool_n = static_cast<int32_t>(lp.size());
+        b->max_pool = std::max(b->max_pool, L.pool_n);
         pool.insert(pool.end(), lp.begin(), lp.end());
         b->off.push_back(off);
         b->th_off.push_back(th);
@@ -561,6 +837,14 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
     }
     b->th_off.push_back(th);
     b->total = off;
+    for (int rc = 0; rc < kBatchRmaxCands; ++rc) {
+        if (items[rc] >= (int64_t(1) << 30)) {  // more rows than any memory holds
+            delete b;
+            return MRMF_E_OVERFLOW;
+        }
+        lats[n].item_beg[rc] = static_cast<int32_t>(items[rc]);
+        lats[n].part_beg[rc] = static_cast<int32_t>(parts[rc]);
+    }
     if (off * 8 >= (int64_t(1) << 62)) {
         delete b;
         return MRMF_E_OVERFLOW;
@@ -582,6 +866,23 @@ mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, m
     std::memcpy(b->image.data() + b->off_pool, pool.data(), sizeof(float) * pool.size());
     *out = b;
     return MRMF_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+mrmf_status mrmf_batch_create(int32_t n, const mrmf_plan* plans, int32_t nvec, mrmf_batch* out) {
+    return create(n, plans, nvec, false, out);
+}
+
+mrmf_status mrmf_batch_create_groups(mrmf_plan plan, int32_t nvec, mrmf_batch* out) {
+    if (!plan || !out) return MRMF_E_INVALID_ARG;
+    *out = nullptr;
+    if (plan->n_params < 1 || plan->n_params > mrmf::kBatchMaxParams) return MRMF_E_UNSUPPORTED;
+    const std::vector<mrmf_plan> plans(plan->n_params, plan);
+    const mrmf_status st = create(plan->n_params, plans.data(), nvec, true, out);
+    return st == MRMF_OK ? mrmf_batch_share_input(*out, 1) : st;
 }
 
 void mrmf_batch_destroy(mrmf_batch batch) { delete batch; }

@@ -390,6 +390,22 @@ class Batch:
         arr = (ctypes.c_void_p * len(self.plans))(*[p.handle.value for p in self.plans])
         self._handle = ctypes.c_void_p()
         L.call("mrmf_batch_create", len(self.plans), arr, self.nvec, ctypes.byref(self._handle))
+        self._upload()
+
+    @classmethod
+    def _of_groups(cls, plan: Plan, nvec: int):
+        """n_params lattices of one plan with a shared input, lattice p holding the terms of coupling p alone."""
+        self = cls.__new__(cls)
+        self.plans = [plan] * plan.n_params
+        self.nvec = int(nvec)
+        self.device = plan.device
+        self._handle = ctypes.c_void_p()
+        L.call("mrmf_batch_create_groups", plan.handle, self.nvec, ctypes.byref(self._handle))
+        self.shared_input = True
+        self._upload()
+        return self
+
+    def _upload(self):
         n = len(self.plans)
         te = ctypes.c_int64()
         L.call("mrmf_batch_total_elems", self._handle, ctypes.byref(te))
@@ -476,7 +492,7 @@ class Batch:
         """Launch shape: tiles of at most tile_rows_max rows ((64, 128, 256, 512) * 8 / nvec), block
         threads (a multiple of 64, at most 512 and 4096 / nvec) and, when given, the work schedule
         ("runs": a contiguous run of items per block; "windows": consecutive items side by side;
-        "xcd_chunk": each XCD its own eighth of the items, its blocks side by side)."""
+        "xcd_chunk": each XCD its own eighth of every lattice, its blocks side by side)."""
         L.call("mrmf_batch_set_shape", self._handle, int(tile_rows_max), int(block))
         if schedule is not None:
             L.call("mrmf_batch_set_schedule", self._handle,
@@ -561,8 +577,8 @@ class Sweep:
         if not 1 <= P <= 16:
             raise ValueError("a sweep by linearity needs 1 to 16 couplings")
         self.plan, self.nvec, self.P, self.device = plan, int(nvec), P, plan.device
-        self.basis = Batch([plan] * P, self.nvec)
-        self.basis.share_input(True)
+        self.basis = Batch._of_groups(plan, self.nvec)
+        self.basis.set_shape(256 * 8 // self.nvec, 256, "xcd_chunk")
         self.n = plan.D * self.nvec
         self.stride = (self.n + 31) // 32 * 32          # the batch's block pitch (offsets padded to 32)
         if P > 1 and self.basis.offsets[1] - self.basis.offsets[0] != self.stride:

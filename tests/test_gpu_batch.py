@@ -296,3 +296,62 @@ def test_sweep_by_linearity():
         def block(self, T, k):
             return sw.block(T, k)
     check_all(_View(), models, [x] * len(models), Y)
+
+
+@pytest.mark.parametrize("nvec", [1, 2, 4, 8])
+def test_batch_tiles_and_term_sets(nvec):
+    """Lattices at the edges of the tiling, in one batch and in every launch shape: one whose large site is cut into
+    chunks of digits (the last of them shorter), one with more than 64 terms, one smaller than a wave, one with complex
+    weights.  The product of each against the oracle (c64 tolerance), and the same bits from every shape."""
+    from workloads.model import OP_LOWER, OP_RAISE, OP_Z, Model, Term, boson_site, spin_site, xxz_bond_terms
+    rng = np.random.default_rng(300 + nvec)
+
+    def pairs(sites, bonds):
+        terms, theta = [], []
+        for k, (i, j) in enumerate(bonds):
+            terms += xxz_bond_terms(i, j, 2 * k, 2 * k + 1)
+            theta += list(rng.uniform(0.5, 1.5, 2))
+        return Model(sites, terms, np.array(theta))
+    spins = [spin_site(int(k)) for k in rng.integers(1, 4, 7)]
+    cut = [spin_site(1), spin_site(2), boson_site(198), spin_site(2), spin_site(1)]
+    models = [
+        pairs(cut, [(0, 1), (1, 2), (2, 3), (3, 4), (0, 4), (1, 3)]),
+        pairs(spins + [spin_site(1)], [(i, j) for i in range(8) for j in range(i)]),
+        pairs([spin_site(2), spin_site(3)], [(0, 1)]),
+        Model([spin_site(2)] * 6, [t for i in range(5) for t in (Term(i, OP_RAISE, i + 1, OP_LOWER, 0, 0.3 + 0.4j),
+                                                               Term(i, OP_LOWER, i + 1, OP_RAISE, 0, 0.3 - 0.4j))]
+              + [Term(i, OP_Z, -1, OP_Z, 1, 1.0) for i in range(6)], np.array([0.9, 0.3])),
+    ]
+    for group in (models, models[:3]):   # with and without complex weights
+        xs = [W.random_state(m.dim, rng, np.complex64, nvec=nvec) for m in group]
+        B, X, th = build(group, xs, nvec=nvec)
+        first = None
+        for rows in (64, 128, 256, 512):
+            for block, sched in ((64, "runs"), (256, "windows"), (512, "xcd_chunk")):
+                B.set_shape(rows * 8 // nvec, block, sched)
+                Y = B.matvec(th, X, torch.zeros_like(X))
+                torch.cuda.synchronize()
+                if first is None:
+                    first = Y
+                    check_all(B, group, xs, Y)
+                assert torch.equal(Y, first), (rows, block, sched)
+
+
+@pytest.mark.parametrize("nvec", [1, 8])
+def test_group_products(nvec):
+    """The sweep's batch: block p is the product of the terms of coupling p alone, equal to the batch of full plans at
+    unit couplings up to the FP32 roundings of one product (1e-6)."""
+    from paper_2606_02169_amd.plan import Batch, Plan, Sweep
+    base = W.ferrimagnetic_ring(8)
+    x = W.random_state(base.dim, np.random.default_rng(76), np.complex64, nvec=nvec)
+    plan = Plan.from_model(base)
+    sw = Sweep(plan, nvec)
+    X = torch.zeros(sw.input_elems, dtype=torch.complex64, device=DEV)
+    X[: sw.n].view(base.dim, nvec).copy_(torch.from_numpy(x.reshape(base.dim, nvec)).to(DEV))
+    full = Batch([plan] * plan.n_params, nvec)
+    full.share_input(True)
+    G = sw.basis.matvec(sw.unit, X)
+    F = full.matvec(sw.unit, X)
+    torch.cuda.synchronize()
+    for p in range(plan.n_params):
+        assert rel_err(sw.basis.block(G, p).cpu().numpy(), full.block(F, p).cpu().numpy()) <= 1e-6, p
