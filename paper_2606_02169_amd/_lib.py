@@ -187,10 +187,17 @@ def check(status: int, where: str):
         raise MrmfError(status, where)
 
 
+_entry = {}   # entry points by name, as lib() holds them
+
+
 def call(name: str, *args):
     """Call an entry point and raise MrmfError on a non-OK status."""
-    st = getattr(lib(), name)(*args)
-    check(st, name)
+    f = _entry.get(name)
+    if f is None:
+        f = _entry[name] = getattr(lib(), name)
+    st = f(*args)
+    if st != MRMF_OK:
+        raise MrmfError(st, name)
     return st
 
 

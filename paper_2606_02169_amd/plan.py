@@ -14,16 +14,19 @@ import torch
 from . import _lib as L
 
 
-def _stream(device=None) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# Small products are bound by this path: a 12-site chain takes 4 us on the device.  The stream is read as a handle,
+# without a torch.cuda.Stream around it, and addresses go to ctypes as integers (the argument types convert them).
+def _stream(device=None) -> int:
+    index = None if device is None else device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
-def _ptr(t: torch.Tensor) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr())
+def _ptr(t: torch.Tensor) -> int:
+    return t.data_ptr()
 
 
 def _need_gpu(t: torch.Tensor, name: str, dtype=None):
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
