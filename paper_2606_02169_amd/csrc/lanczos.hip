@@ -267,6 +267,89 @@ __global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* __r
     if (threadIdx.x == 0) pn[blockIdx.x] = nrm[0];
 }
 
+// The update of one pass and the coefficients of the next in one read of the basis: w -= sum_{i<k} c_i V_i, then
+// partial[i * nb + block] = <V_i|w> of the new w.  A thread keeps the k entries of its row in registers between the two,
+// and the k sums; rows, order and rounding are those of k_gs_update and k_gs_dots.  Bound by the reads of the basis (three
+// instead of four for two passes): 40 steps of 10 million rows 130 -> 105 ms.
+// Up to kMidMax vectors: 4 KM registers for the row and as many for the sums (beyond 256 in the accumulator half of the
+// register file, whose moves the arithmetic has room for); one wave per SIMD still has KM KB of loads under way.
+constexpr int kMidMax = 48;
+template <int KM>
+__global__ __launch_bounds__(kRB) void k_gs_middle(int64_t n, const double2* __restrict__ V, int k,
+                                                    const double2* __restrict__ c, int nbs, double2* __restrict__ w,
+                                                    double2* __restrict__ partial, int nb,
+                                                    const int32_t* __restrict__ stopped) {
+    if (halted(stopped)) return;
+    __shared__ double2 lc[KM];
+    __shared__ double lds[2 * kGroup * (kRB / 64)];
+    if (threadIdx.x < KM) {  // beyond k: row k - 1 once more, with coefficient 0 and a sum that is not used
+        double2 a = make_double2(0.0, 0.0);
+        if (threadIdx.x >= k) {
+        } else if (nbs > 0) {
+            for (int q = 0; q < nbs; ++q) {
+                const double2 p = c[int64_t(threadIdx.x) * nbs + q];
+                a.x += p.x;
+                a.y += p.y;
+            }
+        } else {
+            a = c[threadIdx.x];
+        }
+        lc[threadIdx.x] = a;
+    }
+    __syncthreads();
+    double v[2 * KM];
+#pragma unroll
+    for (int g = 0; g < 2 * KM; ++g) v[g] = 0.0;
+    const auto at = [](const double2* base, uint32_t byte) {  // 32-bit lane offset from a uniform base
+        return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(base) + byte);
+    };
+    for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(nb) * kRB) {
+        double2 x[KM];
+        const uint32_t o = static_cast<uint32_t>(i) * 16u;
+#pragma unroll
+        for (int g = 0; g < KM; ++g) x[g] = at(V + int64_t(g < k ? g : k - 1) * n, o);
+        const double2 y = at(w, o);
+        asm volatile("" ::: "memory");  // coefficients come from LDS for each row, not from registers held across rows
+        double ar = 0.0, ai = 0.0;
+#pragma unroll
+        for (int g = 0; g < KM; ++g) {
+            const double2 cg = lc[g];
+            ar += cg.x * x[g].x - cg.y * x[g].y;
+            ai += cg.x * x[g].y + cg.y * x[g].x;
+        }
+        const double2 r = make_double2(y.x - ar, y.y - ai);
+        w[i] = r;
+#pragma unroll
+        for (int g = 0; g < KM; ++g) {
+            v[2 * g] += x[g].x * r.x + x[g].y * r.y;
+            v[2 * g + 1] += x[g].x * r.y - x[g].y * r.x;
+        }
+    }
+#pragma unroll
+    for (int g0 = 0; g0 < KM; g0 += kGroup) {  // a group at a time, for the registers
+        double t[2 * kGroup];
+#pragma unroll
+        for (int g = 0; g < 2 * kGroup; ++g) t[g] = v[2 * g0 + g];
+        block_sum<2 * kGroup>(t, lds);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int g = 0; g < kGroup; ++g)
+                if (g0 + g < k) partial[int64_t(g0 + g) * nb + blockIdx.x] = make_double2(t[2 * g], t[2 * g + 1]);
+    }
+}
+
+using MiddleKernel = void (*)(int64_t, const double2*, int, const double2*, int, double2*, double2*, int, const int32_t*);
+MiddleKernel middle_kernel(int k) {  // 1 <= k <= kMidMax
+    switch ((k + 7) / 8) {
+        case 1: return k_gs_middle<8>;
+        case 2: return k_gs_middle<16>;
+        case 3: return k_gs_middle<24>;
+        case 4: return k_gs_middle<32>;
+        case 5: return k_gs_middle<40>;
+        default: return k_gs_middle<48>;
+    }
+}
+
 // u = sum_{i<steps} s_i V_i and the partial sums of ||u||^2
 __global__ __launch_bounds__(kRB) void k_ritz_vector(int64_t n, const double2* __restrict__ V,
                                                       const LzState* __restrict__ st,
@@ -822,16 +905,36 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
     mrmf_status rc = launch_status();
     if (rc != MRMF_OK) return rc;
 
-    // One Gram-Schmidt pass of w against rows 0..k-1.  decides: it runs only where the first one shrank w; stop: the
-    // flag that skips it otherwise; pn: where the new ||w||^2 leaves its partial sums (null: not needed).
-    auto pass = [&](int k, double2* w, bool decides, const int32_t* stop, double* pn) {
-        const int32_t* after = decides ? &st->skip2 : stop;  // the flag of the pass's later kernels
+    // The kernels of Gram-Schmidt passes of w against rows 0..k-1.  Few partial sums (a small vector): the kernels that
+    // use the coefficients sum them themselves.
+    const bool inl = nb <= 32;
+    double2* pc2 = pc + int64_t(m + 1) * (kMaxRedBlocks / 2);  // (then) the second pass's partial sums
+    auto dots = [&](int k, const double2* w, bool decides, const int32_t* stop) {
         hipLaunchKernelGGL(k_gs_dots, dim3(nb, (k + kGroup - 1) / kGroup), tb, 0, s, D, V, k, w, pc, nb,
                            decides ? pn0 : nullptr, pn1, nb, st, stop);
-        // few partial sums (a small vector): the update sums them itself
-        const bool inl = nb <= 32;
-        if (!inl) hipLaunchKernelGGL(k_gs_finalize, dim3(k), tb, 0, s, nb, pc, coef, after);
-        hipLaunchKernelGGL(k_gs_update, gv, tb, 0, s, D, V, k, inl ? pc : coef, inl ? nb : 0, w, pn, after);
+    };
+    auto finalize = [&](int k, const int32_t* stop) {
+        if (!inl) hipLaunchKernelGGL(k_gs_finalize, dim3(k), tb, 0, s, nb, pc, coef, stop);
+    };
+    auto update = [&](int k, double2* w, const double2* part, double* pn, const int32_t* stop) {
+        hipLaunchKernelGGL(k_gs_update, gv, tb, 0, s, D, V, k, inl ? part : coef, inl ? nb : 0, w, pn, stop);
+    };
+    // One pass.  decides: it runs only where the first one shrank w; stop: the flag that skips it otherwise; pn: where
+    // the new ||w||^2 leaves its partial sums (null: not needed).
+    auto pass = [&](int k, double2* w, bool decides, const int32_t* stop, double* pn) {
+        const int32_t* after = decides ? &st->skip2 : stop;  // the flag of the pass's later kernels
+        dots(k, w, decides, stop);
+        finalize(k, after);
+        update(k, w, pc, pn, after);
+    };
+    // Two passes that always run, the first one's update with the second one's dots (32-bit offsets: D < 2^28).
+    auto two_passes = [&](int k, double2* w, const int32_t* stop, double* pn) {
+        dots(k, w, false, stop);
+        finalize(k, stop);
+        hipLaunchKernelGGL(middle_kernel(k), gv, tb, 0, s, D, V, k, inl ? pc : coef, inl ? nb : 0, w, inl ? pc2 : pc, nb,
+                           stop);
+        finalize(k, stop);
+        update(k, w, pc2, pn, stop);
     };
 
     const bool full = reorth == MRMF_REORTH_CGS2, cond = reorth == MRMF_REORTH_CGS2_COND;
@@ -847,7 +950,10 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
                            j > 0 ? row(j - 1) : nullptr, pa, nb, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr, pn0,
                            stopped);
         const double* pn = pn0;  // where the partial sums of the final ||w||^2 are
-        if (full || cond) {
+        if (full && j + 1 <= kMidMax && D < (int64_t(1) << 28)) {
+            two_passes(j + 1, w, stopped, pn1);
+            pn = pn1;
+        } else if (full || cond) {
             pass(j + 1, w, false, stopped, cond ? pn1 : nullptr);
             pass(j + 1, w, cond, stopped, pn1);
             pn = pn1;
