@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstddef>
+#include <type_traits>
 
 #include "mrmf_internal.h"
 #include "reduce.h"
@@ -137,6 +138,24 @@ __global__ __launch_bounds__(kRB) void k_resid_partial(int64_t n, const double2*
 }
 
 // ---------------------------------------------------------------- Gram-Schmidt
+// partial[i * nb + block], i < k, from the threads' KM sums (the waves' trees, then in wave order); lds: 2 KM doubles a
+// wave.  One barrier, and every lane ends some of the sums: 40 vectors of a small lattice took 4 us in the reduction.
+template <int KM>
+__device__ __forceinline__ void store_sums(double (&v)[2 * KM], int k, double2* __restrict__ partial, int nb, double* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wave_tree_shared<2 * KM>(v, lane);
+    if ((lane & 3) == 0) {
+#pragma unroll
+        for (int j = 0; j < KM / 8; ++j) lds[wave * 2 * KM + wave_share(lane, 2 * KM) + j] = v[j];
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 2 * k; t += kRB) {
+        double s = 0.0;
+        for (int w = 0; w < kRB / 64; ++w) s += lds[w * 2 * KM + t];
+        reinterpret_cast<double*>(partial + int64_t(t >> 1) * nb + blockIdx.x)[t & 1] = s;
+    }
+}
+
 // A pass is k_gs_dots, k_gs_finalize (large vectors) and k_gs_update; `stopped` is the step's halt flag, or the flag of a
 // pass that may be skipped.  The second pass of the conditional form decides by itself, in its first kernel (pre set):
 // it runs when the first one left ||w||^2 below half its value before (Daniel, Gragg, Kaufman and Stewart, 1976), and
@@ -180,11 +199,7 @@ __global__ __launch_bounds__(kRB) void k_gs_dots(int64_t n, const double2* __res
             }
         }
     }
-    block_sum<2 * kGroup>(v, lds);
-    if (threadIdx.x == 0) {
-        for (int g = 0; g < kGroup; ++g)
-            if (base + g < k) partial[int64_t(base + g) * nb + blockIdx.x] = make_double2(v[2 * g], v[2 * g + 1]);
-    }
+    store_sums<kGroup>(v, k - base < kGroup ? k - base : kGroup, partial + int64_t(base) * nb, nb, lds);
 }
 
 // c_i from its partial sums, a block per coefficient (57 us -> 5 us for 512 partials: they were read by one thread each)
@@ -267,6 +282,11 @@ __global__ __launch_bounds__(kRB) void k_gs_update(int64_t n, const double2* __r
     if (threadIdx.x == 0) pn[blockIdx.x] = nrm[0];
 }
 
+// a basis entry: 32-bit lane offset from a uniform row
+__device__ __forceinline__ double2 entry(const double2* __restrict__ row, uint32_t byte) {
+    return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(row) + byte);
+}
+
 // The update of one pass and the coefficients of the next in one read of the basis: w -= sum_{i<k} c_i V_i, then
 // partial[i * nb + block] = <V_i|w> of the new w.  A thread keeps the k entries of its row in registers between the two,
 // and the k sums; rows, order and rounding are those of k_gs_update and k_gs_dots.  Bound by the reads of the basis (three
@@ -281,7 +301,7 @@ __global__ __launch_bounds__(kRB) void k_gs_middle(int64_t n, const double2* __r
                                                     const int32_t* __restrict__ stopped) {
     if (halted(stopped)) return;
     __shared__ double2 lc[KM];
-    __shared__ double lds[2 * kGroup * (kRB / 64)];
+    __shared__ double lds[2 * KM * (kRB / 64)];
     if (threadIdx.x < KM) {  // beyond k: row k - 1 once more, with coefficient 0 and a sum that is not used
         double2 a = make_double2(0.0, 0.0);
         if (threadIdx.x >= k) {
@@ -300,15 +320,12 @@ __global__ __launch_bounds__(kRB) void k_gs_middle(int64_t n, const double2* __r
     double v[2 * KM];
 #pragma unroll
     for (int g = 0; g < 2 * KM; ++g) v[g] = 0.0;
-    const auto at = [](const double2* base, uint32_t byte) {  // 32-bit lane offset from a uniform base
-        return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(base) + byte);
-    };
     for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(nb) * kRB) {
         double2 x[KM];
         const uint32_t o = static_cast<uint32_t>(i) * 16u;
 #pragma unroll
-        for (int g = 0; g < KM; ++g) x[g] = at(V + int64_t(g < k ? g : k - 1) * n, o);
-        const double2 y = at(w, o);
+        for (int g = 0; g < KM; ++g) x[g] = entry(V + int64_t(g < k ? g : k - 1) * n, o);
+        const double2 y = entry(w, o);
         asm volatile("" ::: "memory");  // coefficients come from LDS for each row, not from registers held across rows
         double ar = 0.0, ai = 0.0;
 #pragma unroll
@@ -325,30 +342,73 @@ __global__ __launch_bounds__(kRB) void k_gs_middle(int64_t n, const double2* __r
             v[2 * g + 1] += x[g].x * r.y - x[g].y * r.x;
         }
     }
-#pragma unroll
-    for (int g0 = 0; g0 < KM; g0 += kGroup) {  // a group at a time, for the registers
-        double t[2 * kGroup];
-#pragma unroll
-        for (int g = 0; g < 2 * kGroup; ++g) t[g] = v[2 * g0 + g];
-        block_sum<2 * kGroup>(t, lds);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g)
-                if (g0 + g < k) partial[int64_t(g0 + g) * nb + blockIdx.x] = make_double2(t[2 * g], t[2 * g + 1]);
-    }
+    store_sums<KM>(v, k, partial, nb, lds);
 }
 
-using MiddleKernel = void (*)(int64_t, const double2*, int, const double2*, int, double2*, double2*, int, const int32_t*);
-MiddleKernel middle_kernel(int k) {  // 1 <= k <= kMidMax
-    switch ((k + 7) / 8) {
-        case 1: return k_gs_middle<8>;
-        case 2: return k_gs_middle<16>;
-        case 3: return k_gs_middle<24>;
-        case 4: return k_gs_middle<32>;
-        case 5: return k_gs_middle<40>;
-        default: return k_gs_middle<48>;
+// k_three_term_norm and the coefficients <V_i|w> of the new w, i < k = j + 1, in one pass (up to kMidMax vectors): the
+// row's entries of v_j and v_{j-1} are read anyway, and w and the launch are saved.  Rounding as in the two kernels.
+template <int KM>
+__global__ __launch_bounds__(kRB) void k_three_term_dots(int64_t n, double2* __restrict__ w,
+                                                          const float2* __restrict__ h32,
+                                                          const double2* __restrict__ V, int k,
+                                                          const double* __restrict__ pa, int nb,
+                                                          double* __restrict__ alpha, const double* __restrict__ beta,
+                                                          double* __restrict__ pn, double2* __restrict__ partial,
+                                                          const int32_t* __restrict__ stopped) {
+    if (halted(stopped)) return;
+    __shared__ double lds[kMaxRedBlocks + 1];
+    const double a = sum_partials(pa, nb, 1, lds);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
+    const bool two = k > 1;
+    const double b = two ? *beta : 0.0;
+    double v[2 * KM], nrm[1] = {0.0};
+#pragma unroll
+    for (int g = 0; g < 2 * KM; ++g) v[g] = 0.0;
+    for (int64_t i = int64_t(blockIdx.x) * kRB + threadIdx.x; i < n; i += int64_t(nb) * kRB) {
+        double2 x[KM];
+        const uint32_t o = static_cast<uint32_t>(i) * 16u;
+#pragma unroll
+        for (int g = 0; g < KM; ++g) x[g] = entry(V + int64_t(g < k ? g : k - 1) * n, o);
+        const double2 xj = entry(V + int64_t(k - 1) * n, o), xm = entry(V + int64_t(two ? k - 2 : 0) * n, o);
+        double2 y;
+        if (h32) {
+            const float2 h = h32[i];
+            y = make_double2(h.x, h.y);
+        } else {
+            y = entry(w, o);
+        }
+        y.x -= a * xj.x;
+        y.y -= a * xj.y;
+        if (two) {
+            y.x -= b * xm.x;
+            y.y -= b * xm.y;
+        }
+        w[i] = y;
+        nrm[0] += y.x * y.x + y.y * y.y;
+#pragma unroll
+        for (int g = 0; g < KM; ++g) {
+            v[2 * g] += x[g].x * y.x + x[g].y * y.y;
+            v[2 * g + 1] += x[g].x * y.y - x[g].y * y.x;
+        }
+    }
+    block_sum<1>(nrm, lds);
+    if (threadIdx.x == 0) pn[blockIdx.x] = nrm[0];
+    store_sums<KM>(v, k, partial, nb, lds);
+}
+
+// f with the kernels' vector count for k <= kMidMax: the next multiple of a group
+template <typename F>
+void with_vectors(int k, F&& f) {
+    switch ((k + kGroup - 1) / kGroup) {
+        case 1: return f(std::integral_constant<int, kGroup>{});
+        case 2: return f(std::integral_constant<int, 2 * kGroup>{});
+        case 3: return f(std::integral_constant<int, 3 * kGroup>{});
+        case 4: return f(std::integral_constant<int, 4 * kGroup>{});
+        case 5: return f(std::integral_constant<int, 5 * kGroup>{});
+        default: return f(std::integral_constant<int, 6 * kGroup>{});
     }
 }
+static_assert(kMidMax == 6 * kGroup, "with_vectors covers every count");
 
 // u = sum_{i<steps} s_i V_i and the partial sums of ||u||^2
 __global__ __launch_bounds__(kRB) void k_ritz_vector(int64_t n, const double2* __restrict__ V,
@@ -920,19 +980,20 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
         hipLaunchKernelGGL(k_gs_update, gv, tb, 0, s, D, V, k, inl ? part : coef, inl ? nb : 0, w, pn, stop);
     };
     // One pass.  decides: it runs only where the first one shrank w; stop: the flag that skips it otherwise; pn: where
-    // the new ||w||^2 leaves its partial sums (null: not needed).
-    auto pass = [&](int k, double2* w, bool decides, const int32_t* stop, double* pn) {
+    // the new ||w||^2 leaves its partial sums (null: not needed); dotted: the coefficients' partial sums are there.
+    auto pass = [&](int k, double2* w, bool decides, const int32_t* stop, double* pn, bool dotted) {
         const int32_t* after = decides ? &st->skip2 : stop;  // the flag of the pass's later kernels
-        dots(k, w, decides, stop);
+        if (!dotted) dots(k, w, decides, stop);
         finalize(k, after);
         update(k, w, pc, pn, after);
     };
-    // Two passes that always run, the first one's update with the second one's dots (32-bit offsets: D < 2^28).
+    // Two passes that always run, the first one's update with the second one's dots.
     auto two_passes = [&](int k, double2* w, const int32_t* stop, double* pn) {
-        dots(k, w, false, stop);
         finalize(k, stop);
-        hipLaunchKernelGGL(middle_kernel(k), gv, tb, 0, s, D, V, k, inl ? pc : coef, inl ? nb : 0, w, inl ? pc2 : pc, nb,
-                           stop);
+        with_vectors(k, [&](auto KM) {
+            hipLaunchKernelGGL(k_gs_middle<decltype(KM)::value>, gv, tb, 0, s, D, V, k, inl ? pc : coef, inl ? nb : 0, w,
+                               inl ? pc2 : pc, nb, stop);
+        });
         finalize(k, stop);
         update(k, w, pc2, pn, stop);
     };
@@ -946,16 +1007,33 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
         rc = c32 ? mv_c(x32, y32, s, stopped) : mv_z(row(j), w, s, stopped);
         if (rc != MRMF_OK) return rc;
         hipLaunchKernelGGL(k_alpha_partial, gv, tb, 0, s, D, row(j), w, c32 ? y32 : nullptr, pa, stopped);
-        hipLaunchKernelGGL(k_three_term_norm, gv, tb, 0, s, D, w, c32 ? y32 : nullptr, row(j),
-                           j > 0 ? row(j - 1) : nullptr, pa, nb, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr, pn0,
-                           stopped);
         const double* pn = pn0;  // where the partial sums of the final ||w||^2 are
-        if (full && j + 1 <= kMidMax && D < (int64_t(1) << 28)) {
-            two_passes(j + 1, w, stopped, pn1);
+        // The kernels that hold a row of the basis in registers: up to kMidMax vectors and 32-bit lane offsets.  Up to 24
+        // vectors (two waves per SIMD) they are never slower; beyond that one wave per SIMD has to be worth the read
+        // that it saves.  Steps 25 to 40, with k_gs_middle against without: 2^14 rows 0.82 against 0.71 ms, 2^16 1.11
+        // and 1.11, 2^18 2.49 and 2.77, 2^20 7.1 and 8.6; k_three_term_dots on top of it: 2^18 2.64, 2^20 7.30, 2^21
+        // 12.2 against 12.3, 2^22 23.8 against 24.6.
+        const int k = j + 1;
+        const bool fits = (full || cond) && k <= kMidMax && D < (int64_t(1) << 28);
+        const bool fused = fits && (k <= 24 || D >= (int64_t(1) << 21));        // three-term update with the dots
+        const bool middle = full && fits && (k <= 24 || D >= (int64_t(1) << 16));  // update with the next pass's dots
+        if (fused) {
+            with_vectors(j + 1, [&](auto KM) {
+                hipLaunchKernelGGL(k_three_term_dots<decltype(KM)::value>, gv, tb, 0, s, D, w, c32 ? y32 : nullptr, V,
+                                   j + 1, pa, nb, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr, pn0, pc, stopped);
+            });
+        } else {
+            hipLaunchKernelGGL(k_three_term_norm, gv, tb, 0, s, D, w, c32 ? y32 : nullptr, row(j),
+                               j > 0 ? row(j - 1) : nullptr, pa, nb, d_alpha + j, j > 0 ? d_beta + (j - 1) : nullptr,
+                               pn0, stopped);
+        }
+        if (middle) {
+            if (!fused) dots(k, w, false, stopped);
+            two_passes(k, w, stopped, pn1);
             pn = pn1;
         } else if (full || cond) {
-            pass(j + 1, w, false, stopped, cond ? pn1 : nullptr);
-            pass(j + 1, w, cond, stopped, pn1);
+            pass(j + 1, w, false, stopped, cond ? pn1 : nullptr, fused);
+            pass(j + 1, w, cond, stopped, pn1, false);
             pn = pn1;
         }
         if (reorth == MRMF_REORTH_PARTIAL) {
@@ -964,7 +1042,7 @@ mrmf_status lanczos_run(int64_t D, const MatvecOp& mv_z, const MatvecOp& mv_c, i
             const double eps = c32 ? 1.1920928955078125e-07 : 2.220446049250313e-16;  // 2^-23 or 2^-52
             hipLaunchKernelGGL(k_pro_estimate, dim3(1), tb, 0, s, pn0, nb, j, m, D, eps, d_alpha, d_beta, tnorm, omega,
                                st, stopped);
-            pass(j + 1, w, false, &st->skip_pro, pn0);
+            pass(j + 1, w, false, &st->skip_pro, pn0, false);
         }
         hipLaunchKernelGGL(k_next, gv, tb, 0, s, D, w, pn, nb, j, j == m - 1 ? 1 : 0, d_alpha, d_beta, tnorm,
                            c32 ? x32 : nullptr, st, halt);

@@ -50,6 +50,33 @@ __device__ __forceinline__ void wave_tree(double (&v)[NV]) {
     for (int k = 0; k < NV; ++k) v[k] += dpp_move<0xB1, 0xf>(v[k]);   // quad_perm [1, 0, 3, 2]
 }
 
+// The same sums (distances 32, 16, 8, 4, 2, 1) for many values, NV a multiple of 16: the lanes share them out as the
+// distances halve, so that NV moves do what wave_tree does with 6 NV.  v[j], j < NV / 16, ends as value
+// wave_share(lane, NV) + j, the same in the four lanes of a quad.
+__device__ __forceinline__ int wave_share(int lane, int nv) {
+    return (lane >> 5 & 1) * (nv / 2) + (lane >> 4 & 1) * (nv / 4) + (lane >> 3 & 1) * (nv / 8) + (lane >> 2 & 1) * (nv / 16);
+}
+
+template <int NV>
+__device__ __forceinline__ void wave_tree_shared(double (&v)[NV], int lane) {
+    static_assert(NV % 16 == 0, "halved four times");
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        const int d = 32 >> l, n = NV >> (l + 1);
+        const bool up = (lane & d) != 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const double give = up ? v[k] : v[n + k], keep = up ? v[n + k] : v[k];
+            v[k] = keep + (d == 8 ? dpp_move<0x128, 0xf>(give) : __shfl_xor(give, d, 64));  // row_ror:8
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NV / 16; ++k) {
+        v[k] += dpp_move<0x4E, 0xf>(v[k]);  // quad_perm [2, 3, 0, 1]
+        v[k] += dpp_move<0xB1, 0xf>(v[k]);  // quad_perm [1, 0, 3, 2]
+    }
+}
+
 // Sums v over the block (the waves' trees, then in wave order); the result is valid in thread 0.  `lds` must hold
 // NV * (blockDim / 64) doubles.
 template <int NV>
