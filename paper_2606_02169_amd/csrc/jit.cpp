@@ -1838,6 +1838,7 @@ bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
     const double wT = f32 ? 0.1 : 0.05, wR = f32 ? 0.1 : 0.02, wE = f32 ? 1.0 : 0.5, wN = f32 ? 0.3 : 1.0;
     const double R0 = f32 ? 6144.0 : 4096.0;
     double best = -1e30;
+    int64_t best_T = 0;  // of equal tiles the one with more inner rows (spins 3/2, 10^6 rows: 18.9 -> 16.2 us)
     int64_t T = 1;
     for (int k = N - 1; k >= 0; --k) {
         T *= p->d[k];
@@ -1852,7 +1853,8 @@ bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
             const double R = double(T * PU * (top ? p->d[0] : 1)), tiles = double(p->D) / R;
             const double score = wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
                                  wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
-            if (score <= best) continue;
+            if (score < best - 1e-9 || (score <= best + 1e-9 && T == best_T)) continue;
+            best_T = T;
             best = score;
             tl->k_in = k;
             tl->k_u = k - u;

@@ -458,9 +458,10 @@ std::string WinGen::source() {
         tile_off << "    const " << type << " " << n << " = " << e << ";\n";
         return tile_regs[e] = n;
     };
-    auto excludes = [&](const DevChan& x, const DevChan& y) {  // no digits of their (uniform or inner) sites admit both
+    auto both = [&](const DevChan& x, const DevChan& y) {  // share of the digits of their (uniform or inner) sites that admit both
         const int sa = x.a, sb = x.b;
         const int da = p->d[sa], db = sb >= 0 ? p->d[sb] : 1;
+        int n = 0;
         for (int i = 0; i < da; ++i)
             for (int k = 0; k < db; ++k) {
                 auto on = [&](const DevChan& c) {
@@ -469,13 +470,18 @@ std::string WinGen::source() {
                             return false;
                     return true;
                 };
-                if (on(x) && on(y)) return false;
+                if (on(x) && on(y)) ++n;
             }
-        return true;
+        return double(n) / double(da * db);
     };
+    // The second gather of a pair gets a branch where at most this share of the digits admits both: two spins 1 (1/9), whose
+    // branch is mostly skipped (4 x 4 lattice 1.33 ms either way).  Above it a masked load for every lane costs less than
+    // the waits around a branch that is often taken: ring of 12 spins 3/2 (1/4) 434 -> 301 us, chain 328 -> 284 us,
+    // chain of 13 spins 1 and 3/2 363 -> 337 us, in c64 222 -> 195 us.
+    constexpr double kRareShare = 0.125;
     int64_t span = 0;  // largest lane offset of a row in its copy
     for (int i = w.n_uni + w.n_unr; i < N; ++i) span += (P.d[w.ord[i]] - 1) * P.M[w.ord[i]];
-    std::map<std::pair<int, int>, bool> excludes_at;
+    std::map<std::pair<int, int>, double> both_at;
     for (int64_t j = 0; j < PU; ++j) {
         std::vector<char> used(glob[j].size(), 0);
         for (size_t i = 0; i < glob[j].size(); ++i) {
@@ -490,10 +496,11 @@ std::string WinGen::source() {
                 const bool scalar = g.lf < 0 && h.lf < 0;  // no inner site
                 if (g.coef != h.coef && !scalar) continue;
                 const auto key = std::make_pair(g.chan, h.chan);
-                auto it = excludes_at.find(key);
-                if (it == excludes_at.end()) it = excludes_at.emplace(key, excludes(x, y)).first;
-                if (!it->second && !(scalar && !g.cond.empty() && !h.cond.empty())) continue;
-                if (it->second ? false : g.cond == h.cond) continue;
+                auto it = both_at.find(key);
+                if (it == both_at.end()) it = both_at.emplace(key, both(x, y)).first;
+                const double share = it->second;
+                if (share > 0.0 && !(scalar && !g.cond.empty() && !h.cond.empty())) continue;
+                if (share > 0.0 && g.cond == h.cond) continue;
                 if (g.delta < h.delta) std::swap(g, h);  // the other offset is ahead of the base: never negative
                 if ((g.delta - h.delta + span) * SZ >= (int64_t(1) << 31)) break;
                 auto on = [&](const Glob& q) {
@@ -510,13 +517,13 @@ std::string WinGen::source() {
                 l.off = tile_reg("unsigned", "o", "(" + og + ") ? voff : (" + oh + ") ? voff + " + ahead + " : OOB");
                 l.coef = g.coef == h.coef ? g.coef : tile_reg("R", "c", "(" + og + ") ? " + g.coef + " : " + h.coef);
                 load[j].push_back(l);
-                if (!it->second) {  // both: the second one of the pair
+                if (share > 0.0) {  // both: the second one of the pair
                     Load r;
                     r.delta = h.delta;
                     r.off = "voff";
                     r.coef = h.coef;
                     r.branch = g.cond + " && " + h.cond;
-                    if (!w.rare_branch) {
+                    if (share > kRareShare) {
                         r.off = tile_reg("unsigned", "o", "(" + r.branch + ") ? voff : OOB");
                         r.branch.clear();
                     }

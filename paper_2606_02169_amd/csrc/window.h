@@ -27,7 +27,6 @@ struct WindowPass {
     int waves = 0;        // > 0: ask the compiler for at least this many waves per SIMD
     int64_t dbuf_bytes = 49152;  // the staged rows are double-buffered while that takes no more LDS than this
     bool prefetch = true;  // the rows of the next super-tile are requested while the current one is computed
-    bool rare_branch = true;  // the second gather of a pair (both channels admitted) sits in a branch
     bool keep_y = false;  // y is stored with the default cache policy (a later pass reads it), else non-temporal
     std::string name, tag;  // kernel name; suffix of the pass's constants
 };

@@ -30,6 +30,7 @@ def diagonal_only():
 MODELS = {
     "spin half ring": lambda: W.configs.staggered_xxz_ring([1] * 8),
     "spin 1 ring": lambda: W.configs.staggered_xxz_ring([2] * 6),          # both channels of a bond admitted at once
+    "spins 1 and 3/2 above the tile": lambda: W.configs.open_xxz_chain([3, 3, 2, 2, 1, 2, 3, 2], np.ones(7), np.full(7, 0.7)),
     "spin 3/2 chain": lambda: W.configs.open_xxz_chain([3, 1, 3, 2, 3], np.ones(4), np.full(4, 0.7)),  # factor tables
     "ferrimagnet": lambda: W.ferrimagnetic_ring(8),
     "square": lambda: W.square_lattice_spin1(2, np.random.default_rng(3)),  # double bonds
