@@ -486,22 +486,23 @@ std::string WinGen::source() {
         std::vector<char> used(glob[j].size(), 0);
         for (size_t i = 0; i < glob[j].size(); ++i) {
             if (used[i]) continue;
-            Glob g = glob[j][i];
+            const Glob& one = glob[j][i];
             bool paired = false;
             for (size_t k = i + 1; k < glob[j].size() && !paired; ++k) {
-                Glob h = glob[j][k];
-                if (used[k] || h.delta == g.delta) continue;
-                const DevChan &x = P.chans[g.chan], &y = P.chans[h.chan];
+                const Glob& two = glob[j][k];
+                if (used[k] || two.delta == one.delta) continue;
+                const DevChan &x = P.chans[one.chan], &y = P.chans[two.chan];
                 if (!((x.a == y.a && x.b == y.b) || (x.a == y.b && x.b == y.a))) continue;
-                const bool scalar = g.lf < 0 && h.lf < 0;  // no inner site
-                if (g.coef != h.coef && !scalar) continue;
-                const auto key = std::make_pair(g.chan, h.chan);
+                const bool scalar = one.lf < 0 && two.lf < 0;  // no inner site
+                if (one.coef != two.coef && !scalar) continue;
+                const auto key = std::make_pair(one.chan, two.chan);
                 auto it = both_at.find(key);
                 if (it == both_at.end()) it = both_at.emplace(key, both(x, y)).first;
                 const double share = it->second;
-                if (share > 0.0 && !(scalar && !g.cond.empty() && !h.cond.empty())) continue;
-                if (share > 0.0 && g.cond == h.cond) continue;
-                if (g.delta < h.delta) std::swap(g, h);  // the other offset is ahead of the base: never negative
+                if (share > 0.0 && !(scalar && !one.cond.empty() && !two.cond.empty())) continue;
+                if (share > 0.0 && one.cond == two.cond) continue;
+                // h's rows are ahead of the gather's base, which is g's: never negative
+                const Glob &g = one.delta > two.delta ? one : two, &h = one.delta > two.delta ? two : one;
                 if ((g.delta - h.delta + span) * SZ >= (int64_t(1) << 31)) break;
                 auto on = [&](const Glob& q) {
                     std::string e = q.cond;
@@ -534,10 +535,11 @@ std::string WinGen::source() {
             }
             if (paired) continue;
             Load l;
-            l.delta = g.delta;
-            l.coef = g.coef;
-            const std::string lane_off = g.lf < 0 || !lanes[g.lf].masked ? "voff" : reg("unsigned", "vo", mask(g.lf) + " ? voff : OOB");
-            l.off = g.cond.empty() ? lane_off : tile_reg("unsigned", "o", "(" + g.cond + ") ? " + lane_off + " : OOB");
+            l.delta = one.delta;
+            l.coef = one.coef;
+            const std::string lane_off =
+                one.lf < 0 || !lanes[one.lf].masked ? "voff" : reg("unsigned", "vo", mask(one.lf) + " ? voff : OOB");
+            l.off = one.cond.empty() ? lane_off : tile_reg("unsigned", "o", "(" + one.cond + ") ? " + lane_off + " : OOB");
             load[j].push_back(l);
         }
         // the gathers in branches of their own last

@@ -2,6 +2,8 @@
 of the uniform digits, site orders of the second pass, blocks with a ragged last wave, plans with one pass, two passes or
 no uniform site.  On the CPU through the emulator (every buffer access checked to lie inside its buffer), on the GPU
 through the library; c128 to 1e-12, c64 to 2e-5 of the oracle."""
+import re
+
 import numpy as np
 import pytest
 
@@ -93,6 +95,49 @@ def test_chosen_by_rule():
     assert "window form" not in E.kernel_source(cplx, L.MRMF_DTYPE_Z, tuning={"variant": 2})
 
 
+def swapped_chain(n):
+    """Open chain of spins 1/2 whose bonds list the lowering of their first site first."""
+    terms = []
+    for i in range(n - 1):
+        terms += [W.Term(i, W.OP_LOWER, i + 1, W.OP_RAISE, 0, 0.5), W.Term(i, W.OP_RAISE, i + 1, W.OP_LOWER, 0, 0.5)]
+    return W.Model([W.spin_site(1)] * n, terms, np.array([0.9]))
+
+
+# Bonds whose two channels read 2^31 bytes or more apart: no 32-bit lane offset reaches both, so neither can share the
+# other's gather.  At 27 spins of c128 (28 of c64) for a closing bond, one site more for the first bond of a chain.
+FAR_PAIRS = {"ring 27 c128": (lambda: W.heisenberg_chain(27, periodic=True), L.MRMF_DTYPE_Z, (7, 3)),
+             "ring 28 c64": (lambda: W.heisenberg_chain(28, periodic=True), L.MRMF_DTYPE_C, (0, -1)),
+             "ferrimagnet 22 c64": (lambda: W.ferrimagnetic_ring(22), L.MRMF_DTYPE_C, (0, -1)),
+             "lower first 28 c128": (lambda: swapped_chain(28), L.MRMF_DTYPE_Z, (0, -1))}
+
+
+@pytest.mark.parametrize("name", list(FAR_PAIRS))
+def test_far_pairs_read_each_channel_once(name):
+    """No two gathers of a copy read the same rows (the channels of these lattices have offsets of their own)."""
+    model, dtype, shape = FAR_PAIRS[name]
+    src = E.kernel_source(model(), dtype, *shape, tuning={"variant": L.MRMF_VARIANT_WINDOW})
+    assert "window form" in src
+    at = {}
+    for copy, base in re.findall(r"const C s(\d+)_\d+ = LD\(xs, \w+, F0 \+ \(unsigned long long\)\((-?\d+)ll\)\)", src):
+        at.setdefault(copy, []).append(int(base))
+    assert at
+    for copy, bases in at.items():
+        assert len(set(bases)) == len(bases), (copy, sorted(bases))
+
+
+def test_far_pairs_emulated():
+    """Rows of the ring of 27 spins 1/2 (2 GiB) whose closing bond is gathered, against the oracle: super-tiles all over
+    the vector, site 0 up and down."""
+    model, _, (inner, unrolled) = FAR_PAIRS["ring 27 c128"]
+    m = model()
+    x = np.resize(W.random_state(1000003, np.random.default_rng(12)), m.dim)
+    tiles = m.dim >> (inner + unrolled)
+    y = E.run(m, x, inner=inner, unrolled=unrolled, grid=tiles, tuning={"variant": L.MRMF_VARIANT_WINDOW}, blocks=(0, 8))
+    rows = np.flatnonzero(~np.isnan(y.real))
+    assert rows.size == 8 << (inner + unrolled) and rows[-1] >= m.dim // 2
+    assert rel_err(y[rows], mf.matvec(m, x, rows=rows)) <= 1e-12
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(MODELS))
 def test_gpu(name):
@@ -130,3 +175,27 @@ def test_gpu_two_passes_of_the_square_lattice():
     rows = np.unique(np.random.default_rng(2).choice(m.dim, 2000, replace=False)).astype(np.int64)
     ref = mf.matvec(m, x.cpu().numpy(), rows=rows)
     assert rel_err(y2[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= 1e-12
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(FAR_PAIRS))
+def test_gpu_far_pairs(name):
+    """The whole vector against the generic kernel's; a row sums at most 2 x 28 products, so 1e-14 (c128) and 1e-5 (c64)
+    of the largest entry leave room for two orders of the roundings."""
+    import torch
+
+    from paper_2606_02169_amd.plan import Plan
+    model, dtype, (inner, unrolled) = FAR_PAIRS[name]
+    m = model()
+    real = torch.float32 if dtype == L.MRMF_DTYPE_C else torch.float64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.view_as_complex(torch.randn((m.dim, 2), dtype=real, device="cuda", generator=g))
+    th = torch.as_tensor(m.theta, dtype=real, device="cuda")
+    win, gen = Plan.from_model(m), Plan.from_model(m)
+    win.set_kernel("specialized", inner_sites=inner, unrolled_sites=unrolled)
+    gen.set_kernel("generic")
+    assert "window form" in win.kernel_source(x.dtype)
+    a, b = win.matvec(th, x), gen.matvec(th, x)
+    scale = float(torch.view_as_real(b).abs().max())
+    worst = max(float(torch.view_as_real(u - v).abs().max()) for u, v in zip(a.split(1 << 26), b.split(1 << 26)))
+    assert worst <= (1e-5 if real == torch.float32 else 1e-14) * scale
