@@ -1850,6 +1850,8 @@ bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
             bool wrap = false;
             for (const auto& c : p->chans) wrap |= (c.a == 0 && c.b >= k - u) || (c.b == 0 && c.a >= k - u);
             const int top = !f32 && p->D >= 1000000 && wrap && k - u > 1 && PU * p->d[0] <= 16 ? 1 : 0;
+            // its rows (with a zero row each copy) and the largest tables have to fit in LDS
+            if ((T + 1) * PU * (top ? p->d[0] : 1) * (f32 ? 8 : 16) + kWindowTab * (f32 ? 4 : 8) > kWindowLds) continue;
             const double R = double(T * PU * (top ? p->d[0] : 1)), tiles = double(p->D) / R;
             const double score = wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
                                  wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
@@ -1987,7 +1989,7 @@ int lanczos_slot(const mrmf_plan_t* p, int dtype) {
     return window_real(p) && window_by_rule(p->cfg[dtype]) ? kSlotLanczos + dtype : dtype;
 }
 
-std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom* geo, bool epi, bool lanczos) {
+std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom* geo, bool epi, bool masked) {
     const bool f32 = dtype == MRMF_DTYPE_C;
     const int64_t SZ = f32 ? 8 : 16, lim = int64_t(1) << 31;
     const KernelCfg& cfg = p->cfg[epi && p->cheb_shape_set ? kSlotCheb : f32 ? MRMF_DTYPE_C : MRMF_DTYPE_Z];
@@ -2001,9 +2003,9 @@ std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom*
     // 32-bit signed scalar
     auto is_wide = [&](const Tile& t) { return cfg.wide != 0 || (p->D + dmax - dmin + 2 * t.T_in) * SZ >= lim; };
     Tile tl;
-    // The window form unless another one, or a knob that only the others have, was asked for; a plan that does not fit
-    // it (tables of the uniform digits beyond LDS, complex weights) takes the masked one.
-    if (!lanczos && window_real(p) && (cfg.variant == MRMF_VARIANT_WINDOW || window_by_rule(cfg))) {
+    // The window form unless another one, or a knob that only the others have, was asked for; a plan or a tile that does
+    // not fit it (rows or tables of the uniform digits beyond LDS, complex weights) takes the masked one.
+    if (!masked && window_real(p) && (cfg.variant == MRMF_VARIANT_WINDOW || window_by_rule(cfg))) {
         const bool rule = cfg.inner == 0 && cfg.unroll < 0 && cfg.unroll_top == 0;
         std::vector<WindowPass> passes;
         if ((rule ? window_tile(p, f32, &tl) : choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) &&
@@ -2019,6 +2021,7 @@ std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom*
             }
             if (!src.empty()) {
                 geo->n = static_cast<int>(passes.size());
+                geo->window = true;
                 *tl_out = tl;
                 return src;
             }
@@ -2044,6 +2047,7 @@ std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom*
     gen.variant = cfg.variant;
     *tl_out = tl;
     geo->n = 1;
+    geo->window = false;
     geo->tiles[0] = n_st;
     geo->block[0] = gen.block;
     if (gen.variant != MRMF_VARIANT_LIST && gen.masked_fits()) return gen.source();
@@ -2142,13 +2146,6 @@ mrmf_status compile_spec(mrmf_plan_t* p, int slot, SpecKernel& K) {
     K.tried = true;
     K.ok = false;
     const int dtype = slot == kSlotCheb ? MRMF_DTYPE_Z : slot >= kSlotLanczos ? slot - kSlotLanczos : slot;
-    Tile tl;
-    SpecGeom geo;
-    const std::string src = spec_source(p, dtype, &tl, &geo, slot == kSlotCheb, slot >= kSlotLanczos);
-    if (src.empty()) {
-        K.log = "plan does not qualify for the specialized kernel";
-        return MRMF_E_UNSUPPORTED;
-    }
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return MRMF_E_HIP;
     hipDeviceProp_t prop;
@@ -2157,8 +2154,20 @@ mrmf_status compile_spec(mrmf_plan_t* p, int slot, SpecKernel& K) {
     hipFunction_t fn;
     hipFunction_t fn2 = nullptr;
     const bool cheb = slot == kSlotCheb;
-    const mrmf_status bs = rtc_build(src, cheb ? "mrmf_spec_cheb" : "mrmf_spec", prop, &mod, &fn, &K.log,
-                                     geo.n > 1 ? (cheb ? "mrmf_spec_cheb_b" : "mrmf_spec_b") : nullptr, &fn2);
+    Tile tl;
+    SpecGeom geo;
+    std::string src;
+    auto build = [&](bool masked) {
+        src = spec_source(p, dtype, &tl, &geo, cheb, masked);
+        if (src.empty()) {
+            K.log = "plan does not qualify for the specialized kernel";
+            return MRMF_E_UNSUPPORTED;
+        }
+        return rtc_build(src, cheb ? "mrmf_spec_cheb" : "mrmf_spec", prop, &mod, &fn, &K.log,
+                         geo.n > 1 ? (cheb ? "mrmf_spec_cheb_b" : "mrmf_spec_b") : nullptr, &fn2);
+    };
+    mrmf_status bs = build(slot >= kSlotLanczos);
+    if (bs == MRMF_E_UNSUPPORTED && geo.window) bs = build(true);  // the window form's source was refused
     if (bs != MRMF_OK) return bs;
     const int bpc = p->cfg[cheb && p->cheb_shape_set ? kSlotCheb : dtype].blocks_per_cu;
     for (int i = 0; i < geo.n; ++i) {

@@ -283,13 +283,14 @@ mrmf_status propagate_run(int64_t n, int32_t n_params, const ThetaMatvecOp& mv, 
                           const void* d_x0, void* d_x, void* d_scratch, size_t scratch_bytes, int32_t* h_n_terms,
                           hipStream_t s);
 // Generated source of the specialized kernel (no device needed) and its launches' block size and super-tiles;
-// "" when the plan does not qualify.
+// "" when the plan does not qualify.  masked: never the window form.
 struct SpecGeom {
     int n = 1;
+    bool window = false;  // the window form
     int block[2] = {0, 0};
     int64_t tiles[2] = {0, 0};
 };
-std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl, SpecGeom* geo, bool epi = false, bool lanczos = false);
+std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl, SpecGeom* geo, bool epi = false, bool masked = false);
 // slot of the kernel that Lanczos launches for a dtype: its own (kSlotLanczos + dtype) or the plan's
 int lanczos_slot(const mrmf_plan_t* p, int dtype);
 // Fused Chebyshev step (time propagation) with the specialized c128 kernel:

@@ -32,7 +32,6 @@
 namespace mrmf {
 namespace {
 
-constexpr size_t kTabMax = 1024;   // entries of the uniform digits' tables in LDS
 constexpr int kPairMax = 256;      // largest d_a d_b tabulated for a pair of uniform sites
 
 struct WinGen {
@@ -230,7 +229,7 @@ struct WinGen {
     bool too_big = false;
     int new_tab(int a, int b) {
         const size_t n = size_t(p->d[a]) * (b >= 0 ? p->d[b] : 1);
-        if (entries.size() + n > kTabMax) {
+        if (entries.size() + n > size_t(kWindowTab)) {
             too_big = true;
             return -1;
         }
@@ -658,6 +657,7 @@ std::string WinGen::source() {
     std::ostringstream body;
     const bool use_lds = any_static || need_x;
     const bool dbuf = use_lds && 2 * PU * CS * SZ <= w.dbuf_bytes;
+    if ((use_lds ? (dbuf ? 2 : 1) * PU * CS * SZ : 0) + int64_t(ne) * (f32 ? 4 : 8) > kWindowLds) return "";
     body << "extern \"C\" __global__ __launch_bounds__(" << block << ") ";
     if (w.waves > 0) body << "__attribute__((amdgpu_waves_per_eu(" << w.waves << "))) ";
     body << "void " << w.name << "(const R* __restrict__ theta,\n    const C* __restrict__ x, C* __restrict__ y, ";

@@ -9,6 +9,9 @@
 
 namespace mrmf {
 
+constexpr int64_t kWindowLds = 163840;  // LDS of a compute unit: the staged rows and the tables of the uniform digits
+constexpr int kWindowTab = 1024;        // most entries of those tables
+
 // What a pass does with the rows it computes (H': the pass's terms).
 constexpr int kPassSet = 0;       // y = H' x
 constexpr int kPassAdd = 1;       // y += H' x
@@ -34,7 +37,8 @@ struct WindowPass {
 // true when every term weight is real (the form has no complex coefficients)
 bool window_real(const mrmf_plan_t* p);
 std::string window_prelude(bool f32, bool wide);
-// Source of one pass (after window_prelude, which several passes share); "" when the plan does not fit the form.
+// Source of one pass (after window_prelude, which several passes share); "" when the plan or its tile does not fit the
+// form (tables, LDS).
 std::string window_pass(const mrmf_plan_t* p, const WindowPass& w, int64_t* n_tiles, int64_t* rows);
 
 }  // namespace mrmf

@@ -138,6 +138,67 @@ def test_far_pairs_emulated():
     assert rel_err(y[rows], mf.matvec(m, x, rows=rows)) <= 1e-12
 
 
+def lds_bytes(src):
+    """LDS of each pass: the staged rows and the tables of the uniform digits."""
+    f32 = "typedef float R" in src
+    one = {"C": 8 if f32 else 16, "R": 4 if f32 else 8}
+    return [sum(one[t] * int(n) for t, n in re.findall(r"__shared__ (C|R) \w+\[(\d+)\]", body))
+            for body in src.split("extern \"C\" __global__")[1:]]
+
+
+# lattices whose large sites leave tiles of many rows only: (lattice, default tile beyond the 160 KB of LDS in c128)
+LARGE_SITES = {
+    "16 and 250 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(15), W.boson_site(249), W.spin_site(2)]),
+    "12 and 256 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(11), W.boson_site(255), W.spin_site(3)]),
+    "15 and 200 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(14), W.boson_site(199), W.spin_site(3)]),
+}
+
+
+def chain_of(sites):
+    """Open chain with one exchange coupling per bond."""
+    terms = []
+    for i in range(len(sites) - 1):
+        terms += [W.Term(i, W.OP_RAISE, i + 1, W.OP_LOWER, i, 0.5), W.Term(i, W.OP_LOWER, i + 1, W.OP_RAISE, i, 0.5),
+                  W.Term(i, W.OP_Z, i + 1, W.OP_Z, i, 1.0)]
+    return W.Model(sites, terms, np.linspace(0.6, 1.2, len(sites) - 1))
+
+
+@pytest.mark.parametrize("name", list(LARGE_SITES))
+@pytest.mark.parametrize("dtype", [L.MRMF_DTYPE_Z, L.MRMF_DTYPE_C, L.MRMF_SOURCE_CHEB])
+def test_tile_by_rule_fits_in_lds(name, dtype):
+    src = E.kernel_source(LARGE_SITES[name](), dtype)
+    assert "window form" in src
+    assert max(lds_bytes(src)) <= 163840
+
+
+def test_tile_beyond_lds_takes_the_masked_form():
+    """A shape asked for whose rows do not fit in LDS: the masked form, as for any plan that the window form does not take."""
+    m = LARGE_SITES["16 and 250 levels"]()
+    for tuning in ({}, {"variant": L.MRMF_VARIANT_WINDOW}):
+        src = E.kernel_source(m, L.MRMF_DTYPE_Z, inner=2, unrolled=1, tuning=tuning)
+        assert src is not None and "window form" not in src
+    assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z, inner=2, unrolled=0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(LARGE_SITES))
+def test_gpu_large_sites(name):
+    """The default kernel of these plans is a specialized one, and its rows are the oracle's."""
+    import torch
+
+    from paper_2606_02169_amd.plan import Plan
+    m = LARGE_SITES[name]()
+    rows = np.unique(np.random.default_rng(2).integers(0, m.dim, 2000))
+    for dtype, tdt in ((np.complex128, torch.float64), (np.complex64, torch.float32)):
+        x = np.resize(W.random_state(1000003, np.random.default_rng(12)), m.dim).astype(dtype)
+        p = Plan.from_model(m)
+        p.set_kernel("specialized")
+        y = p.matvec(torch.as_tensor(m.theta, dtype=tdt, device="cuda"), torch.from_numpy(x).cuda())
+        assert p.kernel_info(y.dtype)["kind"] == "specialized"
+        ref = mf.matvec(m, x.astype(np.complex128), rows=rows)
+        assert rel_err(y[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= TOL[dtype]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(MODELS))
 def test_gpu(name):
