@@ -310,6 +310,8 @@ class Plan:
         arch = torch.cuda.get_device_properties(self.device).gcnArchName.split(":")[0]
         key = tuning.signature(self._sites, self._terms, dt, arch, self._local)
         ent = tuning.lookup(key) if use_cache else None
+        if ent is not None and ent["variant"] == L.MRMF_VARIANT_WINDOW and not tuning.real_weights(self._terms):
+            ent = None   # a cache written when the key did not tell real weights from complex ones
         if ent is None:
             y = torch.empty_like(x) if y is None else y
             _need_gpu(x, "x")

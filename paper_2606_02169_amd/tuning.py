@@ -2,8 +2,9 @@
 
 mrmf_plan_autotune (C ABI) times every candidate shape of the specialized kernel on real buffers and
 keeps the fastest in the plan.  This module remembers the winners in a JSON file keyed by the plan's
-structure (site dimensions and the operator pattern of every term), the element type and the GPU
-architecture, so that later plans with the same structure skip the search.  The cache path is
+structure (site dimensions and the operator pattern of every term), the element type, the GPU
+architecture and the kernel forms that the plan can take, so that later plans with the same structure
+skip the search.  The cache path is
 $MRMF_TUNE_CACHE, else ~/.cache/mrmf/tuning.json; entries measured on MI355X ship with the package in
 tuned_gfx950.json and are consulted after the user cache.
 """
@@ -22,11 +23,24 @@ def cache_path() -> str:
                                                               "tuning.json")
 
 
+# Forms that the generator has for plans with real weights, in their keys: a shape found before the window form came
+# is slower than what an untuned plan takes, so it is not found again.  Complex weights have the masked and the list form
+# alone, and keys without this mark: a shape of a real plan (window form, copies for it) spills hundreds of registers
+# in theirs.
+REAL_FORMS = "window"
+
+
+def real_weights(terms) -> bool:
+    return all(complex(t.w if hasattr(t, "site_a") else t[5]).imag == 0.0 for t in terms)
+
+
 def signature(sites, terms, dtype_code: int, arch: str, local_ops=()) -> str:
     """Key of a plan structure: site kinds and dimensions, each term's sites and operators (couplings and
-    weights do not change the kernel's shape), the (site, shift) of general one-site operators, the
-    element type and the architecture."""
+    weights do not change the kernel's shape, but whether the weights are real does), the (site, shift) of general
+    one-site operators, the element type and the architecture."""
     parts = [arch, str(int(dtype_code))]
+    if real_weights(terms):
+        parts.append(REAL_FORMS)
     for site, shift in local_ops:
         parts.append(f"l{int(site)}:{int(shift)}")
     for s in sites:
