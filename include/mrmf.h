@@ -186,9 +186,10 @@ mrmf_status mrmf_plan_set_kernel(mrmf_plan plan, int32_t kind, int32_t inner_sit
  *                                                   swept in an order of the library's (real term weights only;
  *                                                   MRMF_TUNE_LOAD_GROUP = gathers in flight).
  *                             Until one is set, the window form where the weights are real and none of
- *                             MRMF_TUNE_BRANCH_SKIP, MRMF_TUNE_FAR_LOADS and MRMF_TUNE_OUTER_FIRST is, else the masked
- *                             form (which a plan that the window form does not take runs as well); mrmf_lanczos keeps
- *                             the masked form until one is set.
+ *                             MRMF_TUNE_BRANCH_SKIP, MRMF_TUNE_FAR_LOADS and MRMF_TUNE_OUTER_FIRST is, unless the library's
+ *                             rule finds the plan's terms too many or too varied for it; else the masked form (which a plan
+ *                             that the window form does not take runs as well).  mrmf_lanczos keeps the masked form until
+ *                             one is set.
  *   MRMF_TUNE_FAR_PASS      : window form: channels whose offset |Delta| spans at least 2^k bytes (k in 10..40) are
  *                             applied by a second launch that sweeps their sites as neighbours; 0 = the library's
  *                             rule (default), 1 = never.
@@ -256,8 +257,9 @@ mrmf_status mrmf_plan_set_tuning(mrmf_plan plan, int32_t knob, int32_t value);
 mrmf_status mrmf_plan_set_shape(mrmf_plan plan, int32_t dtype, int32_t variant, int32_t inner_sites,
                                 int32_t unrolled_sites, int32_t load_group, int32_t unroll_top);
 /* Autotuner for the plain matvec: times every candidate shape of the specialized kernel (inner block of
- * 32..1024 rows; masked form with 0..2 unrolled sites, window form with 0..4, or for complex weights list form with
- * chunk 4/8/12; where a term joins site 0 to the unrolled/inner sites, also with sites 0 and 0..1 unrolled,
+ * 32..1024 rows; masked form with 0..2 unrolled sites; window form with 0..4; for complex weights, or more than
+ * 128 off-diagonal terms, list form with chunk 4/8/12; where a term joins site 0 to the unrolled/inner sites,
+ * also with sites 0 and 0..1 unrolled,
  * MRMF_TUNE_UNROLL_TOP) on the given buffers with HIP events on the stream (synchronising it),
  * keeps the fastest in the plan for this element type only (selection MRMF_KERNEL_AUTO) and writes host
  * out[0..5] = (variant, inner sites, unrolled sites, load group, microseconds per call, top sites

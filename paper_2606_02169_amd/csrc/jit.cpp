@@ -1826,6 +1826,31 @@ double admitted_share(const mrmf_plan_t* p, const DevChan& c) {
     return f;
 }
 
+// One pass or two.  An XCD that sweeps the rows in order keeps the last rows it read in its 4 MB L2, so a channel whose
+// source lies within kFarBytes of its row finds it there, from either side; every other ("far") channel reads its
+// share of x from memory once more.  In units of one vector, a single pass moves 2 + the far channels' shares.  A
+// second pass that applies the far channels alone, in an order where their sites are neighbours, makes it 5 (x, y and
+// y again on top of the first pass's two), but its short runs of rows stream at 4.6 TB/s where a single pass moves
+// 7.3, so it pays from about 9 units on: 4 x 4 spin-1 lattice (12 far bonds, 12.7 units) 1765 -> 1205 us in c128 and
+// 835 -> 756 us in c64; 20-site ring (7 far bonds, 6.7 units) 1014 -> 1117 us, open chain of 25 spins 1/2 (5 units)
+// 526 -> 626 us.
+constexpr int64_t kFarBytes = 3 << 19;
+bool is_far(const DevChan& c, const KernelCfg& cfg, bool f32) {
+    const int64_t far = cfg.far_pass >= 10 ? int64_t(1) << cfg.far_pass : kFarBytes;
+    return std::llabs(c.delta) * (f32 ? 8 : 16) >= far;
+}
+bool two_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32) {
+    if (cfg.far_pass == 1) return false;
+    double u1 = 2.0;
+    int n = 0;
+    for (const auto& c : p->chans)
+        if (is_far(c, cfg, f32)) {
+            u1 += admitted_share(p, c);
+            ++n;
+        }
+    return n > 0 && (cfg.far_pass != 0 || u1 > 1.8 * 5.0);
+}
+
 // Tile of the window form.  Fitted to the times of every tile on 70 random chains, rings and spin-boson lattices of
 // 10^3 to 4 x 10^7 rows: about 768 super-tiles or more (three for each CU; fewer leave CUs idle at the end of the
 // sweep), then super-tiles of a few thousand rows (more of the bonds in LDS, fewer barriers and scalar set-ups a row)
@@ -1833,10 +1858,32 @@ double admitted_share(const mrmf_plan_t* p, const DevChan& c) {
 // lattice's best, 1.27 and 1.24 times faster than the masked form's on average.  Site 0 joins the unrolled ones from
 // 10^6 c128 rows on where a channel joins it to the tile (a ring's closing bond: 18 sites 146 -> 140 us); in c64 and
 // below that it cost as much as it gave.
-bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
+//
+// Of the tiles with several copies, those whose copies gather at no more than kWindowGathers places in all in the first
+// pass (half the global channels a copy: the two of a bond exclude each other).  Beyond that the kernel only gets longer:
+// couplings of all pairs of 22 spins 1/2 in c128, 16 copies 569 us and 3.1 s to compile, 8 589 us and 2.1 s, 4 514 us and
+// 1.4 s; of 24 spins 3162, 3011 and 2673 us; but 22 spins of range 6 170, 214 and 239 us, where 16 copies gather less
+// often than 4 of those.  A c64 value takes half the registers: all pairs of 22 spins 344, 355 and 397 us.
+constexpr double kWindowGathers[2] = {720.0, 1440.0};  // c128, c64
+double window_gathers(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool two, const Tile& t) {
+    auto uniform = [&](int s) { return s >= t.n_top && s < t.k_u; };
+    int n = 0;
+    for (const auto& c : p->chans) n += (uniform(c.a) || uniform(c.b)) && !(two && is_far(c, cfg, f32));
+    return 0.5 * n * double(t.P_U);
+}
+
+// two: the plan takes two passes
+bool window_fits(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool two, const Tile& t) {
+    // its rows (with a zero row each copy) and the largest tables have to fit in LDS
+    if ((t.T_in + 1) * t.P_U * (f32 ? 8 : 16) + kWindowTab * (f32 ? 4 : 8) > kWindowLds) return false;
+    return t.P_U == 1 || window_gathers(p, cfg, f32, two, t) <= kWindowGathers[f32];
+}
+
+bool window_tile(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, Tile* tl) {
     const int N = p->N;
     const double wT = f32 ? 0.1 : 0.05, wR = f32 ? 0.1 : 0.02, wE = f32 ? 1.0 : 0.5, wN = f32 ? 0.3 : 1.0;
     const double R0 = f32 ? 6144.0 : 4096.0;
+    const bool two = two_passes(p, cfg, f32);
     double best = -1e30;
     int64_t best_T = 0;  // of equal tiles the one with more inner rows (spins 3/2, 10^6 rows: 18.9 -> 16.2 us)
     int64_t T = 1;
@@ -1850,36 +1897,27 @@ bool window_tile(const mrmf_plan_t* p, bool f32, Tile* tl) {
             bool wrap = false;
             for (const auto& c : p->chans) wrap |= (c.a == 0 && c.b >= k - u) || (c.b == 0 && c.a >= k - u);
             const int top = !f32 && p->D >= 1000000 && wrap && k - u > 1 && PU * p->d[0] <= 16 ? 1 : 0;
-            // its rows (with a zero row each copy) and the largest tables have to fit in LDS
-            if ((T + 1) * PU * (top ? p->d[0] : 1) * (f32 ? 8 : 16) + kWindowTab * (f32 ? 4 : 8) > kWindowLds) continue;
-            const double R = double(T * PU * (top ? p->d[0] : 1)), tiles = double(p->D) / R;
+            Tile t;
+            t.k_in = k;
+            t.k_u = k - u;
+            t.T_in = T;
+            t.P_C = PU;
+            t.n_top = top;
+            t.P_U = PU * (top ? p->d[0] : 1);
+            if (!window_fits(p, cfg, f32, two, t)) continue;
+            const double R = double(T * t.P_U), tiles = double(p->D) / R;
             const double score = wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
                                  wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
             if (score < best - 1e-9 || (score <= best + 1e-9 && T == best_T)) continue;
             best_T = T;
             best = score;
-            tl->k_in = k;
-            tl->k_u = k - u;
-            tl->T_in = T;
-            tl->P_C = PU;
-            tl->n_top = top;
-            tl->P_U = PU * (top ? p->d[0] : 1);
+            *tl = t;
         }
     }
     return best > -1e30;
 }
 
 // Passes of the window form for the tile tl.
-//
-// One pass or two.  An XCD that sweeps the rows in order keeps the last rows it read in its 4 MB L2, so a channel whose
-// source lies within kFarBytes of its row finds it there, from either side; every other ("far") channel reads its
-// share of x from memory once more.  In units of one vector, a single pass moves 2 + the far channels' shares.  A
-// second pass that applies the far channels alone, in an order where their sites are neighbours, makes it 5 (x, y and
-// y again on top of the first pass's two), but its short runs of rows stream at 4.6 TB/s where a single pass moves
-// 7.3, so it pays from about 9 units on: 4 x 4 spin-1 lattice (12 far bonds, 12.7 units) 1765 -> 1205 us in c128 and
-// 835 -> 756 us in c64; 20-site ring (7 far bonds, 6.7 units) 1014 -> 1117 us, open chain of 25 spins 1/2 (5 units)
-// 526 -> 626 us.
-constexpr int64_t kFarBytes = 3 << 19;
 void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool epi, const Tile& tl,
                    std::vector<WindowPass>* out) {
     const int64_t SZ = f32 ? 8 : 16;
@@ -1905,17 +1943,10 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
     w.n_unr = static_cast<int>(w.ord.size()) - w.n_uni;
     for (int s = tl.k_in; s < p->N; ++s) w.ord.push_back(s);
     for (size_t i = 0; i < p->diags.size(); ++i) w.diags.push_back(static_cast<int>(i));
-    const int64_t far = cfg.far_pass >= 10 ? int64_t(1) << cfg.far_pass : kFarBytes;
+    bool two = two_passes(p, cfg, f32);
     std::vector<int> near_c, far_c;
-    double u1 = 2.0;
-    for (size_t i = 0; i < p->chans.size(); ++i) {
-        const DevChan& c = p->chans[i];
-        const bool f = std::llabs(c.delta) * SZ >= far;
-        (f ? far_c : near_c).push_back(static_cast<int>(i));
-        if (f) u1 += admitted_share(p, c);
-    }
+    for (size_t i = 0; i < p->chans.size(); ++i) (is_far(p->chans[i], cfg, f32) ? far_c : near_c).push_back(static_cast<int>(i));
     WindowPass w2 = w;
-    bool two = !far_c.empty() && cfg.far_pass != 1;
     if (two) {
         // the far channels' sites, the ones with most of their channels innermost, under a run of the lowest sites of
         // at least 128 bytes (whole cache lines); the other sites outermost
@@ -1961,7 +1992,6 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
         int64_t span = 0;  // bytes from the first to the last row of a copy: a 32-bit lane offset
         for (int i = k_in; i < N; ++i) span += (p->d[w2.ord[i]] - 1) * p->M[w2.ord[i]] * SZ;
         two = T <= 1024 && span < (int64_t(1) << 31) - SZ;
-        if (cfg.far_pass == 0) two = two && u1 > 1.8 * 5.0;
     }
     w.chans = near_c;
     if (two) {
@@ -1977,6 +2007,28 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
 }  // namespace
 
 namespace {
+
+// Plans that the masked form (or the list form, which it gives way to) serves better, from the times of both on 127
+// lattices in c128 and c64: rings and squares of range 1 to 8, power laws, couplings of all pairs, one coupling for all
+// bonds or one a bond, spins 1/2 to 5/2 and modes of 4 to 8 levels, 10^3 to 5 x 10^7 rows.
+//  - One copy, so that a block does one or two super-tiles: what it works out before the first one counts.  From a set-up
+//    of 56 on (a coefficient and a varying gather 1 each, a round of table entries 8): 16 spins 1/2, range 4 and a
+//    coupling a bond (88) 8.9 against 7.6 us, all pairs (160) 14.4 against 10.7; 8 spins 3/2, range 2 (82) 6.6 against
+//    5.2 us; six modes of 8 levels (88) 9.0 against 6.6 us.  Below: 16 spins, range 3, one coupling (41) 10.0 against 10.4.
+//  - c128 and every gather with a factor that varies: from 13 gathers on their values no longer fit in registers.  10
+//    spins 3/2 of range 2 (24 gathers) 30.2 against 25.7 us, 11 modes of 5 levels (13) 926 against 789; below, a ring of
+//    10 such spins (11) 15.4 against 18.4 us.
+//  - c128, more than 150 coefficients and below 2^20 rows: 19 spins, all pairs, a coupling a bond (165) 67.0 against
+//    61.0 us; 18 spins of range 8 (143) 33.2 against 45.8 us, 20 spins, all pairs (179) 156 against 318.
+// None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.8, 10.1 and 38.2 us
+// against 14.4, 24.8 and 56.6.
+bool masked_is_better(const mrmf_plan_t* p, bool f32, const Tile& t, const WindowCost& c) {
+    for (int d : p->d)
+        if (d == 3) return false;
+    if (t.P_U == 1 && c.coefs + 8 * c.fills + c.varying >= 56) return true;
+    if (f32) return false;
+    return (c.varying == c.gathers && c.varying > 12) || (c.coefs > 150 && p->D < (1 << 20));
+}
 
 // no form was asked for, and no knob that only the masked and list forms have
 bool window_by_rule(const KernelCfg& cfg) {
@@ -2003,21 +2055,24 @@ std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom*
     // 32-bit signed scalar
     auto is_wide = [&](const Tile& t) { return cfg.wide != 0 || (p->D + dmax - dmin + 2 * t.T_in) * SZ >= lim; };
     Tile tl;
-    // The window form unless another one, or a knob that only the others have, was asked for; a plan or a tile that does
-    // not fit it (rows or tables of the uniform digits beyond LDS, complex weights) takes the masked one.
+    // The window form unless another one, or a knob that only the others have, was asked for or is better by rule; a plan
+    // or a tile that does not fit it (rows or tables of the uniform digits beyond LDS, complex weights) takes the masked
+    // one.
     if (!masked && window_real(p) && (cfg.variant == MRMF_VARIANT_WINDOW || window_by_rule(cfg))) {
         const bool rule = cfg.inner == 0 && cfg.unroll < 0 && cfg.unroll_top == 0;
         std::vector<WindowPass> passes;
-        if ((rule ? window_tile(p, f32, &tl) : choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) &&
+        if ((rule ? window_tile(p, cfg, f32, &tl) : choose_tiling(p, cfg.inner, cfg.unroll, cfg.unroll_top, &tl)) &&
             p->D / (tl.T_in * tl.P_U) < lim && (std::max<int64_t>(dmax, -dmin) + tl.T_in * tl.P_C) * SZ < lim) {
             window_passes(p, cfg, f32, epi, tl, &passes);
             std::string src = window_prelude(f32, is_wide(tl));
             for (size_t i = 0; i < passes.size() && !src.empty(); ++i) {
                 int64_t rows = 0;
                 passes[i].wide = is_wide(tl);
-                const std::string one = window_pass(p, passes[i], &geo->tiles[i], &rows);
+                WindowCost cost;
+                const std::string one = window_pass(p, passes[i], &geo->tiles[i], &rows, &cost);
                 geo->block[i] = static_cast<int>(round_up(rows, 64));
-                src = one.empty() ? "" : src + one;
+                const bool other = i == 0 && cfg.variant == kVariantAuto && masked_is_better(p, f32, tl, cost);
+                src = one.empty() || other ? "" : src + one;
             }
             if (!src.empty()) {
                 geo->n = static_cast<int>(passes.size());
@@ -2573,8 +2628,12 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
         int variant, inner, unrolled, group, top;
     };
     // inner blocks of 32..1024 rows: the window form with up to 4 unrolled sites and 16 copies (plans with real
-    // weights) or the list form in three chunk sizes, and the masked form with up to 2 unrolled sites and 9 copies
-    const bool real = window_real(plan);
+    // weights), the list form in three chunk sizes (complex weights, or many channels: 18 spins 1/2 with a coupling for
+    // each of all pairs, 306 channels, 27.8 us in c128 against 32 for the window form's best shape), and the masked form
+    // with up to 2 unrolled sites and 9 copies
+    const bool real = window_real(plan), f32 = dtype == MRMF_DTYPE_C, list = !real || plan->chans.size() > 128;
+    const KernelCfg defaults;
+    const bool two = two_passes(plan, defaults, f32);
     std::vector<Cand> cands;
     int64_t T = 1;
     for (int k = plan->N - 1; k >= 0; --k) {
@@ -2590,10 +2649,15 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
             // problem is that small)
             if (plan->D / (T * PU) < 64 && u > 0) break;
             const bool old = u <= 2 && PU <= 9;
+            Tile tl;
+            tl.k_in = k;
+            tl.k_u = k - u;
+            tl.T_in = T;
+            tl.P_C = tl.P_U = PU;
             if (old) cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, 0});
-            if (real) cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, 0});
+            if (real && window_fits(plan, defaults, f32, two, tl)) cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, 0});
             for (int g : {4, 8, 12})
-                if (!real) cands.push_back({MRMF_VARIANT_LIST, inner, u, g, 0});
+                if (old && list) cands.push_back({MRMF_VARIANT_LIST, inner, u, g, 0});
             // site 0 unrolled as well, when a term joins it to a site of this tile (a ring's closing bond)
             const int k_u = k - u;
             bool wrap = false;
@@ -2603,11 +2667,11 @@ mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, 
             for (int top = 1; wrap && top <= 2 && k_u > top; ++top) {  // sites 0..top-1 unrolled too
                 PT *= plan->d[top - 1];
                 if (PT > 16 || plan->D / (T * PT) < 64) break;
+                tl.n_top = top;
+                tl.P_U = PT;
                 if (old) cands.push_back({MRMF_VARIANT_MASKED, inner, u, 0, top});
-                if (real)
-                    cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, top});
-                else
-                    cands.push_back({MRMF_VARIANT_LIST, inner, u, 4, top});
+                if (real && window_fits(plan, defaults, f32, two, tl)) cands.push_back({MRMF_VARIANT_WINDOW, inner, u, 0, top});
+                if (old && list) cands.push_back({MRMF_VARIANT_LIST, inner, u, 4, top});
             }
         }
     }

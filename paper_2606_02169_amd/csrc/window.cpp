@@ -267,10 +267,10 @@ struct WinGen {
         return b + " + " + std::to_string(static_cast<uint32_t>(static_cast<uint64_t>(o))) + "u";
     }
 
-    std::string source();
+    std::string source(WindowCost* cost);
 };
 
-std::string WinGen::source() {
+std::string WinGen::source(WindowCost* cost) {
     const mrmf_plan_t& P = *p;
     const int block = static_cast<int>(round_up(T, 64));
     const bool cheb = w.mode >= kPassCheb;
@@ -292,13 +292,14 @@ std::string WinGen::source() {
         std::string cond, coef;
         int64_t delta;
         int chan, lf;
-        bool ucoef;  // the coefficient is the same for every lane
+        bool varying;  // the coefficient differs between rows or super-tiles
     };
     // a gather: per-lane byte offset, offset of its scalar base, coefficient; `branch`: scalar condition of a gather
     // that is rare enough to be issued and used in a branch of its own
     struct Load {
         std::string off, coef, branch;
         int64_t delta;
+        bool varying = false;  // the coefficient differs between rows or super-tiles
     };
     std::vector<std::vector<Stat>> stat(PU);
     std::vector<std::vector<Glob>> glob(PU);
@@ -377,7 +378,7 @@ std::string WinGen::source() {
                 g.delta = c.delta;
                 g.chan = ci;
                 g.lf = lf;
-                g.ucoef = lconst;
+                g.varying = !lconst || !ut.empty();
                 if (!ut.empty()) {
                     g.coef = ut + (uf != 1.0 ? " * " + lit(uf, f32) : std::string(""));
                     if (!lconst) g.coef += " * " + value(ops, lf);
@@ -513,6 +514,7 @@ std::string WinGen::source() {
                 if (og == "act" || oh == "act") break;
                 Load l;
                 l.delta = g.delta;
+                l.varying = g.varying || h.varying;
                 // voff + ahead of an inactive lane stays out of range: 2^31 + ahead < 2^32
                 l.off = tile_reg("unsigned", "o", "(" + og + ") ? voff : (" + oh + ") ? voff + " + ahead + " : OOB");
                 l.coef = g.coef == h.coef ? g.coef : tile_reg("R", "c", "(" + og + ") ? " + g.coef + " : " + h.coef);
@@ -520,6 +522,7 @@ std::string WinGen::source() {
                 if (share > 0.0) {  // both: the second one of the pair
                     Load r;
                     r.delta = h.delta;
+                    r.varying = h.varying;
                     r.off = "voff";
                     r.coef = h.coef;
                     r.branch = g.cond + " && " + h.cond;
@@ -535,6 +538,7 @@ std::string WinGen::source() {
             if (paired) continue;
             Load l;
             l.delta = one.delta;
+            l.varying = one.varying;
             l.coef = one.coef;
             const std::string lane_off =
                 one.lf < 0 || !lanes[one.lf].masked ? "voff" : reg("unsigned", "vo", mask(one.lf) + " ? voff : OOB");
@@ -639,6 +643,10 @@ std::string WinGen::source() {
     // ---------------------------------------------------------------- kernel
     std::ostringstream o;
     const size_t ne = entries.size();
+    cost->coefs = static_cast<int>(uk.size());
+    cost->fills = static_cast<int>((ne + block - 1) / block);
+    cost->gathers = static_cast<int>(load[0].size());
+    cost->varying = static_cast<int>(std::count_if(load[0].begin(), load[0].end(), [](const Load& l) { return l.varying; }));
     std::ostringstream cb, cp, cv;
     size_t at = 0;
     for (size_t e = 0; e < ne; ++e) {
@@ -925,11 +933,11 @@ std::string window_prelude(bool f32, bool wide) {
     return o.str();
 }
 
-std::string window_pass(const mrmf_plan_t* p, const WindowPass& w, int64_t* n_tiles, int64_t* rows) {
+std::string window_pass(const mrmf_plan_t* p, const WindowPass& w, int64_t* n_tiles, int64_t* rows, WindowCost* cost) {
     WinGen g(p, w);
     *n_tiles = g.n_st;
     *rows = g.T;
-    return g.source();
+    return g.source(cost);
 }
 
 }  // namespace mrmf

@@ -34,11 +34,19 @@ struct WindowPass {
     std::string name, tag;  // kernel name; suffix of the pass's constants
 };
 
+// What a pass asks of a block: values that are worked out before its first super-tile, and gathers.
+struct WindowCost {
+    int coefs = 0;    // coefficients that are the same for every row
+    int fills = 0;    // rounds of the block that fill the tables of the uniform digits
+    int gathers = 0;  // of the first copy
+    int varying = 0;  // of those, with a factor that differs between rows or super-tiles
+};
+
 // true when every term weight is real (the form has no complex coefficients)
 bool window_real(const mrmf_plan_t* p);
 std::string window_prelude(bool f32, bool wide);
 // Source of one pass (after window_prelude, which several passes share); "" when the plan or its tile does not fit the
 // form (tables, LDS).
-std::string window_pass(const mrmf_plan_t* p, const WindowPass& w, int64_t* n_tiles, int64_t* rows);
+std::string window_pass(const mrmf_plan_t* p, const WindowPass& w, int64_t* n_tiles, int64_t* rows, WindowCost* cost);
 
 }  // namespace mrmf

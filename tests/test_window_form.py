@@ -180,6 +180,50 @@ def test_tile_beyond_lds_takes_the_masked_form():
     assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z, inner=2, unrolled=0)
 
 
+def pairs(sites, reach, per_bond=False, ring=False):
+    """Couplings of sites up to `reach` apart: one pair (J_xy, J_z) for all bonds, or one a bond."""
+    n, terms, theta = len(sites), [], [1.0, 0.8]
+    for b, (i, j) in enumerate((i, (i + k) % n) for k in range(1, reach + 1) for i in range(n) if ring or i + k < n):
+        terms += W.xxz_bond_terms(i, j, 2 * b, 2 * b + 1) if per_bond else W.xxz_bond_terms(i, j, 0, 1)
+    return W.Model(sites, terms, np.array(theta * (b + 1) if per_bond else theta))
+
+
+# (lattice, window form by rule in c128, in c64): both sides of each line of the rule
+RULE = {
+    "16 spins 1/2, range 3": (lambda: pairs([W.spin_site(1)] * 16, 3, ring=True), True, True),
+    "16 spins 1/2, range 4, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 16, 4, True, True), False, False),
+    "18 spins 1/2, range 4, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 4, True, True), True, True),
+    "16 spins 1/2, all pairs": (lambda: pairs([W.spin_site(1)] * 16, 15), True, True),
+    "18 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 17, True), False, True),
+    "20 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 20, 19, True), True, True),
+    "10 spins 1, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(2)] * 10, 9, True), True, True),
+    "10 spins 3/2": (lambda: pairs([W.spin_site(3)] * 10, 1, ring=True), True, True),
+    "10 spins 3/2, range 2": (lambda: pairs([W.spin_site(3)] * 10, 2, ring=True), False, True),
+    "8 spins 3/2, range 2": (lambda: pairs([W.spin_site(3)] * 8, 2, ring=True), False, False),
+}
+
+
+@pytest.mark.parametrize("name", list(RULE))
+def test_form_of_plans_with_many_terms(name):
+    model, z, c = RULE[name]
+    m = model()
+    for dtype, window in ((L.MRMF_DTYPE_Z, z), (L.MRMF_DTYPE_C, c)):
+        assert ("window form" in E.kernel_source(m, dtype)) == window, dtype
+        # asked for, it is taken all the same
+        assert "window form" in E.kernel_source(m, dtype, tuning={"variant": L.MRMF_VARIANT_WINDOW})
+
+
+@pytest.mark.parametrize("n", [20, 24, 26])
+def test_gathers_of_all_copies_are_bounded(n):
+    """Couplings of all pairs: the kernel by rule does not grow with copies times channels.  720 and 1440 by the rule's
+    count, half of a copy's channels; a copy's own digits leave up to a third more of them."""
+    m = pairs([W.spin_site(1)] * n, n - 1)
+    for dtype, most in ((L.MRMF_DTYPE_Z, 720), (L.MRMF_DTYPE_C, 1440)):
+        first = E.kernel_source(m, dtype).split('extern "C" __global__')[1]
+        gathers = re.findall(r"const C s(\d+)_\d+ = LD", first)
+        assert len(set(gathers)) > 1 and len(gathers) <= most * 4 / 3
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(LARGE_SITES))
 def test_gpu_large_sites(name):
