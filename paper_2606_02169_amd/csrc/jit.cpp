@@ -2008,16 +2008,19 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
 
 namespace {
 
-// Plans that the masked form (or the list form, which it gives way to) serves better, from the times of both on 127
+// Plans that the masked form (or the list form, which it gives way to) serves better, from the times of both on 150
 // lattices in c128 and c64: rings and squares of range 1 to 8, power laws, couplings of all pairs, one coupling for all
 // bonds or one a bond, spins 1/2 to 5/2 and modes of 4 to 8 levels, 10^3 to 5 x 10^7 rows.
 //  - One copy, so that a block does one or two super-tiles: what it works out before the first one counts.  From a set-up
-//    of 56 on (a coefficient and a varying gather 1 each, a round of table entries 8): 16 spins 1/2, range 4 and a
-//    coupling a bond (88) 8.9 against 7.6 us, all pairs (160) 14.4 against 10.7; 8 spins 3/2, range 2 (82) 6.6 against
-//    5.2 us; six modes of 8 levels (88) 9.0 against 6.6 us.  Below: 16 spins, range 3, one coupling (41) 10.0 against 10.4.
-//  - c128 and every gather with a factor that varies: from 13 gathers on their values no longer fit in registers.  10
-//    spins 3/2 of range 2 (24 gathers) 30.2 against 25.7 us, 11 modes of 5 levels (13) 926 against 789; below, a ring of
-//    10 such spins (11) 15.4 against 18.4 us.
+//    of 56 on (a coefficient 1, a round of table entries 8, a varying gather 1, from 2^18 rows on 2.5): 16 spins 1/2, range
+//    4 and a coupling a bond (88) 8.9 against 7.6 us, all pairs (160) 14.4 against 10.7; 8 spins 3/2, range 2 (82) 6.6
+//    against 5.2 us; six modes of 8 levels (100) 9.0 against 6.6 us; 12 spins around a mode of 65 levels (66) 9.2 against
+//    7.3 us.  Below: 16 spins, all pairs, one coupling (41) 10.0 against 10.4 us; 12 spins around a mode of 21 levels
+//    (28) 4.8 against 5.8.
+//  - c128 and every gather with a factor that varies, a quarter of them from tables: from 13 gathers on their values no
+//    longer fit in registers.  10 spins 3/2 of range 2 (24 gathers) 30.2 against 25.7 us, 11 modes of 5 levels (13) 926
+//    against 789; below, a ring of 10 such spins (11) 15.4 against 18.4 us.  Spins 1/2 around a mode have no tables
+//    (14 of them, 65 levels, 20 gathers: 20.3 against 21.5 us).
 //  - c128, more than 150 coefficients and below 2^20 rows: 19 spins, all pairs, a coupling a bond (165) 67.0 against
 //    61.0 us; 18 spins of range 8 (143) 33.2 against 45.8 us, 20 spins, all pairs (179) 156 against 318.
 // None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.8, 10.1 and 38.2 us
@@ -2025,9 +2028,9 @@ namespace {
 bool masked_is_better(const mrmf_plan_t* p, bool f32, const Tile& t, const WindowCost& c) {
     for (int d : p->d)
         if (d == 3) return false;
-    if (t.P_U == 1 && c.coefs + 8 * c.fills + c.varying >= 56) return true;
+    if (t.P_U == 1 && c.coefs + 8 * c.fills + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0) >= 56.0) return true;
     if (f32) return false;
-    return (c.varying == c.gathers && c.varying > 12) || (c.coefs > 150 && p->D < (1 << 20));
+    return (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) || (c.coefs > 150 && p->D < (1 << 20));
 }
 
 // no form was asked for, and no knob that only the masked and list forms have

@@ -292,14 +292,14 @@ std::string WinGen::source(WindowCost* cost) {
         std::string cond, coef;
         int64_t delta;
         int chan, lf;
-        bool varying;  // the coefficient differs between rows or super-tiles
+        bool varying, tabled;  // as a gather's
     };
     // a gather: per-lane byte offset, offset of its scalar base, coefficient; `branch`: scalar condition of a gather
     // that is rare enough to be issued and used in a branch of its own
     struct Load {
         std::string off, coef, branch;
         int64_t delta;
-        bool varying = false;  // the coefficient differs between rows or super-tiles
+        bool varying = false, tabled = false;  // the coefficient differs between rows or super-tiles; comes from a table
     };
     std::vector<std::vector<Stat>> stat(PU);
     std::vector<std::vector<Glob>> glob(PU);
@@ -378,7 +378,8 @@ std::string WinGen::source(WindowCost* cost) {
                 g.delta = c.delta;
                 g.chan = ci;
                 g.lf = lf;
-                g.varying = !lconst || !ut.empty();
+                g.tabled = !ut.empty();
+                g.varying = !lconst || g.tabled;
                 if (!ut.empty()) {
                     g.coef = ut + (uf != 1.0 ? " * " + lit(uf, f32) : std::string(""));
                     if (!lconst) g.coef += " * " + value(ops, lf);
@@ -515,6 +516,7 @@ std::string WinGen::source(WindowCost* cost) {
                 Load l;
                 l.delta = g.delta;
                 l.varying = g.varying || h.varying;
+                l.tabled = g.tabled || h.tabled;
                 // voff + ahead of an inactive lane stays out of range: 2^31 + ahead < 2^32
                 l.off = tile_reg("unsigned", "o", "(" + og + ") ? voff : (" + oh + ") ? voff + " + ahead + " : OOB");
                 l.coef = g.coef == h.coef ? g.coef : tile_reg("R", "c", "(" + og + ") ? " + g.coef + " : " + h.coef);
@@ -523,6 +525,7 @@ std::string WinGen::source(WindowCost* cost) {
                     Load r;
                     r.delta = h.delta;
                     r.varying = h.varying;
+                    r.tabled = h.tabled;
                     r.off = "voff";
                     r.coef = h.coef;
                     r.branch = g.cond + " && " + h.cond;
@@ -539,6 +542,7 @@ std::string WinGen::source(WindowCost* cost) {
             Load l;
             l.delta = one.delta;
             l.varying = one.varying;
+            l.tabled = one.tabled;
             l.coef = one.coef;
             const std::string lane_off =
                 one.lf < 0 || !lanes[one.lf].masked ? "voff" : reg("unsigned", "vo", mask(one.lf) + " ? voff : OOB");
@@ -646,7 +650,10 @@ std::string WinGen::source(WindowCost* cost) {
     cost->coefs = static_cast<int>(uk.size());
     cost->fills = static_cast<int>((ne + block - 1) / block);
     cost->gathers = static_cast<int>(load[0].size());
-    cost->varying = static_cast<int>(std::count_if(load[0].begin(), load[0].end(), [](const Load& l) { return l.varying; }));
+    for (const Load& l : load[0]) {
+        cost->varying += l.varying;
+        cost->tabled += l.tabled;
+    }
     std::ostringstream cb, cp, cv;
     size_t at = 0;
     for (size_t e = 0; e < ne; ++e) {

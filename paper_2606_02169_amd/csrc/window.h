@@ -40,6 +40,7 @@ struct WindowCost {
     int fills = 0;    // rounds of the block that fill the tables of the uniform digits
     int gathers = 0;  // of the first copy
     int varying = 0;  // of those, with a factor that differs between rows or super-tiles
+    int tabled = 0;   // of those, with a factor read from the tables for every super-tile
 };
 
 // true when every term weight is real (the form has no complex coefficients)

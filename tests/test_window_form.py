@@ -199,6 +199,9 @@ RULE = {
     "10 spins 1, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(2)] * 10, 9, True), True, True),
     "10 spins 3/2": (lambda: pairs([W.spin_site(3)] * 10, 1, ring=True), True, True),
     "10 spins 3/2, range 2": (lambda: pairs([W.spin_site(3)] * 10, 2, ring=True), False, True),
+    "12 spins 1/2 around a mode of 21 levels": (lambda: W.tavis_cummings(12, 20, rng=np.random.default_rng(5)), True, True),
+    "12 spins 1/2 around a mode of 65 levels": (lambda: W.tavis_cummings(12, 64, rng=np.random.default_rng(5)), False, False),
+    "14 spins 1/2 around a mode of 65 levels": (lambda: W.tavis_cummings(14, 64, rng=np.random.default_rng(5)), True, True),
     "8 spins 3/2, range 2": (lambda: pairs([W.spin_site(3)] * 8, 2, ring=True), False, False),
 }
 
