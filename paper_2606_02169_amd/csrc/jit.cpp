@@ -1833,8 +1833,10 @@ double admitted_share(const mrmf_plan_t* p, const DevChan& c) {
 // y again on top of the first pass's two), but its short runs of rows stream at 4.6 TB/s where a single pass moves
 // 7.3, so it pays from about 9 units on: 4 x 4 spin-1 lattice (12 far bonds, 12.7 units) 1765 -> 1205 us in c128 and
 // 835 -> 756 us in c64; 20-site ring (7 far bonds, 6.7 units) 1014 -> 1117 us, open chain of 25 spins 1/2 (5 units)
-// 526 -> 626 us.
-constexpr int64_t kFarBytes = 3 << 19;
+// 526 -> 626 us.  Vectors below kTwoPassBytes stay in the L2s whatever the order, and the second launch is all that is
+// added: all pairs of 18 spins 1/2 (4 MB) 27.7 -> 29.2 us with one coupling, 28.3 -> 29.9 us as a power law; above it,
+// of 20 spins 161 -> 114 us (16 MB) and in c64 98.7 -> 89.7 us (8 MB), 20 spins of range 4 (16 MB) 61.0 -> 50.4 us.
+constexpr int64_t kFarBytes = 3 << 19, kTwoPassBytes = 1 << 23;
 bool is_far(const DevChan& c, const KernelCfg& cfg, bool f32) {
     const int64_t far = cfg.far_pass >= 10 ? int64_t(1) << cfg.far_pass : kFarBytes;
     return std::llabs(c.delta) * (f32 ? 8 : 16) >= far;
@@ -1848,7 +1850,7 @@ bool two_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32) {
             u1 += admitted_share(p, c);
             ++n;
         }
-    return n > 0 && (cfg.far_pass != 0 || u1 > 1.8 * 5.0);
+    return n > 0 && (cfg.far_pass != 0 || (u1 > 1.8 * 5.0 && p->D * (f32 ? 8 : 16) >= kTwoPassBytes));
 }
 
 // Tile of the window form.  Fitted to the times of every tile on 70 random chains, rings and spin-boson lattices of

@@ -216,6 +216,16 @@ def test_form_of_plans_with_many_terms(name):
         assert "window form" in E.kernel_source(m, dtype, tuning={"variant": L.MRMF_VARIANT_WINDOW})
 
 
+
+@pytest.mark.parametrize("n,z,c", [(18, 1, 1), (19, 2, 1), (20, 2, 2)])
+def test_passes_by_the_size_of_the_vector(n, z, c):
+    """All pairs of spins 1/2: a second launch from vectors of 8 MB on (18 spins of c128 are 4 MB), unless asked for."""
+    m = pairs([W.spin_site(1)] * n, n - 1)
+    for dtype, passes in ((L.MRMF_DTYPE_Z, z), (L.MRMF_DTYPE_C, c)):
+        assert len(E.launch_shapes(E.kernel_source(m, dtype))) == passes
+        assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 1}))) == 1
+        assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 18}))) == 2
+
 @pytest.mark.parametrize("n", [20, 24, 26])
 def test_gathers_of_all_copies_are_bounded(n):
     """Couplings of all pairs: the kernel by rule does not grow with copies times channels.  720 and 1440 by the rule's
