@@ -270,7 +270,9 @@ mrmf_status mrmf_plan_set_shape(mrmf_plan plan, int32_t dtype, int32_t variant, 
 mrmf_status mrmf_plan_autotune(mrmf_plan plan, int32_t dtype, const void* d_ws, const void* d_theta,
                                const void* d_x, void* d_y, mrmf_stream stream, int32_t* out);
 /* Build (compile and load) the kernel mrmf_matvec_z (dtype Z) or mrmf_matvec_c (dtype C) will use, now
- * rather than on the first call (e.g. before stream capture).  Synchronous; host-side only.
+ * rather than on the first call (e.g. before stream capture, under which it would be built as well, but
+ * slowly).  mrmf_lanczos may launch a kernel of its own, which its first call builds.  Synchronous; host-side
+ * only.
  * dtype = MRMF_SOURCE_GRAD builds the generated coupling-gradient kernel of mrmf_adjoint_z and returns
  * MRMF_E_UNSUPPORTED when the plan does not qualify for it (the adjoint then runs its generic pass). */
 mrmf_status mrmf_plan_prepare(mrmf_plan plan, int32_t dtype);

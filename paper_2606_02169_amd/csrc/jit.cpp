@@ -2180,6 +2180,14 @@ mrmf_status rtc_code(const std::string& src, const std::string& arch, std::share
     return MRMF_OK;
 }
 
+// Loading a code object is no work on any stream, but a capture in the default (global) mode refuses it on every thread;
+// in the relaxed mode it is allowed, so that a kernel may be needed for the first time under capture.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // Compiles a generated source for the device and loads kernel `name` (and `name2` into *fn2_out when given).
 mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceProp_t& prop, hipModule_t* mod_out,
                       hipFunction_t* fn_out, std::string* log_out, const char* name2 = nullptr,
@@ -2187,6 +2195,7 @@ mrmf_status rtc_build(const std::string& src, const char* name, const hipDeviceP
     std::shared_ptr<const std::vector<char>> code;
     const mrmf_status st = rtc_code(src, arch_option(prop), &code, log_out);
     if (st != MRMF_OK) return st;
+    const RelaxedCapture relaxed;
     hipModule_t mod;
     if (hipModuleLoadData(&mod, code->data()) != hipSuccess) return MRMF_E_HIP;
     hipFunction_t fn;
@@ -2615,8 +2624,6 @@ mrmf_status mrmf_plan_prepare(mrmf_plan plan, int32_t dtype) {
     const int32_t mode = plan->cfg[dtype].mode;
     if (mode == MRMF_KERNEL_GENERIC) return MRMF_OK;
     const mrmf_status st = mrmf::spec_prepare(plan, dtype);
-    // Lanczos may launch a kernel of its own: built here too, as it may run under stream capture later
-    if (st == MRMF_OK) mrmf::spec_prepare(plan, mrmf::lanczos_slot(plan, dtype));
     if (st == MRMF_E_UNSUPPORTED && mode == MRMF_KERNEL_AUTO) return MRMF_OK;
     return st;
 }

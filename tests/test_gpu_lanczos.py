@@ -360,3 +360,34 @@ def test_basis_and_recurrence_over_sizes(two_s, m_steps, reorth):
     V = out["V"].reshape(m_steps + 1, -1)[:k].cpu().numpy()
     assert np.max(np.abs(V.conj() @ V.T - np.eye(k))) <= 1e-12
     assert abs(float(out["result"][0]) - o["theta"]) <= 1e-11 * abs(o["theta"])
+
+
+@pytest.mark.parametrize("before", ["prepare", "matvec", "nothing"])
+@pytest.mark.parametrize("precision", ["z", "c_in_z"])
+def test_lanczos_captured_first(before, precision):
+    """mrmf_lanczos captured before any eager call of it: its kernel, which is not the matvec's, is built under the
+    capture.  Replays (with eager work between them) equal an eager call of another plan bitwise."""
+    m = W.ferrimagnetic_ring(8)
+    rng = np.random.default_rng(9200)
+    th = torch.as_tensor(m.theta, dtype=torch.float64, device="cuda")
+    tc = th.float()
+    x = torch.from_numpy(W.random_state(m.dim, rng)).cuda()
+    p = Plan(m)
+    if before == "prepare":
+        p.prepare(torch.complex128)
+    elif before == "matvec":
+        p.matvec(th, x)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = p.lanczos(th, x, 24, precision=precision, theta_c=tc)
+    ref = Plan(m).lanczos(th, x, 24, precision=precision, theta_c=tc)
+    for k in range(3):
+        out["alpha"].zero_()
+        out["result"].fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        p.matvec(th, x)
+        torch.cuda.synchronize()
+        for key in ("alpha", "beta", "result", "u"):
+            assert torch.equal(out[key], ref[key]), (k, key)
