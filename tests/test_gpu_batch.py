@@ -355,3 +355,25 @@ def test_group_products(nvec):
     torch.cuda.synchronize()
     for p in range(plan.n_params):
         assert rel_err(sw.basis.block(G, p).cpu().numpy(), full.block(F, p).cpu().numpy()) <= 1e-6, p
+
+
+@pytest.mark.parametrize("n", [6, 10, 12])
+@pytest.mark.parametrize("nvec", [1, 2, 4, 8])
+def test_sweep_shape(n, nvec):
+    """The launch shape of a sweep's group products on both sides of its line (rings of 6, 10 and 12 sites: 864, 31104
+    and 186624 rows of all couplings): one row a thread, and the bits of any other shape."""
+    from paper_2606_02169_amd.plan import Plan, Sweep
+    m = W.ferrimagnetic_ring(n)
+    sw = Sweep(Plan.from_model(m), nvec)
+    rows = max(512 // nvec, 256 if m.dim * m.n_params >= 160 * 256 else 0)
+    s = sw.basis.shape()
+    assert (s["tile_rows_max"], s["block"], s["schedule"]) == (rows, rows, "xcd_chunk")
+    X = torch.zeros(sw.input_elems, dtype=torch.complex64, device=DEV)
+    x = W.random_state(m.dim, np.random.default_rng(77), np.complex64, nvec=nvec)
+    X[: sw.n].copy_(torch.from_numpy(x.reshape(-1)).to(DEV))
+    th = torch.rand((5, m.n_params), dtype=torch.float32, device=DEV)
+    Y = sw.run(th, X)
+    sw.basis.set_shape(2048 // nvec, 256, "runs")
+    Z = sw.run(th, X)
+    for k in range(5):   # entries between the blocks are nobody's
+        assert torch.equal(sw.block(Y, k), sw.block(Z, k)), k
