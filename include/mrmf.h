@@ -559,10 +559,10 @@ mrmf_status mrmf_batch_graph_launch(mrmf_batch batch, mrmf_stream stream);
  * Synchronises the stream. */
 mrmf_status mrmf_batch_autotune(mrmf_batch batch, const void* d_ws, const float* d_theta_all,
                                 const void* d_X, void* d_Y, mrmf_stream stream, int32_t* out);
-/* Set a launch shape directly (e.g. from a tuning cache).  Each lattice's rows are cut into tiles spanned
- * by its low sites, of at most tile_rows_max rows, one of (64, 128, 256, 512) * 8 / nvec; a block holds
- * max(1, block / T) such tiles in LDS at a time.  block_threads: a multiple of 64, at most 512 and at
- * most 4096 / nvec. */
+/* Set a launch shape directly (e.g. from a tuning cache).  Each lattice's rows are cut into tiles of at most
+ * tile_rows_max rows, one of (64, 128, 256, 512) * 8 / nvec, spanned by its low sites and a run of digits of the
+ * next one; a block holds one tile in LDS at a time.  block_threads: a multiple of 64, at most 512 and at
+ * most 4096 / nvec.  Until a shape is set or tuned, the library's rule from the rows of all lattices. */
 mrmf_status mrmf_batch_set_shape(mrmf_batch batch, int32_t tile_rows_max, int32_t block_threads);
 /* Work schedule of the persistent grid over the work items (a block's tiles, numbered lattice by
  * lattice): MRMF_BATCH_SCHED_RUNS (default) - each block takes a contiguous run of items, the runs of

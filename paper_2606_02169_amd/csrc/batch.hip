@@ -636,11 +636,12 @@ void factor_table(const mrmf_plan_t* p, int site, int op, std::vector<float>& ou
     for (int n = 0; n < p->d[site]; ++n) out.push_back(static_cast<float>(local_factor_host(p, site, op, n)));
 }
 
-// Launch shapes tried by the autotuner: (R_max candidate index, block threads).
+// Launch shapes tried by the autotuner: (R_max candidate index, block threads).  The last two are for one and two
+// vectors, whose smallest tiles have 512 and 256 rows: eight rings of 7 spins 1, one vector, 21.4 -> 12.2 us.
 struct Shape {
     int32_t rc, block;
 };
-const Shape kShapes[] = {{1, 128}, {2, 128}, {2, 256}, {3, 256}, {3, 512}, {0, 64}, {1, 256}, {0, 128}};
+const Shape kShapes[] = {{1, 128}, {2, 128}, {2, 256}, {3, 256}, {3, 512}, {0, 64}, {1, 256}, {0, 128}, {0, 256}, {0, 512}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 BDiv div_of(int64_t m) {  // 1 <= m < 2^30
@@ -651,6 +652,22 @@ BDiv div_of(int64_t m) {  // 1 <= m < 2^30
 }
 
 int32_t rmax_of(int rc, int nvec) { return (64 << rc) * 8 / nvec; }
+
+// Launch shape until one is set, from the rows of all lattices: one row a thread in tiles of 256 rows (one vector: 512, the
+// smallest there is), of 128 (eight vectors) up to 131072 rows and of the smallest size below 40960, where larger tiles
+// leave the GPU short of them.  us, against tiles of 2048 / nvec rows for 256 threads: eight rings of 7 spins 1 (17496
+// rows) 1 vector 12.2 (39.0), 4 vectors 9.8 (18.3), 8 vectors 10.4 (11.6); eight rings of 7 spins 3/2 (131072) 12.3 (52.0),
+// 10.8 (16.5), 12.7 (15.0); eight rings of 12 spins 1/2 and 1 (373248) 27.9 (57.3), 26.5 (31.3), 29.1; the group products
+// of nine spins 1 (59049) 8 vectors 9.4, in the smallest tiles 13.2.  From 2^22 rows on a thread's several rows cost less
+// than more tiles (29 million, 4 vectors: 1801 against 1877 us).
+Shape default_shape(int64_t rows, int nvec) {
+    if (rows >= int64_t(1) << 22) return {2, 256};
+    const int least = 512 / nvec;
+    const int tile = rows < 160 * 256 ? least : std::max(least, nvec == 8 && rows <= 131072 ? 128 : 256);
+    int rc = 0;
+    while (rmax_of(rc, nvec) < tile) ++rc;
+    return {rc, tile};
+}
 
 }  // namespace
 }  // namespace mrmf
@@ -664,7 +681,7 @@ struct mrmf_batch_t {
     int32_t max_terms = 0, max_pool = 0;  // of a lattice
     std::vector<unsigned char> image;
     size_t off_lat = 0, off_site = 0, off_term = 0, off_pool = 0, ws_bytes = 0;
-    int32_t rc = 2, block = 256;  // R_max candidate index and block threads
+    int32_t rc = 0, block = 0;  // R_max candidate index and block threads
     int32_t sched = 0;            // MRMF_BATCH_SCHED_*
     int32_t grid = 0;
     bool shared = false;                     // mrmf_batch_share_input
@@ -837,6 +854,11 @@ mrmf_status create(int32_t n, const mrmf_plan* plans, int32_t nvec, bool groups,
     }
     b->th_off.push_back(th);
     b->total = off;
+    int64_t rows = 0;
+    for (int i = 0; i < n; ++i) rows += plans[i]->D;
+    const Shape shape = default_shape(rows, nvec);
+    b->rc = shape.rc;
+    b->block = shape.block;
     for (int rc = 0; rc < kBatchRmaxCands; ++rc) {
         if (items[rc] >= (int64_t(1) << 30)) {  // more rows than any memory holds
             delete b;
@@ -1044,7 +1066,7 @@ mrmf_status mrmf_batch_autotune(mrmf_batch b, const void* d_ws, const float* d_t
         b->rc = mrmf::kShapes[i % mrmf::kNumShapes].rc;
         b->block = mrmf::kShapes[i % mrmf::kNumShapes].block;
         b->sched = i / mrmf::kNumShapes;
-        if (b->block > mrmf::kBatchTileWords / b->nvec) continue;
+        if (b->block > mrmf::kBatchTileWords / b->nvec || b->block > 2 * mrmf::rmax_of(b->rc, b->nvec)) continue;
         st = launch(b, d_ws, d_theta_all, d_X, d_Y, s);  // warm-up
         if (st != MRMF_OK) break;
         hipEventRecord(e0, s);

@@ -583,13 +583,7 @@ class Sweep:
             raise ValueError("a sweep by linearity needs 1 to 16 couplings")
         self.plan, self.nvec, self.P, self.device = plan, int(nvec), P, plan.device
         self.basis = Batch._of_groups(plan, self.nvec)
-        # One row a thread in tiles of 256 rows (nvec 1: 512, the smallest there is), and of the smallest size where those
-        # leave the GPU short of tiles.  Group products, us, against tiles of 2048 / nvec rows for 256 threads: ring of 8
-        # spins 1/2 and 1 (5184 rows of four couplings) 1 vector 7.9 (26.4), 4 vectors 6.6 (11.4), 8 vectors 7.3 (8.6); 12
-        # sites (186624) 13.0 (30.4), 12.9 (15.7), 13.4; ring of 9 spins 1 (59049) 8 vectors 9.4, in the smallest tiles 13.2.
-        least = 512 // self.nvec
-        rows = least if plan.D * P < 160 * 256 else max(least, 256)
-        self.basis.set_shape(rows, rows, "xcd_chunk")
+        L.call("mrmf_batch_set_schedule", self.basis._handle, L.MRMF_BATCH_SCHED_XCD_CHUNK)
         self.n = plan.D * self.nvec
         self.stride = (self.n + 31) // 32 * 32          # the batch's block pitch (offsets padded to 32)
         if P > 1 and self.basis.offsets[1] - self.basis.offsets[0] != self.stride:

@@ -377,3 +377,20 @@ def test_sweep_shape(n, nvec):
     Z = sw.run(th, X)
     for k in range(5):   # entries between the blocks are nobody's
         assert torch.equal(sw.block(Y, k), sw.block(Z, k)), k
+
+
+@pytest.mark.parametrize("n,two_s,count", [(5, 2, 8), (7, 2, 8), (7, 3, 8), (12, 1, 80)])
+@pytest.mark.parametrize("nvec", [1, 2, 4, 8])
+def test_default_shape(n, two_s, count, nvec):
+    """The launch shape of a batch until one is set, between its lines (1944, 17496, 131072 and 327680 rows): one row a
+    thread, against the oracle."""
+    m = W.staggered_xxz_ring([two_s] * n)
+    rows = m.dim * count
+    x = W.random_state(m.dim, np.random.default_rng(78), np.complex64, nvec=nvec)
+    B, X, th = build([m] * count, [x] * count, nvec=nvec)
+    tile = max(512 // nvec, 0 if rows < 40960 else 128 if nvec == 8 and rows <= 131072 else 256)
+    s = B.shape()
+    assert (s["tile_rows_max"], s["block"], s["schedule"]) == (tile, tile, "runs")
+    Y = B.matvec(th, X, torch.zeros_like(X))
+    torch.cuda.synchronize()
+    check_all(B, [m] * count, [x] * count, Y)
