@@ -1853,13 +1853,33 @@ bool two_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32) {
     return n > 0 && (cfg.far_pass != 0 || (u1 > 1.8 * 5.0 && p->D * (f32 ? 8 : 16) >= kTwoPassBytes));
 }
 
+// a vector far beyond the 256 MB Infinity Cache, whose sweep memory bounds
+bool beyond_cache(const mrmf_plan_t* p, bool f32) { return p->D * (f32 ? 8 : 16) > (f32 ? 600000000 : 300000000); }
+
+// sites on which a channel has factors of several values (spins from 3/2 on, modes)
+std::vector<char> varied_sites(const mrmf_plan_t* p) {
+    std::vector<char> v(p->N, 0);
+    for (const auto& c : p->chans)
+        for (auto so : {std::make_pair(c.a, c.opa), std::make_pair(c.b, c.opb)}) {
+            if (so.first < 0) continue;
+            std::set<double> values;
+            for (double t : op_table(p, so.first, so.second))
+                if (t != 0.0) values.insert(t);
+            if (values.size() > 1) v[so.first] = 1;
+        }
+    return v;
+}
+
 // Tile of the window form.  Fitted to the times of every tile on 70 random chains, rings and spin-boson lattices of
 // 10^3 to 4 x 10^7 rows: about 768 super-tiles or more (three for each CU; fewer leave CUs idle at the end of the
 // sweep), then super-tiles of a few thousand rows (more of the bonds in LDS, fewer barriers and scalar set-ups a row)
 // in blocks near 128 rows that fill their last wave.  The rule's tile is 7 % (c128) and 8 % (c64) slower than each
 // lattice's best, 1.27 and 1.24 times faster than the masked form's on average.  Site 0 joins the unrolled ones from
 // 10^6 c128 rows on where a channel joins it to the tile (a ring's closing bond: 18 sites 146 -> 140 us); in c64 and
-// below that it cost as much as it gave.
+// below that it cost as much as it gave.  An unrolled site of varied factors takes a little off a c128 tile's score: its
+// copies have coefficients of their own and share none of their gathers (12 sites of spins 1 and 3/2 in a ring, 1.7
+// million rows: two spins 3/2 unrolled 37.9 us, none 26.5).  Not where memory bounds the sweep and a larger super-tile
+// counts for more (15 mixed sites, 191 million rows: 4470 us with them, 5460 without).
 //
 // Of the tiles with several copies, those whose copies gather at no more than kWindowGathers places in all in the first
 // pass (half the global channels a copy: the two of a bond exclude each other).  Beyond that the kernel only gets longer:
@@ -1886,6 +1906,8 @@ bool window_tile(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, Tile* tl)
     const double wT = f32 ? 0.1 : 0.05, wR = f32 ? 0.1 : 0.02, wE = f32 ? 1.0 : 0.5, wN = f32 ? 0.3 : 1.0;
     const double R0 = f32 ? 6144.0 : 4096.0;
     const bool two = two_passes(p, cfg, f32);
+    const std::vector<char> varied = varied_sites(p);
+    const double wV = f32 || beyond_cache(p, f32) ? 0.0 : 0.02;
     double best = -1e30;
     int64_t best_T = 0;  // of equal tiles the one with more inner rows (spins 3/2, 10^6 rows: 18.9 -> 16.2 us)
     int64_t T = 1;
@@ -1908,7 +1930,9 @@ bool window_tile(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, Tile* tl)
             t.P_U = PU * (top ? p->d[0] : 1);
             if (!window_fits(p, cfg, f32, two, t)) continue;
             const double R = double(T * t.P_U), tiles = double(p->D) / R;
-            const double score = wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
+            int nv = top && varied[0] ? 1 : 0;
+            for (int s = t.k_u; s < t.k_in; ++s) nv += varied[s];
+            const double score = -wV * nv + wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
                                  wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
             if (score < best - 1e-9 || (score <= best + 1e-9 && T == best_T)) continue;
             best_T = T;
@@ -1931,7 +1955,7 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
     // Sweep: an eighth per XCD (10 million c128 rows 138 against 151 us), windows where the vector is far beyond the
     // 256 MB Infinity Cache (60 million: 1038 against 1103 us); there the prefetch of the next super-tile, which takes
     // its memory bandwidth from the gathers that the block waits for, costs as well (1061 against 1014 us).
-    w.sched = cfg.sched != kSchedAuto ? cfg.sched : p->D * SZ > (f32 ? 600000000 : 300000000) ? MRMF_SCHED_WINDOWS : MRMF_SCHED_XCD_CHUNK;
+    w.sched = cfg.sched != kSchedAuto ? cfg.sched : beyond_cache(p, f32) ? MRMF_SCHED_WINDOWS : MRMF_SCHED_XCD_CHUNK;
     w.prefetch = p->D * SZ <= 300000000;
     w.waves = cfg.waves_per_eu;
     w.f32 = f32;
@@ -2023,8 +2047,9 @@ namespace {
 //    longer fit in registers.  10 spins 3/2 of range 2 (24 gathers) 30.2 against 25.7 us, 11 modes of 5 levels (13) 926
 //    against 789; below, a ring of 10 such spins (11) 15.4 against 18.4 us.  Spins 1/2 around a mode have no tables
 //    (14 of them, 65 levels, 20 gathers: 20.3 against 21.5 us).
-//  - c128, more than 150 coefficients and below 2^20 rows: 19 spins, all pairs, a coupling a bond (165) 67.0 against
-//    61.0 us; 18 spins of range 8 (143) 33.2 against 45.8 us, 20 spins, all pairs (179) 156 against 318.
+//  - c128, more than 160 coefficients and below 2^20 rows: 18 and 19 spins, all pairs, a coupling a bond (167, 165) 33.8
+//    against 27.9 and 67.0 against 61.0 us; 18 spins of range 8 (158) 33.2 against 45.8 us, 20 spins, all pairs (179) 134
+//    against 316.
 // None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.8, 10.1 and 38.2 us
 // against 14.4, 24.8 and 56.6.
 bool masked_is_better(const mrmf_plan_t* p, bool f32, const Tile& t, const WindowCost& c) {
@@ -2032,7 +2057,7 @@ bool masked_is_better(const mrmf_plan_t* p, bool f32, const Tile& t, const Windo
         if (d == 3) return false;
     if (t.P_U == 1 && c.coefs + 8 * c.fills + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0) >= 56.0) return true;
     if (f32) return false;
-    return (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) || (c.coefs > 150 && p->D < (1 << 20));
+    return (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) || (c.coefs > 160 && p->D < (1 << 20));
 }
 
 // no form was asked for, and no knob that only the masked and list forms have

@@ -195,6 +195,7 @@ RULE = {
     "18 spins 1/2, range 4, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 4, True, True), True, True),
     "16 spins 1/2, all pairs": (lambda: pairs([W.spin_site(1)] * 16, 15), True, True),
     "18 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 17, True), False, True),
+    "18 spins 1/2, range 8, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 8, True, True), True, True),
     "20 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 20, 19, True), True, True),
     "10 spins 1, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(2)] * 10, 9, True), True, True),
     "10 spins 3/2": (lambda: pairs([W.spin_site(3)] * 10, 1, ring=True), True, True),
@@ -216,6 +217,14 @@ def test_form_of_plans_with_many_terms(name):
         assert "window form" in E.kernel_source(m, dtype, tuning={"variant": L.MRMF_VARIANT_WINDOW})
 
 
+
+
+@pytest.mark.parametrize("spins,copies", [("232222332322", 3), ("121221212121212", 6)])
+def test_copies_of_varied_sites(spins, copies):
+    """Tile by rule of two rings of about a million rows: above the tile a spin 3/2 is not unrolled, a spin 1/2 is."""
+    m = pairs([W.spin_site(int(c)) for c in spins], 1, ring=True)
+    src = E.kernel_source(m, L.MRMF_DTYPE_Z)
+    assert int(re.search(r"(\d+) unrolled copies", src).group(1)) == copies
 
 @pytest.mark.parametrize("n,z,c", [(18, 1, 1), (19, 2, 1), (20, 2, 2)])
 def test_passes_by_the_size_of_the_vector(n, z, c):
