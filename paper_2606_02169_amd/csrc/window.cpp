@@ -323,7 +323,10 @@ std::string WinGen::source(WindowCost* cost) {
         std::string cond;
         double uconst = 1.0;
         bool utab = false, never = false;
-        for (auto so : {std::make_pair(c.a, c.opa), std::make_pair(c.b, c.opb)})
+        // the lower site first, however the term lists them: the conditions are sorted by their text, and in the other
+        // order the scalars of many bonds spill (all pairs of 16 spins 1/2, 164 instead of 16)
+        const std::pair<int, int> sa(c.a, c.opa), sb(c.b, c.opb);
+        for (auto so : {std::min(sa, sb), std::max(sa, sb)})
             if (uni(so.first)) {
                 const std::string e = nonzero(so.first, so.second, "n" + num(so.first));
                 if (e == "false") never = true;
