@@ -2050,12 +2050,18 @@ namespace {
 //  - c128, more than 160 coefficients and below 2^20 rows: 18 and 19 spins, all pairs, a coupling a bond (167, 165) 33.8
 //    against 27.9 and 67.0 against 61.0 us; 18 spins of range 8 (158) 33.2 against 45.8 us, 20 spins, all pairs (179) 134
 //    against 316.
+//  - The Chebyshev step, whose two more vectors leave a block less room: a set-up of 42 (16 spins 1/2, power law, 55: 12.7
+//    against 11.0 us; range 2 and a coupling a bond, 48: 7.1 against 6.3; 8 spins 3/2, 44: 5.5 against 5.1; below, 14
+//    spins, all pairs, 41: 8.2 against 8.3), and below 2^20 rows more than 100 gathers a copy (18 spins, all pairs, 109: 32.8
+//    against 29.4 us; 19 spins of range 6, 59: 47.8 against 56.9).
 // None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.8, 10.1 and 38.2 us
 // against 14.4, 24.8 and 56.6.
-bool masked_is_better(const mrmf_plan_t* p, bool f32, const Tile& t, const WindowCost& c) {
+bool masked_is_better(const mrmf_plan_t* p, bool f32, bool epi, const Tile& t, const WindowCost& c) {
     for (int d : p->d)
         if (d == 3) return false;
-    if (t.P_U == 1 && c.coefs + 8 * c.fills + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0) >= 56.0) return true;
+    const double setup = c.coefs + 8 * c.fills + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0);
+    if (t.P_U == 1 && setup >= (epi ? 42.0 : 56.0)) return true;
+    if (epi && c.gathers > 100 && p->D < 1 << 20) return true;
     if (f32) return false;
     return (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) || (c.coefs > 160 && p->D < (1 << 20));
 }
@@ -2101,7 +2107,7 @@ std::string spec_source(const mrmf_plan_t* p, int dtype, Tile* tl_out, SpecGeom*
                 WindowCost cost;
                 const std::string one = window_pass(p, passes[i], &geo->tiles[i], &rows, &cost);
                 geo->block[i] = static_cast<int>(round_up(rows, 64));
-                const bool other = i == 0 && cfg.variant == kVariantAuto && masked_is_better(p, f32, tl, cost);
+                const bool other = i == 0 && cfg.variant == kVariantAuto && masked_is_better(p, f32, epi, tl, cost);
                 src = one.empty() || other ? "" : src + one;
             }
             if (!src.empty()) {

@@ -235,6 +235,17 @@ def test_passes_by_the_size_of_the_vector(n, z, c):
         assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 1}))) == 1
         assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 18}))) == 2
 
+
+@pytest.mark.parametrize("model,window", [
+    (lambda: pairs([W.spin_site(1)] * 14, 13), True), (lambda: pairs([W.spin_site(1)] * 16, 2, True, True), False),
+    (lambda: pairs([W.spin_site(1)] * 18, 17), False), (lambda: pairs([W.spin_site(1)] * 20, 19), True),
+    (lambda: pairs([W.spin_site(3)] * 8, 1, ring=True), False), (lambda: W.ferrimagnetic_ring(8), True)])
+def test_form_of_the_chebyshev_step(model, window):
+    """Its own lines of the rule, on plans whose matvec takes the window form."""
+    m = model()
+    assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z)
+    assert ("window form" in E.kernel_source(m, L.MRMF_SOURCE_CHEB)) == window
+
 @pytest.mark.parametrize("n", [20, 24, 26])
 def test_gathers_of_all_copies_are_bounded(n):
     """Couplings of all pairs: the kernel by rule does not grow with copies times channels.  720 and 1440 by the rule's
