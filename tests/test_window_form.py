@@ -71,6 +71,16 @@ def test_emulated(name):
     assert ran
 
 
+
+@pytest.mark.parametrize("name", list(MODELS))
+def test_every_shape_takes_the_form(name):
+    """None of the shapes that the emulated and the GPU test run falls back to another form."""
+    m = MODELS[name]()
+    for inner, unrolled, tuning in shapes(m):
+        for dtype in (L.MRMF_DTYPE_Z, L.MRMF_DTYPE_C):
+            src = E.kernel_source(m, dtype, inner, unrolled, tuning={"variant": L.MRMF_VARIANT_WINDOW, **tuning})
+            assert src is not None and "window form" in src, (inner, unrolled, tuning, dtype)
+
 @pytest.mark.parametrize("far", [1, 10, 11])
 def test_emulated_chebyshev_step(far):
     """One pass, and the two halves of a step."""
@@ -337,3 +347,22 @@ def test_gpu_far_pairs(name):
     scale = float(torch.view_as_real(b).abs().max())
     worst = max(float(torch.view_as_real(u - v).abs().max()) for u, v in zip(a.split(1 << 26), b.split(1 << 26)))
     assert worst <= (1e-5 if real == torch.float32 else 1e-14) * scale
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(MODELS))
+def test_gpu_runs_the_form(name):
+    """The kernel that the library builds for these shapes: specialized, of the window form, with the passes of its source."""
+    import torch
+
+    from paper_2606_02169_amd.plan import Plan
+    m = MODELS[name]()
+    for inner, unrolled, tuning in shapes(m):
+        for dtype in (torch.complex128, torch.complex64):
+            p = Plan.from_model(m)
+            p.set_kernel("specialized", inner_sites=inner, unrolled_sites=unrolled)
+            p.set_tuning(variant=2, **tuning)
+            p.prepare(dtype)
+            src, info = p.kernel_source(dtype), p.kernel_info(dtype)
+            assert "window form" in src and info["kind"] == "specialized"
+            assert (info["block"], info["super_tiles"]) == E.launch_shapes(src)[0]
