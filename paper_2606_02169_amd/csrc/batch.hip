@@ -35,8 +35,9 @@
 // Bound.  64 open chains of 8 to 16 sites (29.3 M rows, eight vectors; 10.5 GB fetched and 1.9 written, against 3.8 that
 // every vector costs once): 2.39 ms with digits, factors and skips per row (2045 vector instructions per 64 rows, two
 // waves per SIMD), 1.92 ms now, limited by the serial chain of a wave's item and by the gathers that miss the L2
-// (6.4 TB/s).  What counts is waves: at 16 per CU (128 registers; two gathers at a time, as three or four spill: 2.25 and
-// 3.4 ms) against 12, 1.92 and 2.12 ms.
+// (6.4 TB/s).  What counts is waves: at 16 per CU (128 registers, of which eight vectors spill one, with complex weights
+// and more than 64 terms 20; two gathers at a time, as three or four spill far more: 2.25 and 3.4 ms) against 12, 1.92 and
+// 2.12 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -56,15 +57,15 @@ constexpr int kBatchMaxBlock = 512;
 constexpr int kBatchPoolMax = 2048;    // factor-table entries of one lattice (LDS)
 constexpr int kBatchTileWords = 4096;  // 8-byte words of the LDS tile (32 KB): at most 4096 / nvec rows
 constexpr int kBatchRmaxCands = 4;     // tile-row limits R_max = (64, 128, 256, 512) * 8 / nvec
-constexpr int kBatchMaxTerms = 128;    // terms (channels + diagonal) of one lattice, held in LDS
-constexpr int kBatchMaxParams = 128;   // couplings of one lattice, held in LDS
+constexpr int kBatchTermSets = 2;      // terms of one lattice, 64 to a set: one to a lane
+constexpr int kBatchMaxTerms = 64 * kBatchTermSets;  // channels and diagonal terms
+constexpr int kBatchMaxParams = 128;   // couplings of one lattice: no more than it has terms
 constexpr int kBatchGather = 2;        // gathers issued together
 
 struct alignas(16) BLat {
     int32_t N, n_chan, n_diag, theta_off;
-    int32_t D, term_off, site_off, n_params;
-    int32_t pool_off, pool_n, pad0, pad1;
-    int64_t x_off, pad2;
+    int32_t term_off, site_off, pool_off, pool_n;
+    int64_t x_off, pad;
     int32_t item_beg[kBatchRmaxCands];    // per R_max candidate: first item of the lattice
     int32_t part_beg[kBatchRmaxCands];    // the same count of items per eighth of a lattice (rounded up)
     int32_t low_rows[kBatchRmaxCands];    // T
@@ -74,7 +75,7 @@ struct alignas(16) BLat {
     int32_t n_local[kBatchRmaxCands];     // channels whose source lies in the tile (a prefix of the list)
     int32_t n_ldiag[kBatchRmaxCands];     // diagonal terms of the T rows' digits alone (a prefix of the list)
 };
-static_assert(sizeof(BLat) == 192, "BLat layout");
+static_assert(sizeof(BLat) == 176, "BLat layout");
 
 // n / m for n < 2^31 is umulhi(2 n, mul) >> shift (mul = ceil(2^(31 + shift) / m), shift = ceil(log2 m))
 struct BDiv {
@@ -103,7 +104,6 @@ struct BatchArgs {
     const BTerm* term;   // channels and diagonal terms of every lattice
     const float* pool;   // factor tables of every lattice
     int32_t n_lat;
-    int32_t all_real;
     int32_t shared;  // every lattice reads its input rows from the one block at the start of X; items tile-major
 };
 
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kBatchMaxBlock, 4) void k_batch(BatchArgs A, const 
     const auto first_item = [&](int l) { return parts ? A.lat[l].part_beg[rc] : A.lat[l].item_beg[rc]; };
     int lb = -1;
     // the current lattice's descriptor, kept in scalar registers (every field is block-uniform)
-    int32_t N = 0, n_chan = 0, n_diag = 0, D = 0, T = 1, ks = 0, n_loc = 0, n_ld = 0, chunk = 1, nch = 1, dp = 1;
+    int32_t N = 0, n_chan = 0, n_diag = 0, T = 1, ks = 0, n_loc = 0, n_ld = 0, chunk = 1, nch = 1, dp = 1;
     const float2* xb = X;
     float2* yb = Y;
     BSite site{};  // lane i: site i
@@ -313,7 +313,6 @@ __global__ __launch_bounds__(kBatchMaxBlock, 4) void k_batch(BatchArgs A, const 
             N = __builtin_amdgcn_readfirstlane(L->N);
             n_chan = __builtin_amdgcn_readfirstlane(L->n_chan);
             n_diag = __builtin_amdgcn_readfirstlane(L->n_diag);
-            D = __builtin_amdgcn_readfirstlane(L->D);
             T = __builtin_amdgcn_readfirstlane(L->low_rows[rc]);
             ks = __builtin_amdgcn_readfirstlane(L->low_sites[rc]);
             chunk = __builtin_amdgcn_readfirstlane(L->chunk[rc]);
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(kBatchMaxBlock, 4) void k_batch(BatchArgs A, const 
             for (int q = 0; q < kSets; ++q) left[q] = todo[q];
             float v[kBatchGather][NP][PW], acc[NP][PW];
             float cr[kBatchGather], ci[kBatchGather];  // by rows
-            static_assert(kSets <= 2, "up to two sets of terms");
+            static_assert(kSets <= kBatchTermSets && kBatchTermSets == 2, "the last set is the first or the second");
             {
                 // diagonal: the low digits' sum, then the other terms
                 float ar[NV], ai[NV];
@@ -704,7 +703,6 @@ mrmf::BatchArgs batch_args(const mrmf_batch_t* b, const void* d_ws) {
     a.term = reinterpret_cast<const mrmf::BTerm*>(w + b->off_term);
     a.pool = reinterpret_cast<const float*>(w + b->off_pool);
     a.n_lat = b->n;
-    a.all_real = b->all_real ? 1 : 0;
     a.shared = b->shared ? 1 : 0;
     return a;
 }
@@ -785,8 +783,6 @@ mrmf_status create(int32_t n, const mrmf_plan* plans, int32_t nvec, bool groups,
         }
         b->dims.emplace_back(p->d.begin(), p->d.end());
         L.N = p->N;
-        L.n_params = p->n_params;
-        L.D = static_cast<int32_t>(p->D);
         L.theta_off = th;
         L.x_off = off;
         L.site_off = static_cast<int32_t>(sites.size());

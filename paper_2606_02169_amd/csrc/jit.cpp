@@ -1951,7 +1951,6 @@ void window_passes(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, bool ep
     // gathers and LDS reads in flight: 2 x 4 gathers of a c128 copy are 32 registers, and 4 + 4 measured best or
     // within 2 % of 6 + 6 and 8 + 8 (18-site ring 138 against 140 us); 8 c64 gathers take as many
     w.group = cfg.group > 0 ? cfg.group : f32 ? 8 : 4;
-    w.lds_group = w.group;
     // Sweep: an eighth per XCD (10 million c128 rows 138 against 151 us), windows where the vector is far beyond the
     // 256 MB Infinity Cache (60 million: 1038 against 1103 us); there the prefetch of the next super-tile, which takes
     // its memory bandwidth from the gathers that the block waits for, costs as well (1061 against 1014 us).

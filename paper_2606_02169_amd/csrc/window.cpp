@@ -849,7 +849,7 @@ std::string WinGen::source(WindowCost* cost) {
             }
             int n = 0;
             for (const Stat& s : stat[u.j]) {
-                if (n && n % w.lds_group == 0) fence();
+                if (n && n % w.group == 0) fence();
                 ++n;
                 body << "    { const C s = lb[" << s.addr << " + " << s.src * CS << "u]; " << ar << " += " << s.coef << " * s.x; "
                      << ai << " += " << s.coef << " * s.y; }\n";
@@ -872,10 +872,10 @@ std::string WinGen::source(WindowCost* cost) {
         if (w.mode == kPassSet || w.mode == kPassAdd) {
             const std::string add = w.mode == kPassAdd ? "yv" + J : "";
             body << "    { C out; out.x = " << ar << (add.empty() ? "" : " + " + add + ".x") << "; out.y = " << ai
-                 << (add.empty() ? "" : " + " + add + ".y") << "; " << (w.keep_y ? "STK" : "ST") << "(out, ys, voff, " << so << "); }\n";
+                 << (add.empty() ? "" : " + " + add + ".y") << "; ST(out, ys, voff, " << so << "); }\n";
         } else {
             body << "    { C np; np.x = ea * " << ar << " + eb * x" << J << ".x + eg * yv" << J << ".x; np.y = ea * " << ai << " + eb * x"
-                 << J << ".y + eg * yv" << J << ".y;\n      " << (w.keep_y ? "STK" : "ST") << "(np, ys, voff, " << so << ");\n";
+                 << J << ".y + eg * yv" << J << ".y;\n      ST(np, ys, voff, " << so << ");\n";
             if (w.mode == kPassCheb)
                 body << "      C na; na.x = av" << J << ".x + ecr * np.x - eci * np.y; na.y = av" << J
                      << ".y + ecr * np.y + eci * np.x;\n      ST(na, as, voff, " << so << ");\n";
@@ -916,22 +916,20 @@ std::string window_prelude(bool f32, bool wide) {
         o << "#define RS(p) __builtin_amdgcn_make_buffer_rsrc((void*)(p), (short)0, 0x7fffffff, 0x00020000)\n"
           << "#define LD(rs, vo, so) __builtin_bit_cast(C, __builtin_amdgcn_raw_buffer_load_b" << bits
           << "(RS((rs) + (so)), (int)(vo), 0, 0))\n"
-          << "#define STA(v, rs, vo, so, aux) __builtin_amdgcn_raw_buffer_store_b" << bits
-          << "(__builtin_bit_cast(U, (v)), RS((rs) + (so)), (int)(vo), 0, aux)\n";
+          << "#define ST(v, rs, vo, so) __builtin_amdgcn_raw_buffer_store_b" << bits
+          << "(__builtin_bit_cast(U, (v)), RS((rs) + (so)), (int)(vo), 0, 2)\n";
     } else {
         // the store's offset goes into the VGPR operand and its scalar offset is the constant 0: with a register
         // scalar offset the compiler inserts no wait state between a 128-bit store and a following VALU write of its
         // data registers, and the stored value was then observed to be overwritten
         o << "#define LD(rs, vo, so) __builtin_bit_cast(C, __builtin_amdgcn_raw_buffer_load_b" << bits
           << "((rs), (int)(vo), (int)(so), 0))\n"
-          << "#define STA(v, rs, vo, so, aux) __builtin_amdgcn_raw_buffer_store_b" << bits
-          << "(__builtin_bit_cast(U, (v)), (rs), (int)((unsigned)(vo) + (unsigned)(so)), 0, aux)\n";
+          << "#define ST(v, rs, vo, so) __builtin_amdgcn_raw_buffer_store_b" << bits
+          << "(__builtin_bit_cast(U, (v)), (rs), (int)((unsigned)(vo) + (unsigned)(so)), 0, 2)\n";
     }
     o << "#ifndef MRMF_GROUP_FENCE\n"
       << "#define MRMF_GROUP_FENCE(a, b) __asm__ __volatile__(\"\" : \"+v\"(a), \"+v\"(b) : : \"memory\")\n"
       << "#endif\n"
-      << "#define ST(v, rs, vo, so) STA(v, rs, vo, so, 2)\n"   // non-temporal
-      << "#define STK(v, rs, vo, so) STA(v, rs, vo, so, 0)\n"
       << "__device__ __forceinline__ R uniform_of(R v) {\n";
     if (f32)
         o << "  return __builtin_bit_cast(R, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));\n}\n";

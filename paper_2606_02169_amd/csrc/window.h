@@ -25,12 +25,10 @@ struct WindowPass {
     int mode = kPassSet;
     bool f32 = false, wide = false;
     int sched = 0;        // MRMF_SCHED_*
-    int group = 8;        // gathers of a copy issued together
-    int lds_group = 6;    // LDS reads issued together
+    int group = 8;        // gathers of a copy issued together, and LDS reads
     int waves = 0;        // > 0: ask the compiler for at least this many waves per SIMD
     int64_t dbuf_bytes = 49152;  // the staged rows are double-buffered while that takes no more LDS than this
     bool prefetch = true;  // the rows of the next super-tile are requested while the current one is computed
-    bool keep_y = false;  // y is stored with the default cache policy (a later pass reads it), else non-temporal
     std::string name, tag;  // kernel name; suffix of the pass's constants
 };
 
