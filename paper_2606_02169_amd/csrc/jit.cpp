@@ -1879,7 +1879,11 @@ std::vector<char> varied_sites(const mrmf_plan_t* p) {
 // below that it cost as much as it gave.  An unrolled site of varied factors takes a little off a c128 tile's score: its
 // copies have coefficients of their own and share none of their gathers (12 sites of spins 1 and 3/2 in a ring, 1.7
 // million rows: two spins 3/2 unrolled 37.9 us, none 26.5).  Not where memory bounds the sweep and a larger super-tile
-// counts for more (15 mixed sites, 191 million rows: 4470 us with them, 5460 without).
+// counts for more (15 mixed sites, 191 million rows: 4470 us with them, 5460 without).  In c64 so
+// does a single copy of more than 320 rows, whose blocks of six and more waves leave part of a CU's wave slots empty (12
+// sites of spins 1/2 to 3/2, 3 x 10^5 rows: 576 rows 9.1 us, 144 in four copies 6.4, the masked form 7.2; 11 sites of
+// spins 1 and 3/2, 6 x 10^5 rows: 432 rows 10.6 us, in three copies 7.4, the masked form 9.0); from 3 x 10^5
+// rows on, as smaller lattices would only take fewer rows in one copy (2 x 10^5: 432 rows 4.9 us, 144 rows 5.5).
 //
 // Of the tiles with several copies, those whose copies gather at no more than kWindowGathers places in all in the first
 // pass (half the global channels a copy: the two of a bond exclude each other).  Beyond that the kernel only gets longer:
@@ -1932,7 +1936,7 @@ bool window_tile(const mrmf_plan_t* p, const KernelCfg& cfg, bool f32, Tile* tl)
             const double R = double(T * t.P_U), tiles = double(p->D) / R;
             int nv = top && varied[0] ? 1 : 0;
             for (int s = t.k_u; s < t.k_in; ++s) nv += varied[s];
-            const double score = -wV * nv + wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
+            const double score = -wV * nv - (f32 && t.P_U == 1 && T > 320 && p->D >= 300000 ? 0.1 : 0.0) + wE * std::log(double(T) / double(round_up(T, 64))) - wT * std::fabs(std::log2(T / 128.0)) -
                                  wR * std::fabs(std::log2(R / R0)) - wN * std::max(0.0, std::log2(768.0 / tiles));
             if (score < best - 1e-9 || (score <= best + 1e-9 && T == best_T)) continue;
             best_T = T;

@@ -236,6 +236,14 @@ def test_copies_of_varied_sites(spins, copies):
     src = E.kernel_source(m, L.MRMF_DTYPE_Z)
     assert int(re.search(r"(\d+) unrolled copies", src).group(1)) == copies
 
+
+@pytest.mark.parametrize("spins,rows,copies", [("23223223322", 432, 3), ("312312312312", 144, 4), ("2222222222", 243, 1)])
+def test_c64_tiles_of_one_copy(spins, rows, copies):
+    """Tile by rule in c64: one copy of many rows is not taken where there is a tile of several."""
+    m = pairs([W.spin_site(int(c)) for c in spins], 1)
+    src = E.kernel_source(m, L.MRMF_DTYPE_C)
+    assert re.search(r"(\d+) rows per block, (\d+) unrolled copies", src).groups() == (str(rows), str(copies))
+
 @pytest.mark.parametrize("n,z,c", [(18, 1, 1), (19, 2, 1), (20, 2, 2)])
 def test_passes_by_the_size_of_the_vector(n, z, c):
     """All pairs of spins 1/2: a second launch from vectors of 8 MB on (18 spins of c128 are 4 MB), unless asked for."""
