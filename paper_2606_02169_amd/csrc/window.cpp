@@ -657,21 +657,19 @@ std::string WinGen::source(WindowCost* cost) {
         cost->varying += l.varying;
         cost->tabled += l.tabled;
     }
-    std::ostringstream cb, cp, cv;
-    size_t at = 0;
-    for (size_t e = 0; e < ne; ++e) {
-        cb << (e ? ", " : "") << at;
-        for (const auto& u : entries[e]) {
-            cp << (at ? ", " : "") << u.first;
-            cv << (at ? ", " : "") << lit(u.second, f32);
-            ++at;
+    // the couplings and values of an entry's addend u at [u * ne + entry]; -1: it has fewer
+    size_t width = 0;
+    for (const auto& e : entries) width = std::max(width, e.size());
+    std::ostringstream cp, cv;
+    for (size_t u = 0; u < width; ++u)
+        for (size_t e = 0; e < ne; ++e) {
+            const bool in = u < entries[e].size();
+            cp << (u + e ? ", " : "") << (in ? entries[e][u].first : -1);
+            cv << (u + e ? ", " : "") << lit(in ? entries[e][u].second : 0.0, f32);
         }
-    }
-    if (ne > 0) {
-        o << "__constant__ int " << name("CB") << "[" << ne + 1 << "] = {" << cb.str() << ", " << at << "};\n"
-          << "__constant__ int " << name("CP") << "[" << std::max<size_t>(1, at) << "] = {" << (at ? cp.str() : "0") << "};\n"
-          << "__constant__ R " << name("CV") << "[" << std::max<size_t>(1, at) << "] = {" << (at ? cv.str() : "0") << "};\n";
-    }
+    if (width > 0)
+        o << "__constant__ int " << name("CP") << "[" << width * ne << "] = {" << cp.str() << "};\n"
+          << "__constant__ R " << name("CV") << "[" << width * ne << "] = {" << cv.str() << "};\n";
     std::ostringstream body;
     const bool use_lds = any_static || need_x;
     const bool dbuf = use_lds && 2 * PU * CS * SZ <= w.dbuf_bytes;
@@ -688,11 +686,21 @@ std::string WinGen::source(WindowCost* cost) {
          << "  const unsigned r = act ? tid : 0u;\n"
          << "  const unsigned ra = act ? tid : " << T << "u;\n"
          << "  const unsigned OOB = 0x80000000u;\n";
-    if (ne > 0)
-        body << "  for (unsigned k = tid; k < " << ne << "u; k += " << block << "u) {\n"
-             << "    R s = (R)0;\n"
-             << "    for (int u = " << name("CB") << "[k]; u < " << name("CB") << "[k + 1u]; ++u) s += theta[" << name("CP")
-             << "[u]] * " << name("CV") << "[u];\n    ut[k] = s;\n  }\n";
+    // The tables.  A thread works all its entries out before it stores the first, so their loads are in flight together: one
+    // entry after another, a chain of three loads each, was what a short launch waited for (8 spins 3/2 in a chain of
+    // different couplings, four rounds of 64 threads: 4.8 -> 4.0 us in c128, 4.7 -> 3.8 in c64; a chain of 12 spins 1/2, one
+    // round: 3.5 -> 3.2; from 10^7 rows up no difference).
+    if (ne > 0) {
+        body << "  R us[" << cost->fills << "];\n#pragma unroll\n  for (unsigned i = 0; i < " << cost->fills << "u; ++i) {\n"
+             << "    const unsigned k = tid + i * " << block << "u < " << ne << "u ? tid + i * " << block << "u : " << ne - 1
+             << "u;\n    (void)k;\n    R s = (R)0;\n";
+        if (width > 0)
+            body << "#pragma unroll " << kWindowSum << "\n    for (unsigned u = 0; u < " << width * ne << "u; u += " << ne
+                 << "u) { const int p = " << name("CP") << "[u + k]; const R t = theta[p < 0 ? 0 : p] * " << name("CV")
+                 << "[u + k]; s = p < 0 ? s : s + t; }\n";
+        body << "    us[i] = s;\n  }\n#pragma unroll\n  for (unsigned i = 0; i < " << cost->fills << "u; ++i)\n    if (tid + i * " << block
+             << "u < " << ne << "u) ut[tid + i * " << block << "u] = us[i];\n";
+    }
     if (use_lds)
         body << "  for (unsigned i = tid; i < " << (dbuf ? 2 : 1) * PU << "u; i += " << block << "u) { const C z = {(R)0, (R)0}; xl[i * "
              << CS << "u + " << T << "u] = z; }\n";

@@ -11,6 +11,7 @@ namespace mrmf {
 
 constexpr int64_t kWindowLds = 163840;  // LDS of a compute unit: the staged rows and the tables of the uniform digits
 constexpr int kWindowTab = 1024;        // most entries of those tables
+constexpr int kWindowSum = 8;           // addends of an entry whose loads a thread issues together
 
 // What a pass does with the rows it computes (H': the pass's terms).
 constexpr int kPassSet = 0;       // y = H' x

@@ -264,6 +264,23 @@ def test_form_of_the_chebyshev_step(model, window):
     assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z)
     assert ("window form" in E.kernel_source(m, L.MRMF_SOURCE_CHEB)) == window
 
+
+@pytest.mark.parametrize("spin,bonds", [(1, 1), (3, 1), (3, 3), (1, 8), (3, 9), (2, 20)])
+def test_tables_with_many_addends(spin, bonds):
+    """Entries of the tables of the uniform digits that are a sum over `bonds` couplings: below, at and above the
+    number that is read together, in one round of the block and in several."""
+    terms, theta = [], []
+    for k in range(5 * bonds):
+        terms += W.xxz_bond_terms(k % 5, k % 5 + 1, 2 * k, 2 * k + 1)
+        theta += [1.0 + 0.01 * k, 0.8 - 0.02 * k]
+    m = W.Model([W.spin_site(spin)] * 6, terms, np.array(theta))
+    for dtype in (np.complex128, np.complex64):
+        x = state(m, dtype)
+        for inner, unrolled in ((2, 0), (2, 1), (3, 0)):
+            _, y = E.run_passes(m, x, inner=inner, unrolled=unrolled, tuning={"variant": L.MRMF_VARIANT_WINDOW})
+            assert rel_err(y, mf.matvec(m, x.astype(np.complex128))) <= TOL[dtype] * bonds
+
+
 @pytest.mark.parametrize("n", [20, 24, 26])
 def test_gathers_of_all_copies_are_bounded(n):
     """Couplings of all pairs: the kernel by rule does not grow with copies times channels.  720 and 1440 by the rule's
