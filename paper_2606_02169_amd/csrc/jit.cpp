@@ -2041,32 +2041,34 @@ namespace {
 // lattices in c128 and c64: rings and squares of range 1 to 8, power laws, couplings of all pairs, one coupling for all
 // bonds or one a bond, spins 1/2 to 5/2 and modes of 4 to 8 levels, 10^3 to 5 x 10^7 rows.
 //  - One copy, so that a block does one or two super-tiles: what it works out before the first one counts.  From a set-up
-//    of 56 on (a coefficient 1, a round of table entries 8, a varying gather 1, from 2^18 rows on 2.5): 16 spins 1/2, range
-//    4 and a coupling a bond (88) 8.9 against 7.6 us, all pairs (160) 14.4 against 10.7; 8 spins 3/2, range 2 (82) 6.6
-//    against 5.2 us; six modes of 8 levels (100) 9.0 against 6.6 us; 12 spins around a mode of 65 levels (66) 9.2 against
-//    7.3 us.  Below: 16 spins, all pairs, one coupling (41) 10.0 against 10.4 us; 12 spins around a mode of 21 levels
-//    (28) 4.8 against 5.8.
+//    of 56 on (a coefficient 1, the first round of table entries 8 and another one 6, a varying gather 1, from 2^18 rows on
+//    2.5): 16 spins 1/2, range 4 and a coupling a bond (84) 8.5 against 7.9 us, all pairs (155) 13.7 against 11.2; 8 spins
+//    3/2, all pairs (82) 6.9 against 6.3 us; 12 spins around a mode of 65 levels (58) 9.1 against 7.7 us.  Below: 16 spins,
+//    all pairs, one coupling (33) 9.4 against 10.8 us; 12 spins around a mode of 21 levels (28) 4.8 against 6.1.
 //  - c128 and every gather with a factor that varies, a quarter of them from tables: from 13 gathers on their values no
-//    longer fit in registers.  10 spins 3/2 of range 2 (24 gathers) 30.2 against 25.7 us, 11 modes of 5 levels (13) 926
-//    against 789; below, a ring of 10 such spins (11) 15.4 against 18.4 us.  Spins 1/2 around a mode have no tables
-//    (14 of them, 65 levels, 20 gathers: 20.3 against 21.5 us).
-//  - c128, more than 160 coefficients and below 2^20 rows: 18 and 19 spins, all pairs, a coupling a bond (167, 165) 33.8
-//    against 27.9 and 67.0 against 61.0 us; 18 spins of range 8 (158) 33.2 against 45.8 us, 20 spins, all pairs (179) 134
-//    against 316.
-//  - The Chebyshev step, whose two more vectors leave a block less room: a set-up of 42 (16 spins 1/2, power law, 55: 12.7
-//    against 11.0 us; range 2 and a coupling a bond, 48: 7.1 against 6.3; 8 spins 3/2, 44: 5.5 against 5.1; below, 14
-//    spins, all pairs, 41: 8.2 against 8.3), and below 2^20 rows more than 100 gathers a copy (18 spins, all pairs, 109: 32.8
-//    against 29.4 us; 19 spins of range 6, 59: 47.8 against 56.9).
-// None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.8, 10.1 and 38.2 us
-// against 14.4, 24.8 and 56.6.
+//    longer fit in registers.  10 spins 3/2 of range 2 (24 gathers) 30.4 against 27.0 us, 11 modes of 5 levels (13) 926
+//    against 789; below, a ring of 10 such spins (11) 16.1 against 18.7 us.  Spins 1/2 around a mode have no tables
+//    (14 of them, 65 levels, 20 gathers: 20.8 against 22.4 us).
+//  - c128, more than 160 coefficients, below 2^20 rows and the bonds site by site: 18 and 19 spins, all pairs, a coupling a
+//    bond (167, 165) 34.9 against 30.1 and 65.2 against 63.8 us; 18 spins of range 8 (158) 31.9 against 47.7 us, 20 spins,
+//    all pairs (179) 131 against 317.  The list form gathers in the order of the bonds: with the same pairs by distance,
+//    where one site's gathers are far apart in time, it takes 50.6 and 118 us against 34.0 and 71.3.
+//  - The Chebyshev step, whose two more vectors leave a block less room: a set-up of 42 (16 spins 1/2, power law, 47: 11.7
+//    against 11.1 us; range 2 and a coupling a bond, 46: 6.9 against 6.3; below, 8 spins 3/2, 38: 5.1 against 5.2; 12 spins,
+//    power law, 37: 6.3 against 7.2), and from 2^18 to 2^20 rows more than 100 gathers a copy (18 spins, all pairs, 125: 34.8
+//    against 31.6 us; 19 spins of range 6, 59: 38.5 against 55.9; 16 spins, all pairs, 105: 10.6 against 13.0).
+// None of it with a spin 1, where the masked form is slow: all pairs of 8, 10 and 12 of them 6.4, 10.2 and 40.4 us
+// against 14.7, 25.2 and 58.8.
 bool masked_is_better(const mrmf_plan_t* p, bool f32, bool epi, const Tile& t, const WindowCost& c) {
     for (int d : p->d)
         if (d == 3) return false;
-    const double setup = c.coefs + 8 * c.fills + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0);
+    const double setup = c.coefs + (c.fills > 0 ? 2 + 6 * c.fills : 0) + c.varying * (p->D >= 1 << 18 ? 2.5 : 1.0);
     if (t.P_U == 1 && setup >= (epi ? 42.0 : 56.0)) return true;
-    if (epi && c.gathers > 100 && p->D < 1 << 20) return true;
+    if (epi && c.gathers > 100 && p->D >= 1 << 18 && p->D < 1 << 20) return true;
     if (f32) return false;
-    return (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) || (c.coefs > 160 && p->D < (1 << 20));
+    if (c.varying == c.gathers && c.varying > 12 && 4 * c.tabled >= c.varying) return true;
+    return c.coefs > 160 && p->D < 1 << 20 &&
+           std::is_sorted(p->chans.begin(), p->chans.end(), [](const DevChan& x, const DevChan& y) { return x.a < y.a; });
 }
 
 // no form was asked for, and no knob that only the masked and list forms have

@@ -190,10 +190,12 @@ def test_tile_beyond_lds_takes_the_masked_form():
     assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z, inner=2, unrolled=0)
 
 
-def pairs(sites, reach, per_bond=False, ring=False):
-    """Couplings of sites up to `reach` apart: one pair (J_xy, J_z) for all bonds, or one a bond."""
+def pairs(sites, reach, per_bond=False, ring=False, by_site=False):
+    """Couplings of sites up to `reach` apart: one pair (J_xy, J_z) for all bonds, or one a bond; bonds by distance, or
+    site by site."""
     n, terms, theta = len(sites), [], [1.0, 0.8]
-    for b, (i, j) in enumerate((i, (i + k) % n) for k in range(1, reach + 1) for i in range(n) if ring or i + k < n):
+    bonds = [(i, (i + k) % n) for k in range(1, reach + 1) for i in range(n) if ring or i + k < n]
+    for b, (i, j) in enumerate(sorted(bonds) if by_site else bonds):
         terms += W.xxz_bond_terms(i, j, 2 * b, 2 * b + 1) if per_bond else W.xxz_bond_terms(i, j, 0, 1)
     return W.Model(sites, terms, np.array(theta * (b + 1) if per_bond else theta))
 
@@ -204,7 +206,9 @@ RULE = {
     "16 spins 1/2, range 4, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 16, 4, True, True), False, False),
     "18 spins 1/2, range 4, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 4, True, True), True, True),
     "16 spins 1/2, all pairs": (lambda: pairs([W.spin_site(1)] * 16, 15), True, True),
-    "18 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 17, True), False, True),
+    "18 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 17, True), True, True),
+    "18 spins 1/2, all pairs site by site, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 17, True, by_site=True),
+                                                                False, True),
     "18 spins 1/2, range 8, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 18, 8, True, True), True, True),
     "20 spins 1/2, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(1)] * 20, 19, True), True, True),
     "10 spins 1, all pairs, a coupling a bond": (lambda: pairs([W.spin_site(2)] * 10, 9, True), True, True),
@@ -257,7 +261,8 @@ def test_passes_by_the_size_of_the_vector(n, z, c):
 @pytest.mark.parametrize("model,window", [
     (lambda: pairs([W.spin_site(1)] * 14, 13), True), (lambda: pairs([W.spin_site(1)] * 16, 2, True, True), False),
     (lambda: pairs([W.spin_site(1)] * 18, 17), False), (lambda: pairs([W.spin_site(1)] * 20, 19), True),
-    (lambda: pairs([W.spin_site(3)] * 8, 1, ring=True), False), (lambda: W.ferrimagnetic_ring(8), True)])
+    (lambda: pairs([W.spin_site(1)] * 16, 15), True), (lambda: pairs([W.spin_site(3)] * 8, 1, ring=True), True),
+    (lambda: W.ferrimagnetic_ring(8), True)])
 def test_form_of_the_chebyshev_step(model, window):
     """Its own lines of the rule, on plans whose matvec takes the window form."""
     m = model()
