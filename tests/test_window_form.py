@@ -15,16 +15,19 @@ from tests.helpers import rel_err
 
 TOL = {np.complex128: 1e-12, np.complex64: 2e-5}
 
+
 def real_random(seed, n_sites=5, max_dim=2000, **kw):
     """Random mixed spin/boson lattice with real weights (the form's condition)."""
     m = W.random_model(np.random.default_rng(seed), n_sites=n_sites, max_dim=max_dim, n_params=3, n_terms=14, **kw)
     terms = [W.Term(t.site_a, t.op_a, t.site_b, t.op_b, t.param, complex(t.w).real) for t in m.terms]
     return W.Model(m.sites, terms, m.theta, name=f"real_random_{seed}")
 
+
 def diagonal_only():
     sites = [W.spin_site(1), W.spin_site(2), W.boson_site(4)]
     return W.Model(sites, [W.Term(0, W.OP_Z, 2, W.OP_Z, 0, 0.7), W.Term(1, W.OP_Z2, -1, W.OP_Z, 1, -1.3)],
                    np.array([0.9, 1.1]))
+
 
 MODELS = {
     "spin half ring": lambda: W.configs.staggered_xxz_ring([1] * 8),
@@ -42,11 +45,14 @@ MODELS = {
 SHAPES = [(0, -1, {}), (1, 0, {}), (2, 1, {"schedule": 1, "load_group": 2}), (1, 2, {"addressing": 1}),
           (2, 0, {"far_pass": 10}), (1, 1, {"far_pass": 11, "addressing": 1}), (2, 0, {"unroll_top": 1, "schedule": 2})]
 
+
 def shapes(m):
     return [s for s in SHAPES if s[0] + max(0, s[1]) + s[2].get("unroll_top", 0) <= len(m.sites)]
 
+
 def state(m, dtype=np.complex128):
     return W.random_state(m.dim, np.random.default_rng(8)).astype(dtype)
+
 
 @pytest.mark.parametrize("name", list(MODELS))
 def test_emulated(name):
@@ -64,6 +70,7 @@ def test_emulated(name):
             assert np.all(np.isfinite(y))
     assert ran
 
+
 @pytest.mark.parametrize("name", list(MODELS))
 def test_every_shape_takes_the_form(name):
     """None of the shapes that the emulated and the GPU test run falls back to another form."""
@@ -72,6 +79,7 @@ def test_every_shape_takes_the_form(name):
         for dtype in (L.MRMF_DTYPE_Z, L.MRMF_DTYPE_C):
             src = E.kernel_source(m, dtype, inner, unrolled, tuning={"variant": L.MRMF_VARIANT_WINDOW, **tuning})
             assert src is not None and "window form" in src, (inner, unrolled, tuning, dtype)
+
 
 @pytest.mark.parametrize("far", [1, 10, 11])
 def test_emulated_chebyshev_step(far):
@@ -85,6 +93,7 @@ def test_emulated_chebyshev_step(far):
     assert passes == (1 if far == 1 else 2)
     assert rel_err(p, want) <= 1e-12 and rel_err(a, acc + c * want) <= 1e-12
 
+
 def test_chosen_by_rule():
     """Real weights take the window form unless another form or one of its knobs is asked for; complex ones never do."""
     m = W.ferrimagnetic_ring(6)
@@ -95,6 +104,7 @@ def test_chosen_by_rule():
                                        W.Term(0, W.OP_LOWER, -1, W.OP_Z, 0, -0.3j)], m.theta)
     assert "window form" not in E.kernel_source(cplx, L.MRMF_DTYPE_Z, tuning={"variant": 2})
 
+
 def swapped_chain(n):
     """Open chain of spins 1/2 whose bonds list the lowering of their first site first."""
     terms = []
@@ -102,12 +112,14 @@ def swapped_chain(n):
         terms += [W.Term(i, W.OP_LOWER, i + 1, W.OP_RAISE, 0, 0.5), W.Term(i, W.OP_RAISE, i + 1, W.OP_LOWER, 0, 0.5)]
     return W.Model([W.spin_site(1)] * n, terms, np.array([0.9]))
 
+
 # Bonds whose two channels read 2^31 bytes or more apart: no 32-bit lane offset reaches both, so neither can share the
 # other's gather.  At 27 spins of c128 (28 of c64) for a closing bond, one site more for the first bond of a chain.
 FAR_PAIRS = {"ring 27 c128": (lambda: W.heisenberg_chain(27, periodic=True), L.MRMF_DTYPE_Z, (7, 3)),
              "ring 28 c64": (lambda: W.heisenberg_chain(28, periodic=True), L.MRMF_DTYPE_C, (0, -1)),
              "ferrimagnet 22 c64": (lambda: W.ferrimagnetic_ring(22), L.MRMF_DTYPE_C, (0, -1)),
              "lower first 28 c128": (lambda: swapped_chain(28), L.MRMF_DTYPE_Z, (0, -1))}
+
 
 @pytest.mark.parametrize("name", list(FAR_PAIRS))
 def test_far_pairs_read_each_channel_once(name):
@@ -122,6 +134,7 @@ def test_far_pairs_read_each_channel_once(name):
     for copy, bases in at.items():
         assert len(set(bases)) == len(bases), (copy, sorted(bases))
 
+
 def test_far_pairs_emulated():
     """Rows of the ring of 27 spins 1/2 (2 GiB) whose closing bond is gathered, against the oracle: super-tiles all over
     the vector, site 0 up and down."""
@@ -134,6 +147,7 @@ def test_far_pairs_emulated():
     assert rows.size == 8 << (inner + unrolled) and rows[-1] >= m.dim // 2
     assert rel_err(y[rows], mf.matvec(m, x, rows=rows)) <= 1e-12
 
+
 def lds_bytes(src):
     """LDS of each pass: the staged rows and the tables of the uniform digits."""
     f32 = "typedef float R" in src
@@ -141,12 +155,14 @@ def lds_bytes(src):
     return [sum(one[t] * int(n) for t, n in re.findall(r"__shared__ (C|R) \w+\[(\d+)\]", body))
             for body in src.split("extern \"C\" __global__")[1:]]
 
+
 # lattices whose large sites leave tiles of many rows only: (lattice, default tile beyond the 160 KB of LDS in c128)
 LARGE_SITES = {
     "16 and 250 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(15), W.boson_site(249), W.spin_site(2)]),
     "12 and 256 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(11), W.boson_site(255), W.spin_site(3)]),
     "15 and 200 levels": lambda: chain_of([W.spin_site(1)] * 10 + [W.boson_site(14), W.boson_site(199), W.spin_site(3)]),
 }
+
 
 def chain_of(sites):
     """Open chain with one exchange coupling per bond."""
@@ -156,12 +172,14 @@ def chain_of(sites):
                   W.Term(i, W.OP_Z, i + 1, W.OP_Z, i, 1.0)]
     return W.Model(sites, terms, np.linspace(0.6, 1.2, len(sites) - 1))
 
+
 @pytest.mark.parametrize("name", list(LARGE_SITES))
 @pytest.mark.parametrize("dtype", [L.MRMF_DTYPE_Z, L.MRMF_DTYPE_C, L.MRMF_SOURCE_CHEB])
 def test_tile_by_rule_fits_in_lds(name, dtype):
     src = E.kernel_source(LARGE_SITES[name](), dtype)
     assert "window form" in src
     assert max(lds_bytes(src)) <= 163840
+
 
 def test_tile_beyond_lds_takes_the_masked_form():
     """A shape asked for whose rows do not fit in LDS: the masked form, as for any plan that the window form does not take."""
@@ -171,6 +189,7 @@ def test_tile_beyond_lds_takes_the_masked_form():
         assert src is not None and "window form" not in src
     assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z, inner=2, unrolled=0)
 
+
 def pairs(sites, reach, per_bond=False, ring=False, by_site=False):
     """Couplings of sites up to `reach` apart: one pair (J_xy, J_z) for all bonds, or one a bond; bonds by distance, or
     site by site."""
@@ -179,6 +198,7 @@ def pairs(sites, reach, per_bond=False, ring=False, by_site=False):
     for b, (i, j) in enumerate(sorted(bonds) if by_site else bonds):
         terms += W.xxz_bond_terms(i, j, 2 * b, 2 * b + 1) if per_bond else W.xxz_bond_terms(i, j, 0, 1)
     return W.Model(sites, terms, np.array(theta * (b + 1) if per_bond else theta))
+
 
 # (lattice, window form by rule in c128, in c64): both sides of each line of the rule
 RULE = {
@@ -200,6 +220,7 @@ RULE = {
     "8 spins 3/2, range 2": (lambda: pairs([W.spin_site(3)] * 8, 2, ring=True), False, False),
 }
 
+
 @pytest.mark.parametrize("name", list(RULE))
 def test_form_of_plans_with_many_terms(name):
     model, z, c = RULE[name]
@@ -209,6 +230,7 @@ def test_form_of_plans_with_many_terms(name):
         # asked for, it is taken all the same
         assert "window form" in E.kernel_source(m, dtype, tuning={"variant": L.MRMF_VARIANT_WINDOW})
 
+
 @pytest.mark.parametrize("spins,copies", [("232222332322", 3), ("121221212121212", 6)])
 def test_copies_of_varied_sites(spins, copies):
     """Tile by rule of two rings of about a million rows: above the tile a spin 3/2 is not unrolled, a spin 1/2 is."""
@@ -216,12 +238,14 @@ def test_copies_of_varied_sites(spins, copies):
     src = E.kernel_source(m, L.MRMF_DTYPE_Z)
     assert int(re.search(r"(\d+) unrolled copies", src).group(1)) == copies
 
+
 @pytest.mark.parametrize("spins,rows,copies", [("23223223322", 432, 3), ("312312312312", 144, 4), ("2222222222", 243, 1)])
 def test_c64_tiles_of_one_copy(spins, rows, copies):
     """Tile by rule in c64: one copy of many rows is not taken where there is a tile of several."""
     m = pairs([W.spin_site(int(c)) for c in spins], 1)
     src = E.kernel_source(m, L.MRMF_DTYPE_C)
     assert re.search(r"(\d+) rows per block, (\d+) unrolled copies", src).groups() == (str(rows), str(copies))
+
 
 @pytest.mark.parametrize("n,z,c", [(18, 1, 1), (19, 2, 1), (20, 2, 2)])
 def test_passes_by_the_size_of_the_vector(n, z, c):
@@ -231,6 +255,7 @@ def test_passes_by_the_size_of_the_vector(n, z, c):
         assert len(E.launch_shapes(E.kernel_source(m, dtype))) == passes
         assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 1}))) == 1
         assert len(E.launch_shapes(E.kernel_source(m, dtype, tuning={"far_pass": 18}))) == 2
+
 
 @pytest.mark.parametrize("model,window", [
     (lambda: pairs([W.spin_site(1)] * 14, 13), True), (lambda: pairs([W.spin_site(1)] * 16, 2, True, True), False),
@@ -242,6 +267,7 @@ def test_form_of_the_chebyshev_step(model, window):
     m = model()
     assert "window form" in E.kernel_source(m, L.MRMF_DTYPE_Z)
     assert ("window form" in E.kernel_source(m, L.MRMF_SOURCE_CHEB)) == window
+
 
 @pytest.mark.parametrize("spin,bonds", [(1, 1), (3, 1), (3, 3), (1, 8), (3, 9), (2, 20)])
 def test_tables_with_many_addends(spin, bonds):
@@ -258,6 +284,7 @@ def test_tables_with_many_addends(spin, bonds):
             _, y = E.run_passes(m, x, inner=inner, unrolled=unrolled, tuning={"variant": L.MRMF_VARIANT_WINDOW})
             assert rel_err(y, mf.matvec(m, x.astype(np.complex128))) <= TOL[dtype] * bonds
 
+
 @pytest.mark.parametrize("n", [20, 24, 26])
 def test_gathers_of_all_copies_are_bounded(n):
     """Couplings of all pairs: the kernel by rule does not grow with copies times channels.  720 and 1440 by the rule's
@@ -267,6 +294,7 @@ def test_gathers_of_all_copies_are_bounded(n):
         first = E.kernel_source(m, dtype).split('extern "C" __global__')[1]
         gathers = re.findall(r"const C s(\d+)_\d+ = LD", first)
         assert len(set(gathers)) > 1 and len(gathers) <= most * 4 / 3
+
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(LARGE_SITES))
@@ -286,6 +314,7 @@ def test_gpu_large_sites(name):
         ref = mf.matvec(m, x.astype(np.complex128), rows=rows)
         assert rel_err(y[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= TOL[dtype]
 
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(MODELS))
 def test_gpu(name):
@@ -303,6 +332,7 @@ def test_gpu(name):
             print(name, inner, unrolled, tuning, dtype.__name__, flush=True)
             y = p.matvec(th, torch.from_numpy(x).cuda()).cpu().numpy()
             assert rel_err(y, mf.matvec(m, x.astype(np.complex128))) <= TOL[dtype]
+
 
 @pytest.mark.gpu
 def test_gpu_two_passes_of_the_square_lattice():
@@ -322,6 +352,7 @@ def test_gpu_two_passes_of_the_square_lattice():
     rows = np.unique(np.random.default_rng(2).choice(m.dim, 2000, replace=False)).astype(np.int64)
     ref = mf.matvec(m, x.cpu().numpy(), rows=rows)
     assert rel_err(y2[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= 1e-12
+
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(FAR_PAIRS))
@@ -345,6 +376,7 @@ def test_gpu_far_pairs(name):
     scale = float(torch.view_as_real(b).abs().max())
     worst = max(float(torch.view_as_real(u - v).abs().max()) for u, v in zip(a.split(1 << 26), b.split(1 << 26)))
     assert worst <= (1e-5 if real == torch.float32 else 1e-14) * scale
+
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", list(MODELS))
